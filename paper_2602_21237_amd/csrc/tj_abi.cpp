@@ -2234,6 +2234,21 @@ static int sort_body(int key_type, const void* keys_in, const int32_t* rids_in, 
     x.bufs.rid[BUF_A][0] = rids_out;
     x.out_is_a = true;  // buffer A is the output (the budget plan's key ranges change that)
 
+    if (n <= (uint64_t)LEAF_CAP) {
+        // one block sorts it all: one launch and one wait, where the passes'
+        // tables, range probe and read-back cost about 40 us more
+        x.stats.key_ranges = 1;
+        x.stats.leaves = 1;
+        x.stats.bytes_read = x.stats.bytes_written = n * row_bytes(key_type, true);
+        TJ_CK(x.timed(F_LEAF_SORT, 2 * n * row_bytes(key_type, true), [&] {
+            return launch_small_sort(key_type, keys_in, rids_in, (uint32_t)n, keys_out, rids_out, x.st);
+        }));
+        TJ_CK(hipStreamSynchronize(x.st));
+        x.stats.workspace_used = workspace_bytes;
+        if (stats) *stats = x.stats;
+        return TJ_OK;
+    }
+
     // buffer B (workspace) is free until the second pass: the training
     // scratch, then the learned pass's bucket ids
     auto train = [&]() -> int {
@@ -2361,6 +2376,27 @@ static int join_body(int key_type, const void* r_keys, const int32_t* r_rids, ui
     x.bufs.key[BUF_IN][1] = s_keys;
     x.bufs.rid[BUF_IN][0] = r_rids;
     x.bufs.rid[BUF_IN][1] = s_rids;
+
+    if (n_r + n_s <= (uint64_t)LEAF_CAP) {
+        // one block joins it all (see sort_body); the count comes back through
+        // pinned memory that the kernel writes
+        uint64_t* total = (uint64_t*)pinned_down(sizeof(uint64_t));
+        if (!total) return TJ_E_HIP;
+        const uint16_t flags = (g_debug_flags.load() & TJ_DEBUG_FORCE_REORDER) ? LEAF_FORCE_REORDER : 0;
+        TJ_CK(x.timed(mat ? F_LEAF_MAT : F_LEAF_COUNT, (n_r + n_s) * row_bytes(key_type, mat), [&] {
+            return launch_small_join(key_type, mat, (uint32_t)n_r, (uint32_t)n_s, flags, x.bufs, total, out_r, out_s,
+                                     capacity, x.st);
+        }));
+        TJ_CK(hipStreamSynchronize(x.st));
+        *count = *total;
+        x.stats.key_ranges = 1;
+        x.stats.leaves = 1;
+        x.stats.bytes_read = (n_r + n_s) * row_bytes(key_type, mat);
+        x.stats.bytes_written = mat ? std::min(*count, capacity) * 8 : 0;
+        x.stats.workspace_used = workspace_bytes;
+        if (stats) *stats = x.stats;
+        return mat && *count > capacity ? TJ_E_CAPACITY : TJ_OK;
+    }
 
     // buffer B is free until the second pass (see tj_sort)
     auto train = [&]() -> int {

@@ -227,6 +227,12 @@ hipError_t launch_leaf_join(int key_bytes, bool wide, bool materialize, const Le
                             uint32_t n, BufSet bufs, uint64_t* status, uint32_t* ticket,
                             uint64_t* total, uint32_t* err, int32_t* out_r, int32_t* out_s,
                             uint64_t capacity, hipStream_t st);
+// Whole inputs of at most LEAF_CAP rows in one block: the sort of keys[n] / rids[n], and the join of the BUF_IN
+// columns (rn and sn rows), whose pair count goes to *total (device-visible memory) in either mode.
+hipError_t launch_small_sort(int key_bytes, const void* keys, const int32_t* rids, uint32_t n, void* out_k,
+                             int32_t* out_r, hipStream_t st);
+hipError_t launch_small_join(int key_bytes, bool materialize, uint32_t rn, uint32_t sn, uint16_t flags, BufSet bufs,
+                             uint64_t* total, int32_t* out_r, int32_t* out_s, uint64_t capacity, hipStream_t st);
 hipError_t launch_cross(const CrossDesc* units, uint32_t n, uint64_t total, BufSet bufs,
                         const uint64_t* status, int32_t* out_r, int32_t* out_s, uint64_t capacity,
                         hipStream_t st);

@@ -1179,14 +1179,16 @@ hipError_t launch_expand(int32_t* dst, const int32_t* src, uint64_t n, uint64_t 
 // the all-ones key and the largest positions, so they sort last.
 // ---------------------------------------------------------------------------
 constexpr int LBINS = 256, LSTRIDE = LBINS + 1;
-// Leaf block shape per key word: 32-bit keys use 512 threads x 16 rows (57 KB
-// of LDS, two blocks per CU); 64-bit keys 1024 threads x 8 rows (97 KB, one
-// block of 16 waves per CU).
-template <typename KW> struct LeafShape {
-    static constexpr int NT = sizeof(KW) == 4 ? 512 : 1024;
-    static constexpr int KI = LEAF_CAP / NT;
+// Block shape of a leaf of at most C rows, per key word. C = LEAF_CAP: 32-bit
+// keys use 512 threads x 16 rows (57 KB of LDS, two blocks per CU); 64-bit keys
+// 1024 threads x 8 rows (97 KB, one block of 16 waves per CU). The smaller
+// capacities are for inputs of one block, where nothing but the block's own
+// latency counts: 4 rows a thread.
+template <typename KW, int C = LEAF_CAP> struct LeafShape {
+    static constexpr int NT = C < LEAF_CAP ? C / 4 : sizeof(KW) == 4 ? 512 : 1024;
+    static constexpr int KI = C / NT;
     static constexpr int NW = NT / 64;
-    static constexpr int NBB = sizeof(KW) == 4 ? 12 : 13;  // bin bits of block_bin_sort
+    static constexpr int NBB = C == 1024 ? 10 : C == 4096 ? 12 : sizeof(KW) == 4 ? 12 : 13;  // bin bits of block_bin_sort
     static constexpr int NBIN = 1 << NBB;
     // LDS words shared by the bin counters and the LSD digit counters
     static constexpr int CNT_WORDS = NBIN > NW * LSTRIDE ? NBIN : NW * LSTRIDE;
@@ -1227,10 +1229,10 @@ struct LdsPad {
 };
 // join blocks read their sorted items in blocked order (padded layout); the
 // sort blocks read them across lanes (plain layout)
-template <typename KW> using KeyLds = LdsPad<KW, LeafShape<KW>::KI, 1>;
-template <typename KW> using IdxLds = LdsPad<uint16_t, LeafShape<KW>::KI, 2>;
-template <typename KW> using KeyPlain = LdsPad<KW, LeafShape<KW>::KI, 0>;
-template <typename KW> using IdxPlain = LdsPad<uint16_t, LeafShape<KW>::KI, 0>;
+template <typename KW, int C = LEAF_CAP> using KeyLds = LdsPad<KW, LeafShape<KW, C>::KI, 1>;
+template <typename KW, int C = LEAF_CAP> using IdxLds = LdsPad<uint16_t, LeafShape<KW, C>::KI, 2>;
+template <typename KW, int C = LEAF_CAP> using KeyPlain = LdsPad<KW, LeafShape<KW, C>::KI, 0>;
+template <typename KW, int C = LEAF_CAP> using IdxPlain = LdsPad<uint16_t, LeafShape<KW, C>::KI, 0>;
 
 // Largest bin block_bin_sort accepts: the exact ranking inside a bin costs
 // every item of the bin one pass over it.
@@ -1431,6 +1433,63 @@ __device__ __forceinline__ bool block_check_order(KA lds_key, IA lds_idx, uint32
     return ok;
 }
 
+// Stable sort of a leaf block's items (see block_bin_sort for their layout) into
+// lds_key / lds_idx: one counting pass, or digit passes when a bin is too full.
+// reload() gives the items their keys and indices again.
+template <typename KW, int NT, int KI, int NBB, typename KA, typename IA, class Reload>
+__device__ __forceinline__ void block_sort(KW (&key)[KI], uint16_t (&idx)[KI], int bits, uint32_t n, KA lds_key,
+                                           IA lds_idx, uint32_t* cnt, uint32_t* tmp, uint64_t* tmp64, Reload&& reload)
+{
+    if (bits > 0 &&
+        block_bin_sort<KW, NT, KI, NBB>(key, bits, n, lds_key, lds_idx, cnt, tmp)) {
+        // sorted in one counting pass
+    } else if (sizeof(KW) == 8 && bits > 32) {
+        // Wide keys: sort by the top 32 bits of the relative key only (4 digit
+        // passes instead of up to 8). The order is final unless two rows share
+        // those 32 bits; short runs of such ties are then put in order by one
+        // thread each (insertion sort on the full key, which keeps equal keys in
+        // input order); many ties fall back to the full sort.
+        const int H = bits - 32;
+        block_lsd_sort<KW, NT, KI>(key, idx, 32, lds_key, lds_idx, cnt, tmp, H);
+        uint32_t ties = 0;
+#pragma unroll
+        for (int r = 0; r < KI; r++) {
+            const uint32_t q = threadIdx.x * KI + r;
+            if (q > 0 && q < n && (lds_key[q] >> H) == (lds_key[q - 1] >> H)) ties++;
+        }
+        ties = (uint32_t)block_sum64<NT>((uint64_t)ties, tmp64);
+        if (ties > 0 && ties <= 256) {
+#pragma unroll
+            for (int r = 0; r < KI; r++) {
+                const uint32_t q = threadIdx.x * KI + r;
+                const bool head = q + 1 < n && (lds_key[q] >> H) == (lds_key[q + 1] >> H) &&
+                                  (q == 0 || (lds_key[q] >> H) != (lds_key[q - 1] >> H));
+                if (!head) continue;
+                uint32_t e = q + 1;
+                while (e < n && (lds_key[e] >> H) == (lds_key[q] >> H)) e++;
+                for (uint32_t i = q + 1; i < e; i++) {  // stable insertion sort of [q, e)
+                    const KW kv = lds_key[i];
+                    const uint16_t iv = lds_idx[i];
+                    uint32_t j = i;
+                    while (j > q && lds_key[j - 1] > kv) {
+                        lds_key[j] = lds_key[j - 1];
+                        lds_idx[j] = lds_idx[j - 1];
+                        j--;
+                    }
+                    lds_key[j] = kv;
+                    lds_idx[j] = iv;
+                }
+            }
+            lds_barrier();
+        } else if (ties > 256) {
+            reload();
+            block_lsd_sort<KW, NT, KI>(key, idx, bits, lds_key, lds_idx, cnt, tmp);
+        }
+    } else {
+        block_lsd_sort<KW, NT, KI>(key, idx, bits, lds_key, lds_idx, cnt, tmp);
+    }
+}
+
 template <typename K, typename KW>
 __global__ __launch_bounds__(LeafShape<KW>::NT)
 __attribute__((amdgpu_waves_per_eu(4))) void k_leaf_sort(const LeafDesc* __restrict__ leaves,
@@ -1475,60 +1534,15 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_leaf_sort(const LeafDesc* __restr
     uint16_t idx[KI];
 #pragma unroll
     for (int r = 0; r < KI; r++) idx[r] = (uint16_t)((w * KI + r) * 64 + l);
-    if (L.bits > 0 &&
-        block_bin_sort<KW, NT, KI, LeafShape<KW>::NBB>(key, (int)L.bits, L.rn, lds_key, lds_idx, cnt, tmp)) {
-        // sorted in one counting pass
-    } else if (sizeof(KW) == 8 && L.bits > 32) {
-        // Wide keys: sort by the top 32 bits of the relative key only (4 digit
-        // passes instead of up to 8). The order is final unless two rows share
-        // those 32 bits; short runs of such ties are then put in order by one
-        // thread each (insertion sort on the full key, which keeps equal keys in
-        // input order); many ties fall back to the full sort.
-        const int H = (int)L.bits - 32;
-        block_lsd_sort<KW, NT, KI>(key, idx, 32, lds_key, lds_idx, cnt, tmp, H);
-        uint32_t ties = 0;
+    block_sort<KW, NT, KI, LeafShape<KW>::NBB>(key, idx, (int)L.bits, L.rn, lds_key, lds_idx, cnt, tmp, tmp64, [&]() {
 #pragma unroll
         for (int r = 0; r < KI; r++) {
-            const uint32_t q = threadIdx.x * KI + r;
-            if (q > 0 && q < L.rn && (lds_key[q] >> H) == (lds_key[q - 1] >> H)) ties++;
+            const uint32_t q = (w * KI + r) * 64 + l;
+            const K v = ld_clamp(src_k, q, L.rn);
+            key[r] = q < L.rn ? (KW)(ord_of(v) - L.base) : (KW)~(KW)0;
+            idx[r] = (uint16_t)q;
         }
-        ties = (uint32_t)block_sum64<NT>((uint64_t)ties, tmp64);
-        if (ties > 0 && ties <= 256) {
-#pragma unroll
-            for (int r = 0; r < KI; r++) {
-                const uint32_t q = threadIdx.x * KI + r;
-                const bool head = q + 1 < L.rn && (lds_key[q] >> H) == (lds_key[q + 1] >> H) &&
-                                  (q == 0 || (lds_key[q] >> H) != (lds_key[q - 1] >> H));
-                if (!head) continue;
-                uint32_t e = q + 1;
-                while (e < L.rn && (lds_key[e] >> H) == (lds_key[q] >> H)) e++;
-                for (uint32_t i = q + 1; i < e; i++) {  // stable insertion sort of [q, e)
-                    const KW kv = lds_key[i];
-                    const uint16_t iv = lds_idx[i];
-                    uint32_t j = i;
-                    while (j > q && lds_key[j - 1] > kv) {
-                        lds_key[j] = lds_key[j - 1];
-                        lds_idx[j] = lds_idx[j - 1];
-                        j--;
-                    }
-                    lds_key[j] = kv;
-                    lds_idx[j] = iv;
-                }
-            }
-            lds_barrier();
-        } else if (ties > 256) {
-#pragma unroll
-            for (int r = 0; r < KI; r++) {
-                const uint32_t q = (w * KI + r) * 64 + l;
-                const K v = ld_clamp(src_k, q, L.rn);
-        key[r] = q < L.rn ? (KW)(ord_of(v) - L.base) : (KW)~(KW)0;
-                idx[r] = (uint16_t)q;
-            }
-            block_lsd_sort<KW, NT, KI>(key, idx, (int)L.bits, lds_key, lds_idx, cnt, tmp);
-        }
-    } else {
-        block_lsd_sort<KW, NT, KI>(key, idx, (int)L.bits, lds_key, lds_idx, cnt, tmp);
-    }
+    });
     // Keys go out first. The bucket may be sorted in place (its rows already
     // sit in the output columns), so its row ids are all read (coalesced, into
     // the now free key array) before any of them is overwritten.
@@ -1571,6 +1585,113 @@ hipError_t launch_leaf_sort(int key_bytes, bool wide, const LeafDesc* leaves, ui
         else
             hipLaunchKernelGGL((k_leaf_sort<int64_t, uint32_t>), grid, block, 0, st, leaves, bufs, (int64_t*)out_k, out_r);
     }
+    return hipGetLastError();
+}
+
+// Smallest and largest ordinal of the block's rows, from each thread's own.
+template <int NT>
+__device__ __forceinline__ void block_minmax64(uint64_t& lo, uint64_t& hi, uint64_t* tmp)
+{
+    constexpr int NW = NT / 64;
+    lo = wave_min64(lo);
+    hi = wave_max64(hi);
+    if ((threadIdx.x & 63) == 0) tmp[threadIdx.x / 64] = lo;
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < NW; i++) lo = tmp[i] < lo ? tmp[i] : lo;
+    lds_barrier();
+    if ((threadIdx.x & 63) == 0) tmp[threadIdx.x / 64] = hi;
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < NW; i++) hi = tmp[i] > hi ? tmp[i] : hi;
+    lds_barrier();
+}
+
+// ---------------------------------------------------------------------------
+// sort of an input that fits one block: the key range, the sort and the output
+// in one launch, so that the call waits once. The time is the block's own
+// chain of latencies (two loads, about a dozen barriers) and hardly depends on
+// the rows, so the block has few rows a thread and all its loads go out at once.
+// A call of 1000 int32 rows: 65 us with two fills, a probe, its read-back and a
+// 512 x 16 leaf, 24 us with this (about 6 us of them in the kernel).
+// ---------------------------------------------------------------------------
+template <typename K, int C>
+__global__ __launch_bounds__((LeafShape<typename std::make_unsigned<K>::type, C>::NT)) void k_small_sort(
+    const K* __restrict__ src_k, const int32_t* __restrict__ src_r, uint32_t n, K* __restrict__ out_k,
+    int32_t* __restrict__ out_r)
+{
+    using KW = typename std::make_unsigned<K>::type;
+    using SH = LeafShape<KW, C>;
+    constexpr int NT = SH::NT, KI = SH::KI, NW = SH::NW;
+    __shared__ KW lds_key_raw[C];
+    __shared__ __align__(16) uint16_t lds_idx_raw[C];
+    __shared__ int32_t lds_rid[C];
+    __shared__ uint32_t cnt[SH::CNT_WORDS];
+    __shared__ uint32_t tmp[NW];
+    __shared__ uint64_t tmp64[NW];
+    const KeyPlain<KW, C> lds_key{lds_key_raw};
+    const IdxPlain<KW, C> lds_idx{lds_idx_raw};
+    const uint32_t w = threadIdx.x / 64, l = threadIdx.x & 63;
+    K v[KI];
+    int32_t rid[KI];
+#pragma unroll
+    for (int r = 0; r < KI; r++) {
+        const uint32_t q = (w * KI + r) * 64 + l;
+        v[r] = ld_clamp(src_k, q, n);
+        rid[r] = ld_clamp(src_r, q, n);
+    }
+    uint64_t lo = ~0ull, hi = 0;  // clamped loads repeat a real row
+#pragma unroll
+    for (int r = 0; r < KI; r++) {
+        const uint64_t o = ord_of(v[r]);
+        lo = o < lo ? o : lo;
+        hi = o > hi ? o : hi;
+    }
+    block_minmax64<NT>(lo, hi, tmp64);
+    const uint64_t span = hi - lo;
+    const int bits = span ? 64 - (int)__clzll((long long)span) : 0;
+    KW key[KI];
+    uint16_t idx[KI];
+    auto load_items = [&]() {
+#pragma unroll
+        for (int r = 0; r < KI; r++) {
+            const uint32_t q = (w * KI + r) * 64 + l;
+            key[r] = q < n ? (KW)(ord_of(v[r]) - lo) : (KW)~(KW)0;
+            idx[r] = (uint16_t)q;
+        }
+    };
+    load_items();
+#pragma unroll
+    for (int r = 0; r < KI; r++) lds_rid[(w * KI + r) * 64 + l] = rid[r];
+    block_sort<KW, NT, KI, SH::NBB>(key, idx, bits, n, lds_key, lds_idx, cnt, tmp, tmp64, load_items);
+#pragma unroll
+    for (int r = 0; r < KI; r++) {
+        const uint32_t q = (w * KI + r) * 64 + l;
+        if (q < n) {
+            out_k[q] = key_of<K>(lo + (uint64_t)lds_key[q]);
+            out_r[q] = lds_rid[lds_idx[q]];
+        }
+    }
+}
+
+hipError_t launch_small_sort(int key_bytes, const void* keys, const int32_t* rids, uint32_t n, void* out_k,
+                             int32_t* out_r, hipStream_t st)
+{
+    if (n == 0) return hipSuccess;
+    if (n > (uint32_t)LEAF_CAP) return hipErrorInvalidValue;
+#define TJ_SS(K, C)                                                                                              \
+    hipLaunchKernelGGL((k_small_sort<K, C>), dim3(1), dim3(LeafShape<typename std::make_unsigned<K>::type, C>::NT), \
+                       0, st, (const K*)keys, rids, n, (K*)out_k, out_r)
+    if (key_bytes == 4) {
+        if (n <= 1024) TJ_SS(int32_t, 1024);
+        else if (n <= 4096) TJ_SS(int32_t, 4096);
+        else TJ_SS(int32_t, LEAF_CAP);
+    } else {
+        if (n <= 1024) TJ_SS(int64_t, 1024);
+        else if (n <= 4096) TJ_SS(int64_t, 4096);
+        else TJ_SS(int64_t, LEAF_CAP);
+    }
+#undef TJ_SS
     return hipGetLastError();
 }
 
@@ -1652,8 +1773,11 @@ __device__ uint64_t look_back(uint64_t* status, uint32_t slot, uint32_t* err)
     }
 }
 
-template <typename K, typename KW, bool MAT>
-__global__ __launch_bounds__(LeafShape<KW>::NT)
+// SELF (a whole input that fits one block): the leaf is `self`, whose key
+// range the block finds itself; its pairs start at 0 and their number is
+// stored to *total (in either mode). One launch then serves the whole call.
+template <typename K, typename KW, bool MAT, bool SELF = false, int C = LEAF_CAP>
+__global__ __launch_bounds__((LeafShape<KW, C>::NT))
 __attribute__((amdgpu_waves_per_eu(4))) void k_leaf_join(const LeafDesc* __restrict__ leaves,
                                                             BufSet bufs, uint64_t* __restrict__ status,
                                                             uint32_t* __restrict__ ticket,
@@ -1661,13 +1785,13 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_leaf_join(const LeafDesc* __restr
                                                             uint32_t* __restrict__ err,
                                                             int32_t* __restrict__ out_r,
                                                             int32_t* __restrict__ out_s,
-                                                            uint64_t capacity)
+                                                            uint64_t capacity, LeafDesc self)
 {
-    constexpr int NT = LeafShape<KW>::NT, KI = LeafShape<KW>::KI, NW = LeafShape<KW>::NW, C = LEAF_CAP;
+    constexpr int NT = LeafShape<KW, C>::NT, KI = LeafShape<KW, C>::KI, NW = LeafShape<KW, C>::NW;
     // (padded for the count; the materialising block keeps the plain layout:
     // the padding's address arithmetic costs it registers it does not have)
-    using KA = typename std::conditional<MAT, KeyPlain<KW>, KeyLds<KW>>::type;
-    using IA = typename std::conditional<MAT, IdxPlain<KW>, IdxLds<KW>>::type;
+    using KA = typename std::conditional<MAT, KeyPlain<KW, C>, KeyLds<KW, C>>::type;
+    using IA = typename std::conditional<MAT, IdxPlain<KW, C>, IdxLds<KW, C>>::type;
     __shared__ KW lds_key_raw[KA::size(C)];
     __shared__ __align__(16) uint16_t lds_idx_raw[IA::size(C)];
     const KA lds_key{lds_key_raw};
@@ -1681,12 +1805,14 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_leaf_join(const LeafDesc* __restr
 
     if (threadIdx.x == 0) s_unordered = 0;
     uint32_t li = blockIdx.x;
-    if (MAT) {
+    if (MAT && !SELF) {
         if (threadIdx.x == 0) s_leaf = atomicAdd(ticket, 1u);
         lds_barrier();
         li = s_leaf;
     }
-    const LeafDesc L = leaves[li];
+    LeafDesc L;
+    if constexpr (SELF) L = self;
+    else L = leaves[li];
     const uint32_t rn = L.rn, n = L.rn + L.sn;
     const K* __restrict__ rk = (const K*)bufs.key[L.buf][0] + L.kr0;
     const K* __restrict__ sk = (const K*)bufs.key[L.buf][1] + L.ks0;
@@ -1694,6 +1820,20 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_leaf_join(const LeafDesc* __restr
 
     KW key[KI];
     uint16_t idx[KI];
+    if constexpr (SELF) {
+        uint64_t lo = ~0ull, hi = 0;
+#pragma unroll
+        for (int r = 0; r < KI; r++) {
+            const uint32_t q = (w * KI + r) * 64 + l;
+            const uint32_t qc = q < n ? q : n - 1;
+            const uint64_t o = ord_of(qc < rn ? rk[qc] : sk[qc - rn]);
+            lo = o < lo ? o : lo;
+            hi = o > hi ? o : hi;
+        }
+        block_minmax64<NT>(lo, hi, tmp64);
+        L.base = lo;
+        L.bits = (uint16_t)(hi > lo ? 64 - (int)__clzll((long long)(hi - lo)) : 0);
+    }
     auto load_items = [&]() {
 #pragma unroll
         for (int r = 0; r < KI; r++) {
@@ -1783,12 +1923,14 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_leaf_join(const LeafDesc* __restr
     }
     if (!MAT) {
         const uint64_t c = block_sum64<NT>((uint64_t)local, tmp64);
-        if (threadIdx.x == 0 && c) atomicAdd((unsigned long long*)total, (unsigned long long)c);
+        if (SELF && threadIdx.x == 0) *total = c;
+        if (!SELF && threadIdx.x == 0 && c) atomicAdd((unsigned long long*)total, (unsigned long long)c);
         return;
     }
     uint32_t ltot;
     uint32_t ex = block_excl_scan<NT>(local, tmp, &ltot);  // barriers: run tables all read
-    if (threadIdx.x == 0) status_store(&status[li + 1], ST_AGG | (uint64_t)ltot);
+    if (SELF && threadIdx.x == 0) *total = ltot;
+    if (!SELF && threadIdx.x == 0) status_store(&status[li + 1], ST_AGG | (uint64_t)ltot);
     // Row ids: one coalesced load of the block's rows (R then S) into the free
     // key array, then every item picks its own from LDS.
     int32_t* lds_w = (int32_t*)lds_key_raw;
@@ -1803,7 +1945,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_leaf_join(const LeafDesc* __restr
             if (q < n) lds_w[q] = v;
         }
     }
-    if (threadIdx.x < 64) {
+    if (!SELF && threadIdx.x < 64) {
         const uint64_t excl = look_back(status, li + 1, err);
         if (threadIdx.x == 0) {
             status_store(&status[li + 1], ST_INC | (excl + ltot));
@@ -1811,7 +1953,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_leaf_join(const LeafDesc* __restr
         }
     }
     lds_barrier();
-    const uint64_t base = s_base;
+    const uint64_t base = SELF ? 0 : s_base;
     // Pair slots: R item j of a run owns E_rs + j*b .. + b (it writes out_r),
     // S item k of a run appears at E_rs + i*b + k for its run's a R items (it
     // writes out_s). Per item: first slot, and packed [side:1][slots:14][stride:14].
@@ -1914,7 +2056,7 @@ hipError_t launch_leaf_join(int key_bytes, bool wide, bool materialize, const Le
     const dim3 grid(n), block(wide ? LeafShape<uint64_t>::NT : LeafShape<uint32_t>::NT);
 #define TJ_LJ(K, KW, M)                                                                              \
     hipLaunchKernelGGL((k_leaf_join<K, KW, M>), grid, block, 0, st, leaves, bufs, status, ticket,    \
-                       total, err, out_r, out_s, capacity)
+                       total, err, out_r, out_s, capacity, LeafDesc{})
     if (key_bytes == 4) {
         if (wide) { if (materialize) TJ_LJ(int32_t, uint64_t, true); else TJ_LJ(int32_t, uint64_t, false); }
         else      { if (materialize) TJ_LJ(int32_t, uint32_t, true); else TJ_LJ(int32_t, uint32_t, false); }
@@ -1923,6 +2065,36 @@ hipError_t launch_leaf_join(int key_bytes, bool wide, bool materialize, const Le
         else      { if (materialize) TJ_LJ(int64_t, uint32_t, true); else TJ_LJ(int64_t, uint32_t, false); }
     }
 #undef TJ_LJ
+    return hipGetLastError();
+}
+
+hipError_t launch_small_join(int key_bytes, bool materialize, uint32_t rn, uint32_t sn, uint16_t flags, BufSet bufs,
+                             uint64_t* total, int32_t* out_r, int32_t* out_s, uint64_t capacity, hipStream_t st)
+{
+    const uint32_t n = rn + sn;
+    if (n == 0 || rn > (uint32_t)LEAF_CAP || n > (uint32_t)LEAF_CAP) return hipErrorInvalidValue;
+    LeafDesc self{};
+    self.rn = rn;
+    self.sn = sn;
+    self.buf = BUF_IN;
+    self.flags = flags;
+#define TJ_SJ(K, M, C)                                                                                              \
+    hipLaunchKernelGGL((k_leaf_join<K, typename std::make_unsigned<K>::type, M, true, C>), dim3(1),                 \
+                       dim3(LeafShape<typename std::make_unsigned<K>::type, C>::NT), 0, st, nullptr, bufs, nullptr, \
+                       nullptr, total, nullptr, out_r, out_s, capacity, self)
+#define TJ_SJC(K, M)                     \
+    do {                                 \
+        if (n <= 1024) TJ_SJ(K, M, 1024); \
+        else if (n <= 4096) TJ_SJ(K, M, 4096); \
+        else TJ_SJ(K, M, LEAF_CAP);      \
+    } while (0)
+    if (key_bytes == 4) {
+        if (materialize) TJ_SJC(int32_t, true); else TJ_SJC(int32_t, false);
+    } else {
+        if (materialize) TJ_SJC(int64_t, true); else TJ_SJC(int64_t, false);
+    }
+#undef TJ_SJC
+#undef TJ_SJ
     return hipGetLastError();
 }
 
