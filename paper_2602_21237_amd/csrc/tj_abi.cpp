@@ -38,11 +38,6 @@ namespace {
 constexpr uint64_t ALIGN = 256;
 constexpr int TABLE_TIERS = 9;
 constexpr uint64_t TARGET_CHUNKS = 2048;  // blocks per partition pass
-#ifndef TJ_PASS_DIGIT_BITS
-#define TJ_PASS_DIGIT_BITS MAX_DIGIT_BITS
-#endif
-// widest digit a partition pass uses (at most MAX_DIGIT_BITS)
-constexpr int PASS_DIGIT_BITS = TJ_PASS_DIGIT_BITS;
 constexpr size_t DEVICE_BATCH_MIN_SEGS = 16;  // segments of a pass before leaves are batched on the device
 // learned partitioner defaults (tj_options_t)
 constexpr uint32_t LEARNED_BUCKETS = 512;        // buckets of the learned pass: one full-width digit
@@ -57,8 +52,6 @@ static_assert((LEARNED_BUCKETS & (LEARNED_BUCKETS - 1)) == 0 && LEARNED_BUCKETS 
               "learned buckets must be one digit of the scatter");
 
 inline uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
-
-inline uint32_t nbits64(uint64_t x) { return x ? 64u - (uint32_t)__builtin_clzll(x) : 0u; }
 
 // Table capacities of one tier. A pass whose groups, chunks, scan blocks or
 // child entries exceed them runs as several launch batches.
@@ -109,6 +102,8 @@ uint64_t table_bytes(const Caps& c)
     b += align_up((uint64_t)c.units * ub, ALIGN);
     return b;
 }
+
+static_assert(sizeof(LeafDesc) % 16 == 0, "leaf tables are copied in 16-byte units");
 
 // Pinned host staging, one grow-only buffer per host thread and direction.
 // It is never freed (the process exit reclaims it), so no HIP call runs from a
@@ -204,42 +199,11 @@ uint64_t min_data_bytes(const Shape& s)
 
 const uint64_t kMaxRows = (1ull << 31) - 1;
 
-// Digit of a pass over a segment of `rows` rows whose ordinals span `span`:
-// enough digits that a child averages LEAF_CAP / 2 rows (at least 2, at most a
-// full digit), at the largest shift at which (span >> shift) + 1 digits still
-// reach that many, so a span that is not a power of two still puts them to
-// use. With `few` (a level of at most FEW_SEGS segments) a segment of at most
-// SMALL_SEG_ROWS rows (mostly a bucket crowded by a few frequent keys) takes
-// a full digit: such a level costs about its launches and read-back whatever
-// the width, and the wider digit separates the frequent keys from their
-// neighbours in fewer levels. (A level of many segments keeps the narrower
-// digit: the children's bookkeeping grows with the width.) A span of 0
-// (filtered roots of a single-key range, which still need a compaction pass)
-// gets one bit.
-constexpr uint64_t SMALL_SEG_ROWS = 16ull * LEAF_CAP;
-constexpr size_t FEW_SEGS = 64;
 // A child bucket is crowded (Seg::skew) when it holds more than SKEW_FACTOR
 // times the rows its parent's digit gave each bucket on average; at most
 // MAX_PIVOT_SEGS crowded buckets of a level are sampled for a pivot key.
 constexpr uint64_t SKEW_FACTOR = 2;
 constexpr size_t MAX_PIVOT_SEGS = 4096;
-inline void plan_digit(uint64_t span, uint64_t rows, bool few, uint32_t& shift, uint32_t& bits)
-{
-    const uint64_t want =
-        few && rows <= SMALL_SEG_ROWS
-            ? 1ull << PASS_DIGIT_BITS
-            : std::min<uint64_t>(std::max<uint64_t>((rows + LEAF_CAP / 2 - 1) / (LEAF_CAP / 2), 2),
-                                 1ull << PASS_DIGIT_BITS);
-    shift = 0;
-    for (uint32_t sh = nbits64(span); sh-- > 0;)
-        if ((span >> sh) + 1 >= want) {
-            shift = sh;
-            break;
-        }
-    while ((span >> shift) >= (1ull << PASS_DIGIT_BITS)) shift++;
-    bits = std::max<uint32_t>(1, nbits64(span >> shift));
-}
-
 // Sample rows of a relation of n rows: max(min(n, 2048), n * permille / 1000).
 inline uint64_t rmi_sample_rows(uint64_t n, uint32_t permille)
 {
@@ -448,6 +412,22 @@ void give_event(hipEvent_t e)
     t_events->push_back({dev, e});
 }
 
+// Events that the host waits for (no timing): one per thread and device.
+thread_local std::vector<std::pair<int, hipEvent_t>>* t_waits = nullptr;
+
+hipEvent_t wait_event()
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+    if (!t_waits) t_waits = new std::vector<std::pair<int, hipEvent_t>>();
+    for (auto& pe : *t_waits)
+        if (pe.first == dev) return pe.second;
+    hipEvent_t e = nullptr;
+    if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return nullptr;
+    t_waits->push_back({dev, e});
+    return e;
+}
+
 void free_thread_staging()
 {
     auto drop = [](PinnedBuf*& b) {
@@ -465,10 +445,11 @@ void free_thread_staging()
         delete t_host_vecs;
         t_host_vecs = nullptr;
     }
-    if (t_events) {
-        for (auto& pe : *t_events) (void)hipEventDestroy(pe.second);
-        delete t_events;
-        t_events = nullptr;
+    for (auto** pool : {&t_events, &t_waits}) {
+        if (!*pool) continue;
+        for (auto& pe : **pool) (void)hipEventDestroy(pe.second);
+        delete *pool;
+        *pool = nullptr;
     }
 }
 
@@ -515,6 +496,7 @@ struct Exec {
     bool learned_pass = false;      // the next partition pass is the learned one
     bool auto_probe = false;        // the next pass may hand over to the learned partitioner
     bool spec_range = false;        // the next pass's digit range comes from a sampled probe
+    bool root_probe = false;        // the next pass probes its key range and plans its digit on the device
 
     // data buffer capacities (rows per side) when the buffers live in the workspace
     uint64_t cap_r = 0, cap_s = 0;
@@ -663,6 +645,8 @@ struct Exec {
         learned_pass = false;
         const bool spec = spec_range && !filter && !learned;
         spec_range = false;
+        const bool root = root_probe && !filter && !learned && segs.size() == 1;
+        root_probe = false;
         // per segment digit choice
         struct Plan {
             uint32_t shift, bits, kb_out;
@@ -688,6 +672,10 @@ struct Exec {
             // join keys are narrowed to 4 bytes once every child spans at most
             // 2^32 ordinals; the sort writes its keys out and never narrows
             plan[i].kb_out = sh.join && write_keys && s.kb == 8 && plan[i].shift <= 32 ? 4u : s.kb;
+            if (root) {  // known once the probe has run; the tables hold any digit
+                plan[i].bits = MAX_DIGIT_BITS;
+                plan[i].kb_out = sh.join && write_keys && s.kb == 8 ? 4u : s.kb;
+            }
             if (learned) {
                 // the model's buckets are the digits; children keep their key width
                 plan[i].bits = nbits64(LEARNED_BUCKETS) - 1;
@@ -814,6 +802,8 @@ struct Exec {
                            ncb = (uint32_t)cblocks.size();
             // the launch narrows when any segment does; the others are marked wide
             uint32_t kb_out = kb_in;
+            bool one_cblock = true;
+            for (const GroupDesc& g : groups) one_cblock = one_cblock && g.ncblocks <= 1;
             bool mixed = false;
             for (uint32_t gi = 0; gi < ng; gi++) kb_out = std::min(kb_out, plan[gseg[gi]].kb_out);
             for (uint32_t gi = 0; gi < ng; gi++)
@@ -821,29 +811,69 @@ struct Exec {
                     groups[gi].flags |= GROUP_WIDE;
                     mixed = true;
                 }
-            {
-                // the three tables go out from one pinned staging buffer (a copy
-                // from pageable memory would block the host until it is done)
-                const size_t gb = ng * sizeof(GroupDesc), cb = nc * sizeof(ChunkDesc),
-                             bb = ncb * sizeof(CBlockDesc);
-                char* pin = (char*)pinned_up(gb + cb + bb, 0);
-                const char* hg = (const char*)groups.data();
-                const char* hc = (const char*)chunks.data();
-                const char* hb = (const char*)cblocks.data();
-                if (pin) {
-                    std::memcpy(pin, hg, gb);
-                    std::memcpy(pin + gb, hc, cb);
-                    std::memcpy(pin + gb + cb, hb, bb);
-                    hg = pin;
-                    hc = pin + gb;
-                    hb = pin + gb + cb;
-                }
-                TJ_CK(hipMemcpyAsync(d_groups, hg, gb, hipMemcpyHostToDevice, st));
-                TJ_CK(hipMemcpyAsync(d_chunks, hc, cb, hipMemcpyHostToDevice, st));
-                TJ_CK(hipMemcpyAsync(d_cblocks, hb, bb, hipMemcpyHostToDevice, st));
+            // device leaves of a range share one key width (one leaf launch)
+            if (dev_ok && (mixed || (dev_leaves && dev_kb != kb_out))) TJ_RET(demote_device_leaves());
+            const uint32_t nrec = child / (uint32_t)nside;
+            // What the host reads back, in pinned memory that the kernels write:
+            // a header, then the child records unless the device batches the leaves.
+            struct Header {
+                uint64_t lo, hi;   // root: the key range
+                uint64_t miss;     // a row lay outside the sampled range
+                uint64_t sum[5];   // device batching summary
+            };
+            Header* hdr = nullptr;
+            if (!t_noalloc) {
+                hdr = (Header*)pinned_down(sizeof(Header) + (dev_ok ? 0 : nrec * sizeof(ChildRec)));
+                if (!hdr) return TJ_E_HIP;
             }
-            TJ_CK(launch_fill_u64(d_gmin, child, ~0ull, st));
-            TJ_CK(launch_fill_u64(d_gmax, child, 0ull, st));
+            // The tables go out together, packed from the first one's place on
+            // (each is a multiple of 16 bytes from the next), with the
+            // regions this launch needs cleared.
+            static_assert(sizeof(GroupDesc) % 8 == 0 && sizeof(ChunkDesc) % 8 == 0 && sizeof(CBlockDesc) % 16 == 0,
+                          "tables are copied in 16-byte units");
+            const size_t gb = align_up(ng * sizeof(GroupDesc), 16), cb = align_up(nc * sizeof(ChunkDesc), 16),
+                         bb = ncb * sizeof(CBlockDesc);
+            GroupDesc* const dg = d_groups;
+            ChunkDesc* const dc = (ChunkDesc*)((char*)d_groups + gb);
+            CBlockDesc* const db = (CBlockDesc*)((char*)d_groups + gb + cb);
+            StageArgs sa{};
+            char* pin = (char*)pinned_up(gb + cb + bb, 0);
+            if (pin) {
+                std::memcpy(pin, groups.data(), ng * sizeof(GroupDesc));
+                std::memcpy(pin + gb, chunks.data(), nc * sizeof(ChunkDesc));
+                std::memcpy(pin + gb + cb, cblocks.data(), bb);
+                sa.dst = d_groups;
+                sa.src = pin;
+                sa.n16 = (gb + cb + bb) / 16;
+            } else {
+                TJ_CK(hipMemcpyAsync(dg, groups.data(), ng * sizeof(GroupDesc), hipMemcpyHostToDevice, st));
+                TJ_CK(hipMemcpyAsync(dc, chunks.data(), nc * sizeof(ChunkDesc), hipMemcpyHostToDevice, st));
+                TJ_CK(hipMemcpyAsync(db, cblocks.data(), bb, hipMemcpyHostToDevice, st));
+            }
+            auto fill = [&](int k, uint64_t* at, uint64_t n, uint64_t v) {
+                sa.fill_p[k] = at;
+                sa.fill_n[k] = n;
+                sa.fill_v[k] = v;
+            };
+            fill(0, d_gmin, child, ~0ull);
+            fill(1, d_gmax, child, 0);
+            fill(2, d_probe + 4, 5, 0);  // batching summary and, among it, the range-miss word
+            RootArgs ra{};
+            if (root) {
+                ra.parts = (uint64_t*)d_cbsum;  // free until the scan
+                ra.nparts = probe_root_blocks(sh.n_r, sh.n_s);
+                ra.narrow = kb_out < kb_in;
+                ra.rows = sh.n_r + sh.n_s;
+                ra.hdr = &hdr->lo;
+                ra.flags = groups[0].flags;
+                const void* kb2 = sh.join ? bufs.key[BUF_IN][1] : nullptr;
+                TJ_CK(timed(F_PROBE, ra.rows * kb_in, [&] {
+                    return launch_probe_root((int)kb_in, bufs.key[BUF_IN][0], sh.n_r, kb2, sh.n_s, (uint64_t*)d_cbsum, sa, st);
+                }));
+                stats.bytes_read += ra.rows * kb_in;
+            } else {
+                TJ_CK(launch_stage(sa, st));
+            }
             uint64_t scanned = 0, written = 0;  // rows read; bytes written
             for (const GroupDesc& g : groups) {
                 scanned += g.len;
@@ -852,36 +882,63 @@ struct Exec {
                 written += (g.side ? s.sn : s.rn) * ((write_keys ? plan[sidx].kb_out : 0) + (sh.rids ? 4 : 0));
             }
             const uint64_t rb = row_bytes((int)kb_in, sh.rids);
+            uint32_t* const d_miss = (uint32_t*)(d_probe + 7);
             if (learned) {
                 // bucket ids: 2 bytes written per row by the histogram, read by the scatter
                 TJ_CK(timed(F_LHIST, scanned * (kb_in + 2), [&] {
-                    return launch_learned_hist((int)kb_in, d_chunks, nc, d_groups, bufs, d_model, bkt, d_hist,
-                                               d_gmin, d_gmax, st);
+                    return launch_learned_hist((int)kb_in, dc, nc, dg, bufs, d_model, bkt, d_hist, d_gmin, d_gmax, st);
                 }));
                 stats.bytes_written += scanned * 2;
                 stats.bytes_read += scanned * 2;
             } else {
-                uint32_t* miss = (uint32_t*)(d_probe + 7);
-                if (spec) TJ_CK(launch_fill_u64(d_probe + 7, 1, 0, st));
                 TJ_CK(timed(F_HIST, scanned * kb_in, [&] {
-                    return launch_hist((int)kb_in, d_chunks, nc, d_groups, bufs, d_hist, d_gmin, d_gmax, miss, st);
+                    return launch_hist((int)kb_in, dc, nc, dg, bufs, d_hist, d_gmin, d_gmax, d_miss,
+                                       root ? &ra : nullptr, st);
                 }));
-                if (spec) {
-                    // a row outside the sampled digit range: nothing moved yet, the
-                    // caller probes the exact range and starts again
-                    uint64_t* flag = (uint64_t*)pinned_down(sizeof(uint64_t));
-                    if (!flag) return TJ_E_HIP;
-                    TJ_CK(hipMemcpyAsync(flag, d_probe + 7, 8, hipMemcpyDeviceToHost, st));
-                    TJ_CK(hipStreamSynchronize(st));
-                    if (*flag) {
-                        stats.passes--;
-                        return TJ_RANGE_MISS;
-                    }
-                }
             }
+            ChildRec* hrec = hdr && !dev_ok ? (ChildRec*)(hdr + 1) : nullptr;
             TJ_CK(timed(F_SCAN, 0, [&] {
-                return launch_scan(d_cblocks, ncb, d_groups, ng, d_hist, d_cbsum, d_ccount, d_cstart, st);
+                return launch_scan(db, ncb, dg, ng, nside, one_cblock, d_hist, d_cbsum, d_ccount, d_cstart, d_gmin,
+                                   d_gmax, d_crec, hrec, d_miss, hdr ? &hdr->miss : nullptr, st);
             }));
+            // leaf batching reads the child records: it needs no row moved
+            BatchArgs ba{};
+            uint64_t* const d_sum = d_probe + 4;
+            if (dev_ok) {
+                ba.nseg = ng / (uint32_t)nside;
+                ba.nside = (uint32_t)nside;
+                ba.narrowing = kb_out < kb_in ? 1u : 0u;
+                ba.join = sh.join ? 1u : 0u;
+                ba.buf = dst;
+                ba.kb = kb_out;
+                ba.flags = (g_debug_flags.load() & TJ_DEBUG_FORCE_REORDER) ? LEAF_FORCE_REORDER : 0u;
+                ba.leaf_base = dev_leaves;
+                ba.leaf_cap = caps.leaves;
+                ba.out_delta = cur_out_delta;
+                TJ_CK(launch_batch_leaves(dg, d_crec, ba, d_segcount, d_leaves, d_sum, 0, st));
+                TJ_CK(launch_batch_leaves(dg, d_crec, ba, d_segcount, d_leaves, d_sum, 1, st));
+                if (hdr) TJ_CK(launch_publish(hdr->sum, d_sum, 5, st));
+            }
+            // The host waits for the scan only: it plans what follows while the
+            // scatter runs. (Without pinned memory, and before the automatic
+            // choice of the partitioner, it reads back first.)
+            hipEvent_t ready = nullptr;
+            if (hdr && !auto_probe) {
+                ready = wait_event();
+                if (!ready) return TJ_E_HIP;
+                TJ_CK(hipEventRecord(ready, st));
+            } else {
+                if (!hdr) {
+                    // (one pageable buffer holds both)
+                    hdr = (Header*)pinned_down(sizeof(Header) + (dev_ok ? 0 : nrec * sizeof(ChildRec)));
+                    TJ_CK(hipMemcpyAsync(hdr->sum, d_sum, 5 * 8, hipMemcpyDeviceToHost, st));
+                    hrec = (ChildRec*)(hdr + 1);
+                    if (!dev_ok)
+                        TJ_CK(hipMemcpyAsync(hrec, d_crec, nrec * sizeof(ChildRec), hipMemcpyDeviceToHost, st));
+                }
+                TJ_CK(hipStreamSynchronize(st));
+                if (t_noalloc) hdr->miss = hdr->sum[3];
+            }
             if (auto_probe) {
                 // The radix digit's bucket sizes decide. Every next pass
                 // narrows the digit to its bucket's own key range, so a few
@@ -891,17 +948,14 @@ struct Exec {
                 // it crowded again level after level: then the learned
                 // partitioner takes over (nothing has been scattered yet).
                 auto_probe = false;
-                std::vector<uint32_t> cnt(child);
-                TJ_CK(hipMemcpyAsync(cnt.data(), d_ccount, (size_t)child * 4, hipMemcpyDeviceToHost, st));
-                TJ_CK(hipStreamSynchronize(st));
+                if (spec && hdr->miss) {
+                    stats.passes--;
+                    return TJ_RANGE_MISS;
+                }
                 uint64_t rows = 0, largest = 0;
-                std::vector<uint64_t> per(child / nside, 0);
-                for (uint32_t gi = 0; gi < ng; gi++)
-                    for (uint32_t d = 0; d < (1u << groups[gi].bits); d++)
-                        per[groups[gi - gi % nside].child0 / nside + d] += cnt[groups[gi].child0 + d];
-                for (uint64_t c : per) {
-                    rows += c;
-                    largest = std::max(largest, c);
+                for (uint32_t i = 0; hrec && i < nrec; i++) {
+                    rows += hrec[i].rn + hrec[i].sn;
+                    largest = std::max<uint64_t>(largest, hrec[i].rn + hrec[i].sn);
                 }
                 if (AUTO_BULK_DEN * largest > rows) {
                     stats.passes--;  // histogram only
@@ -910,17 +964,34 @@ struct Exec {
             }
             if (learned) {
                 TJ_CK(timed(F_LSCATTER, scanned * (rb + 2) + written, [&] {
-                    return launch_learned_scatter((int)kb_in, sh.rids, d_chunks, nc, d_groups, d_hist, d_cbsum,
-                                                  d_cstart, bufs, bkt, st);
+                    return launch_learned_scatter((int)kb_in, sh.rids, dc, nc, dg, d_hist, d_cbsum, d_cstart, bufs, bkt, st);
                 }));
             } else {
                 TJ_CK(timed(F_SCATTER, scanned * rb + written, [&] {
-                    return launch_scatter((int)kb_in, (int)kb_out, sh.rids, write_keys, d_chunks, nc, d_groups, d_hist,
-                                          d_cbsum, d_cstart, bufs, st);
+                    return launch_scatter((int)kb_in, (int)kb_out, sh.rids, write_keys, dc, nc, dg, d_hist, d_cbsum,
+                                          d_cstart, bufs, spec ? d_miss : nullptr, st);
                 }));
             }
-            // one compact record per child (both sides folded)
-            const uint32_t nrec = child / (uint32_t)nside;
+            if (ready) TJ_CK(hipEventSynchronize(ready));
+            if (spec && hdr->miss) {
+                // a row outside the sampled digit range: nothing moved, the
+                // caller probes the exact range and starts again
+                stats.passes--;
+                return TJ_RANGE_MISS;
+            }
+            if (root) {
+                Plan& pl = plan[0];
+                plan_digit(hdr->hi - hdr->lo, ra.rows, true, pl.shift, pl.bits);
+                pl.kb_out = ra.narrow && pl.shift <= 32 ? 4u : kb_in;
+                for (uint32_t gi = 0; gi < ng; gi++) {
+                    groups[gi].base = hdr->lo;
+                    groups[gi].shift = pl.shift;
+                    groups[gi].bits = pl.bits;
+                }
+                written = 0;
+                for (const GroupDesc& g : groups)
+                    written += g.len * ((write_keys ? pl.kb_out : 0) + (sh.rids ? 4 : 0));
+            }
             // Child d of the segment whose first group is gi, with rows [r0, ..) and
             // [s0, ..) in the destination: a Seg for the sink. Its keys may have been
             // narrowed by this pass; a child with more than SKEW_FACTOR times its
@@ -956,32 +1027,10 @@ struct Exec {
                 }
                 sink(c);
             };
-            TJ_CK(launch_children(d_groups, ng, nside, d_ccount, d_gmin, d_gmax, d_crec, st));
-            // device leaves of a range share one key width (one leaf launch)
-            if (dev_ok && (mixed || (dev_leaves && dev_kb != kb_out))) TJ_RET(demote_device_leaves());
             if (dev_ok) {
-                // Batch the children into leaves on the device; the host reads back
+                // The children are batched into leaves on the device; the host reads
                 // four summary words and the children too large for a leaf.
-                BatchArgs ba{};
-                ba.nseg = ng / (uint32_t)nside;
-                ba.nside = (uint32_t)nside;
-                ba.narrowing = kb_out < kb_in ? 1u : 0u;
-                ba.join = sh.join ? 1u : 0u;
-                ba.buf = dst;
-                ba.kb = kb_out;
-                ba.flags = (g_debug_flags.load() & TJ_DEBUG_FORCE_REORDER) ? LEAF_FORCE_REORDER : 0u;
-                ba.leaf_base = dev_leaves;
-                ba.leaf_cap = caps.leaves;
-                ba.out_delta = cur_out_delta;
-                uint64_t* d_sum = d_probe + 4;  // [3] (the range-miss word) is cleared with them
-                TJ_CK(launch_fill_u64(d_sum, 5, 0, st));
-                TJ_CK(launch_batch_leaves(d_groups, d_crec, ba, d_segcount, d_leaves, d_sum, 0, st));
-                TJ_CK(launch_batch_leaves(d_groups, d_crec, ba, d_segcount, d_leaves, d_sum, 1, st));
-                uint64_t* pin = (uint64_t*)pinned_down(5 * sizeof(uint64_t));
-                if (!pin) return TJ_E_HIP;
-                TJ_CK(hipMemcpyAsync(pin, d_sum, 5 * sizeof(uint64_t), hipMemcpyDeviceToHost, st));
-                TJ_CK(hipStreamSynchronize(st));
-                const uint64_t sum[5] = {pin[0], pin[1], pin[2], pin[3], pin[4]};
+                const uint64_t sum[5] = {hdr->sum[0], hdr->sum[1], hdr->sum[2], hdr->sum[3], hdr->sum[4]};
                 const uint64_t nbig = sum[4];
                 if (!(sum[2] & BATCH_OVERFLOW) && dev_leaves + sum[0] + nbig <= caps.leaves) {
                     stats.bytes_written += written;
@@ -1015,10 +1064,14 @@ struct Exec {
                 }
                 TJ_RET(demote_device_leaves());  // this level needs the host planner
             }
-            ChildRec* rec = (ChildRec*)pinned_down((size_t)nrec * sizeof(ChildRec));
-            if (!rec) return TJ_E_HIP;
-            TJ_CK(hipMemcpyAsync(rec, d_crec, nrec * sizeof(ChildRec), hipMemcpyDeviceToHost, st));
-            TJ_CK(hipStreamSynchronize(st));
+            const ChildRec* rec = hrec;
+            if (!rec) {  // the level went back to the host planner after all
+                ChildRec* back = (ChildRec*)pinned_down((size_t)nrec * sizeof(ChildRec));
+                if (!back) return TJ_E_HIP;
+                TJ_CK(hipMemcpyAsync(back, d_crec, nrec * sizeof(ChildRec), hipMemcpyDeviceToHost, st));
+                TJ_CK(hipStreamSynchronize(st));
+                rec = back;
+            }
             // children in key order: segment order, then digit order; a child's
             // rows start where its smaller-digit siblings end
             HostTimer ht(this, F_HOST_CLASSIFY);
@@ -1525,6 +1578,53 @@ struct Exec {
         return TJ_OK;
     }
 
+    // What a join's leaf launch leaves in pinned memory.
+    struct JoinEnd {
+        uint64_t total;  // pairs up to the end of its leaves, carry-in included
+        uint32_t err;    // a look-back expired
+        uint32_t pad;
+    };
+    JoinEnd* join_end()
+    {
+        JoinEnd* e = (JoinEnd*)pinned_down(sizeof(JoinEnd));
+        if (e) *e = JoinEnd{0, 0, 0};
+        return e;
+    }
+
+    // Before a materialising leaf launch: its n leaves (NULL: the device has
+    // them), the look-back status from `carry` on, and the ticket, in one launch.
+    hipError_t stage_join(const LeafDesc* l, uint32_t n, uint64_t carry)
+    {
+        StageArgs sa{};
+        sa.fill_p[0] = d_status;
+        sa.fill_n[0] = 1;
+        sa.fill_v[0] = STATUS_INCLUSIVE | carry;
+        sa.fill_p[1] = d_status + 1;
+        sa.fill_n[1] = n;
+        sa.fill_p[2] = d_probe + 3;  // ticket
+        sa.fill_n[2] = 1;
+        if (l && n) {
+            void* pin = pinned_up(n * sizeof(LeafDesc), 0);
+            if (!pin) return hipErrorOutOfMemory;
+            std::memcpy(pin, l, n * sizeof(LeafDesc));
+            sa.dst = d_leaves;
+            sa.src = pin;
+            sa.n16 = n * sizeof(LeafDesc) / 16;
+        }
+        return launch_stage(sa, st);
+    }
+
+    // The pair total of the count launches so far (waits for the stream).
+    int read_total(uint64_t* out)
+    {
+        uint64_t* t = (uint64_t*)pinned_down(sizeof(uint64_t));
+        if (!t) return TJ_E_HIP;
+        TJ_CK(launch_publish(t, d_probe + 2, 1, st));
+        TJ_CK(hipStreamSynchronize(st));
+        *out = *t;
+        return TJ_OK;
+    }
+
     // Counts (mat = false) or materialises (mat = true) the range's leaves and
     // crosses. Units are taken in key order, which is the order of their first
     // R row (every unit has R rows, and partitioning keeps each bucket inside
@@ -1546,35 +1646,28 @@ struct Exec {
             stats.leaves += nl;
             uint64_t* d_total = d_probe + 2;
             uint32_t* d_ticket = (uint32_t*)(d_probe + 3);
-            uint32_t* d_err = d_ticket + 1;
             if (!mat) {
                 TJ_CK(launch_fill_u64(d_total, 1, 0, st));
                 TJ_CK(timed(F_LEAF_COUNT, rows * kb, [&] {
                     return launch_leaf_join(kb, wide, false, d_leaves, nl, bufs, d_status, d_ticket, d_total,
-                                            d_err, nullptr, nullptr, 0, st);
+                                            nullptr, nullptr, nullptr, 0, st);
                 }));
-                uint64_t t = 0;
-                TJ_CK(hipMemcpyAsync(&t, d_total, 8, hipMemcpyDeviceToHost, st));
-                TJ_CK(hipStreamSynchronize(st));
+                TJ_RET(read_total(total_out));
                 stats.bytes_read += rows * kb;
-                *total_out = t;
                 return TJ_OK;
             }
-            TJ_CK(launch_fill_u64(d_status, 1, STATUS_INCLUSIVE | base, st));
-            TJ_CK(launch_fill_u64(d_status + 1, nl, 0, st));
-            TJ_CK(launch_fill_u64(d_probe + 3, 1, 0, st));  // ticket and error flag
+            JoinEnd* fin = join_end();
+            if (!fin) return TJ_E_HIP;
+            TJ_CK(stage_join(nullptr, nl, base));
             const size_t leaf_timer = pending.size();
             TJ_CK(timed(F_LEAF_MAT, rows * row_bytes(kb, true), [&] {
-                return launch_leaf_join(kb, wide, true, d_leaves, nl, bufs, d_status, d_ticket, d_total, d_err,
+                return launch_leaf_join(kb, wide, true, d_leaves, nl, bufs, d_status, d_ticket, &fin->total, &fin->err,
                                         out_r, out_s, capacity, st);
             }));
             stats.bytes_read += rows * row_bytes(kb, true);
-            uint64_t fin[2] = {0, 0};
-            TJ_CK(hipMemcpyAsync(&fin[0], d_status + nl, 8, hipMemcpyDeviceToHost, st));
-            TJ_CK(hipMemcpyAsync(&fin[1], d_probe + 3, 8, hipMemcpyDeviceToHost, st));
             TJ_CK(hipStreamSynchronize(st));
-            if (fin[1] >> 32) return TJ_E_INTERNAL;  // a look-back expired
-            const uint64_t end = fin[0] & STATUS_VALUE;
+            if (fin->err) return TJ_E_INTERNAL;  // a look-back expired
+            const uint64_t end = fin->total;
             if (leaf_timer < pending.size()) pending[leaf_timer].bytes += (end - base) * 8;
             *total_out = end - base;
             const uint64_t written = std::min(end, capacity) > base ? std::min(end, capacity) - base : 0;
@@ -1585,7 +1678,6 @@ struct Exec {
         stats.leaves += (uint32_t)leaves.size();
         uint64_t* d_total = d_probe + 2;
         uint32_t* d_ticket = (uint32_t*)(d_probe + 3);
-        uint32_t* d_err = d_ticket + 1;
         if (!mat) {
             uint64_t cross_pairs = 0;
             for (const CrossDesc& c : crosses) cross_pairs += c.a * c.b;
@@ -1608,17 +1700,15 @@ struct Exec {
                     TJ_CK(upload(d_leaves, sel.data() + i, n * sizeof(LeafDesc), st, 0));
                     TJ_CK(timed(F_LEAF_COUNT, rows * kb, [&] {
                         return launch_leaf_join(kb, wide, false, d_leaves, n, bufs, d_status, d_ticket, d_total,
-                                                d_err, nullptr, nullptr, 0, st);
+                                                nullptr, nullptr, nullptr, 0, st);
                     }));
                     stats.bytes_read += rows * kb;
                     // the selection buffer is refilled for the next width: wait for the upload
                     TJ_CK(hipStreamSynchronize(st));
                 }
             }
-            uint64_t t = 0;
-            TJ_CK(hipMemcpyAsync(&t, d_total, 8, hipMemcpyDeviceToHost, st));
-            TJ_CK(hipStreamSynchronize(st));
-            *total_out = t + cross_pairs;
+            TJ_RET(read_total(total_out));
+            *total_out += cross_pairs;
         } else {
             // Key order of the units is the order of their R rows in buffer A
             // (LeafDesc/CrossDesc::out until batched). Leaves of a level are
@@ -1671,9 +1761,10 @@ struct Exec {
                 }
                 const uint32_t nl = (uint32_t)bl.size(), nc = (uint32_t)bc.size();
                 ht.stop();
-                TJ_CK(launch_fill_u64(d_status, 1, STATUS_INCLUSIVE | carry, st));
-                TJ_CK(launch_fill_u64(d_status + 1, nl, 0, st));
-                TJ_CK(launch_fill_u64(d_probe + 3, 1, 0, st));  // ticket and error flag
+                JoinEnd* fin = join_end();
+                if (!fin) return TJ_E_HIP;
+                fin->total = carry;
+                TJ_CK(stage_join(bl.data(), nl, carry));
                 size_t leaf_timer = (size_t)-1;
                 if (nl) {
                     uint64_t rows = 0;
@@ -1683,10 +1774,9 @@ struct Exec {
                         wide = wide || L.bits > 32;
                     }
                     leaf_timer = pending.size();
-                    TJ_CK(upload(d_leaves, bl.data(), nl * sizeof(LeafDesc), st, 0));
                     TJ_CK(timed(F_LEAF_MAT, rows * row_bytes(bkb, true), [&] {
                         return launch_leaf_join(bkb, wide, true, d_leaves, nl, bufs, d_status, d_ticket,
-                                                d_total, d_err, out_r, out_s, capacity, st);
+                                                &fin->total, &fin->err, out_r, out_s, capacity, st);
                     }));
                     stats.bytes_read += rows * row_bytes(bkb, true);
                 }
@@ -1704,14 +1794,11 @@ struct Exec {
                     }));
                     stats.bytes_read += in_rows * 4;
                 }
-                uint64_t fin[2] = {0, 0};
-                TJ_CK(hipMemcpyAsync(&fin[0], d_status + nl, 8, hipMemcpyDeviceToHost, st));
-                TJ_CK(hipMemcpyAsync(&fin[1], d_probe + 3, 8, hipMemcpyDeviceToHost, st));
                 TJ_CK(hipStreamSynchronize(st));
-                if (fin[1] >> 32) return TJ_E_INTERNAL;  // a look-back expired
-                const uint64_t leaf_pairs = (fin[0] & STATUS_VALUE) - carry;
+                if (fin->err) return TJ_E_INTERNAL;  // a look-back expired
+                const uint64_t leaf_pairs = fin->total - carry;
                 if (leaf_timer < pending.size()) pending[leaf_timer].bytes += leaf_pairs * 8;
-                carry = (fin[0] & STATUS_VALUE) + pre;
+                carry = fin->total + pre;
             }
             *total_out = carry - base;
             const uint64_t written = std::min(carry, capacity) > base ? std::min(carry, capacity) - base : 0;
@@ -1832,7 +1919,7 @@ struct Exec {
         TJ_CK(hipMemcpyAsync(d_chunks, chunks.data(), nc * sizeof(ChunkDesc), hipMemcpyHostToDevice, st));
         TJ_CK(launch_fill_u64(d_gmin, child, ~0ull, st));
         TJ_CK(launch_fill_u64(d_gmax, child, 0ull, st));
-        TJ_CK(launch_hist(sh.kb, d_chunks, nc, d_groups, bufs, d_hist, d_gmin, d_gmax, nullptr, st));
+        TJ_CK(launch_hist(sh.kb, d_chunks, nc, d_groups, bufs, d_hist, d_gmin, d_gmax, nullptr, nullptr, st));
         std::vector<uint32_t> h((size_t)nc * NB);
         TJ_CK(hipMemcpyAsync(h.data(), d_hist, h.size() * 4, hipMemcpyDeviceToHost, st));
         TJ_CK(hipStreamSynchronize(st));
@@ -2024,7 +2111,8 @@ void layout_join_window(Exec& x, char* p, uint64_t data_bytes)
 
 int probe(Exec& x, const void* a, uint64_t na, const void* b, uint64_t nb, uint64_t& lo, uint64_t& hi)
 {
-    uint64_t mm[2];
+    uint64_t* mm = (uint64_t*)pinned_down(16);
+    if (!mm) return TJ_E_HIP;
     TJ_CK(x.timed(F_PROBE, (na + nb) * (uint64_t)x.sh.kb,
                   [&] { return launch_probe(x.sh.kb, a, na, b, nb, x.d_probe, x.st); }));
     TJ_CK(hipMemcpyAsync(mm, x.d_probe, 16, hipMemcpyDeviceToHost, x.st));
@@ -2041,7 +2129,8 @@ int probe(Exec& x, const void* a, uint64_t na, const void* b, uint64_t nb, uint6
 // histogram checks every row against the range (GROUP_CHECK_RANGE).
 int sampled_range(Exec& x, const void* a, uint64_t na, const void* b, uint64_t nb, uint64_t& lo, uint64_t& hi)
 {
-    uint64_t mm[2];
+    uint64_t* mm = (uint64_t*)pinned_down(16);
+    if (!mm) return TJ_E_HIP;
     const uint64_t sampled = (na + SAMPLED_PROBE_STEP - 1) / SAMPLED_PROBE_STEP +
                              (nb + SAMPLED_PROBE_STEP - 1) / SAMPLED_PROBE_STEP;
     TJ_CK(x.timed(F_PROBE, sampled * (uint64_t)x.sh.kb, [&] {
@@ -2291,7 +2380,10 @@ static int sort_body(int key_type, const void* keys_in, const int32_t* rids_in, 
                 }
             }
         }
-        if (!spec && !learned) TJ_RET(probe(x, keys_in, n, nullptr, 0, lo, hi));
+        if (!spec && !learned) {
+            if (unlimited && !want_learned && !t_noalloc) x.root_probe = true;
+            else TJ_RET(probe(x, keys_in, n, nullptr, 0, lo, hi));
+        }
     }
     if (unlimited) {
         x.stats.key_ranges = 1;
@@ -2437,7 +2529,10 @@ static int join_body(int key_type, const void* r_keys, const int32_t* r_rids, ui
                 }
             }
         }
-        if (!spec && !learned) TJ_RET(probe(x, r_keys, n_r, s_keys, n_s, lo, hi));
+        if (!spec && !learned) {
+            if (unlimited && !want_learned) x.root_probe = true;  // (see sort_body)
+            else TJ_RET(probe(x, r_keys, n_r, s_keys, n_s, lo, hi));
+        }
     }
     uint64_t total = 0;
     if (unlimited) {
@@ -2724,9 +2819,10 @@ static int partition_pass_body(const int64_t* keys, const int32_t* rids, uint64_
     TJ_CK(hipMemcpyAsync(x.d_cblocks, cbs.data(), cbs.size() * sizeof(CBlockDesc), hipMemcpyHostToDevice, st));
     TJ_CK(launch_fill_u64(x.d_gmin, 1u << bits, ~0ull, st));
     TJ_CK(launch_fill_u64(x.d_gmax, 1u << bits, 0ull, st));
-    TJ_CK(launch_hist(8, x.d_chunks, g.nchunks, x.d_groups, x.bufs, x.d_hist, x.d_gmin, x.d_gmax, nullptr, st));
-    TJ_CK(launch_scan(x.d_cblocks, g.ncblocks, x.d_groups, 1, x.d_hist, x.d_cbsum, x.d_ccount, x.d_cstart, st));
-    TJ_CK(launch_scatter(8, 8, true, true, x.d_chunks, g.nchunks, x.d_groups, x.d_hist, x.d_cbsum, x.d_cstart, x.bufs, st));
+    TJ_CK(launch_hist(8, x.d_chunks, g.nchunks, x.d_groups, x.bufs, x.d_hist, x.d_gmin, x.d_gmax, nullptr, nullptr, st));
+    TJ_CK(launch_scan(x.d_cblocks, g.ncblocks, x.d_groups, 1, 1, g.ncblocks == 1, x.d_hist, x.d_cbsum, x.d_ccount,
+                      x.d_cstart, x.d_gmin, x.d_gmax, x.d_crec, nullptr, nullptr, nullptr, st));
+    TJ_CK(launch_scatter(8, 8, true, true, x.d_chunks, g.nchunks, x.d_groups, x.d_hist, x.d_cbsum, x.d_cstart, x.bufs, nullptr, st));
     TJ_CK(hipMemcpyAsync(counts_out, x.d_ccount, (1u << bits) * 4ull, hipMemcpyDeviceToDevice, st));
     TJ_CK(hipStreamSynchronize(st));
     return TJ_OK;

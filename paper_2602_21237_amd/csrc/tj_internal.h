@@ -170,8 +170,72 @@ struct KeyRef {
     uint32_t kb, pad;
 };
 
+// Table staging (k_stage): n16 16-byte units from src (pinned host memory) to
+// dst (16-byte aligned), and up to STAGE_FILLS regions of 64-bit words to set.
+constexpr int STAGE_FILLS = 4;
+struct StageArgs {
+    void* dst;
+    const void* src;
+    uint64_t n16;
+    uint64_t* fill_p[STAGE_FILLS];
+    uint64_t fill_n[STAGE_FILLS];
+    uint64_t fill_v[STAGE_FILLS];
+};
+
+// First pass of a call that plans its digit on the device (k_probe_root, k_hist).
+constexpr uint32_t PROBE_PARTS = 512;  // blocks of the probe at most
+struct RootArgs {
+    const uint64_t* parts;  // minimum and maximum ordinal of each probe block
+    uint32_t nparts;
+    uint32_t narrow;        // the launch narrows keys: groups whose children span more than 2^32 keep theirs
+    uint64_t rows;          // rows of the segment, all sides
+    uint64_t* hdr;          // pinned: receives the extremes
+    uint32_t flags;         // GROUP_* flags of the groups
+    uint32_t pad;
+};
+
 // Rows per leaf block (the block shape depends on the key word, see the kernels).
 constexpr int LEAF_CAP = 8192;
+
+#ifndef TJ_PASS_DIGIT_BITS
+#define TJ_PASS_DIGIT_BITS MAX_DIGIT_BITS
+#endif
+// widest digit a partition pass uses (at most MAX_DIGIT_BITS)
+constexpr int PASS_DIGIT_BITS = TJ_PASS_DIGIT_BITS;
+
+// Digit of a pass over a segment of `rows` rows whose ordinals span `span`:
+// enough digits that a child averages LEAF_CAP / 2 rows (at least 2, at most a
+// full digit), at the largest shift at which (span >> shift) + 1 digits still
+// reach that many, so a span that is not a power of two still puts them to
+// use. With `few` (a level of at most FEW_SEGS segments) a segment of at most
+// SMALL_SEG_ROWS rows (mostly a bucket crowded by a few frequent keys) takes
+// a full digit: such a level costs about its launches and read-back whatever
+// the width, and the wider digit separates the frequent keys from their
+// neighbours in fewer levels. (A level of many segments keeps the narrower
+// digit: the children's bookkeeping grows with the width.) A span of 0
+// (filtered roots of a single-key range, which still need a compaction pass)
+// gets one bit.
+constexpr uint64_t SMALL_SEG_ROWS = 16ull * LEAF_CAP;
+constexpr size_t FEW_SEGS = 64;
+__host__ __device__ inline uint32_t nbits64(uint64_t x) { return x ? 64u - (uint32_t)__builtin_clzll(x) : 0u; }
+
+__host__ __device__ inline uint64_t clamp64(uint64_t x, uint64_t lo, uint64_t hi) { return x < lo ? lo : x > hi ? hi : x; }
+
+__host__ __device__ inline void plan_digit(uint64_t span, uint64_t rows, bool few, uint32_t& shift, uint32_t& bits)
+{
+    const uint64_t want =
+        few && rows <= SMALL_SEG_ROWS
+            ? 1ull << PASS_DIGIT_BITS
+            : clamp64((rows + LEAF_CAP / 2 - 1) / (LEAF_CAP / 2), 2, 1ull << PASS_DIGIT_BITS);
+    shift = 0;
+    for (uint32_t sh = nbits64(span); sh-- > 0;)
+        if ((span >> sh) + 1 >= want) {
+            shift = sh;
+            break;
+        }
+    while ((span >> shift) >= (1ull << PASS_DIGIT_BITS)) shift++;
+    bits = (span >> shift) ? nbits64(span >> shift) : 1u;
+}
 
 // ---------------------------------------------------------------------------
 // Launchers (tj_kernels.hip). key_bytes is 4 or 8. All return hipSuccess or the
@@ -180,6 +244,11 @@ constexpr int LEAF_CAP = 8192;
 hipError_t launch_fill_u64(uint64_t* p, uint64_t n, uint64_t v, hipStream_t st);
 hipError_t launch_probe(int key_bytes, const void* a, uint64_t na, const void* b, uint64_t nb,
                         uint64_t* minmax, hipStream_t st);
+hipError_t launch_stage(const StageArgs& a, hipStream_t st);
+hipError_t launch_publish(uint64_t* dst, const uint64_t* src, uint32_t n, hipStream_t st);
+uint32_t probe_root_blocks(uint64_t na, uint64_t nb);
+hipError_t launch_probe_root(int key_bytes, const void* a, uint64_t na, const void* b, uint64_t nb, uint64_t* parts,
+                             const StageArgs& sa, hipStream_t st);
 // Min and max ordinal of every step-th element of a and of b (step 1: all).
 // out[i] = ordinal of a[i * step], i < ceil(n / step)
 hipError_t launch_gather_step(int key_bytes, const void* a, uint64_t n, uint64_t step, uint64_t* out, hipStream_t st);
@@ -188,30 +257,33 @@ hipError_t launch_read_ords(const KeyRef* refs, uint32_t n, uint64_t* out, hipSt
 hipError_t launch_probe_step(int key_bytes, const void* a, uint64_t na, const void* b, uint64_t nb,
                              uint64_t step, uint64_t* minmax, hipStream_t st);
 // range_miss: set to nonzero when a GROUP_CHECK_RANGE group has a row outside its digit range.
+// root: the groups' digit is planned from the probe's partial extremes (see RootArgs).
 hipError_t launch_hist(int key_bytes, const ChunkDesc* chunks, uint32_t nchunks,
-                       const GroupDesc* groups, BufSet bufs, uint32_t* hist,
-                       uint64_t* gmin, uint64_t* gmax, uint32_t* range_miss, hipStream_t st);
+                       GroupDesc* groups, BufSet bufs, uint32_t* hist,
+                       uint64_t* gmin, uint64_t* gmax, uint32_t* range_miss, const RootArgs* root, hipStream_t st);
 // Histogram of the learned pass: the digit is the bucket of `model` (device
 // copy), and each row's bucket is also stored in bkt.b[side][row].
 hipError_t launch_learned_hist(int key_bytes, const ChunkDesc* chunks, uint32_t nchunks,
-                               const GroupDesc* groups, BufSet bufs, const tj_rmi_t* model, BktSet bkt,
+                               GroupDesc* groups, BufSet bufs, const tj_rmi_t* model, BktSet bkt,
                                uint32_t* hist, uint64_t* gmin, uint64_t* gmax, hipStream_t st);
-hipError_t launch_scan(const CBlockDesc* cblocks, uint32_t ncblocks, const GroupDesc* groups,
-                       uint32_t ngroups, uint32_t* hist, uint32_t* cbsum, uint32_t* ccount,
-                       uint64_t* cstart, hipStream_t st);
-// out_key_bytes < key_bytes (8 -> 4) writes narrowed keys (see k_scatter).
+// Offsets of the scatter and the children's records: each segment's sides folded
+// into ChildRec records at group.child0 / nside (groups come in side order per
+// segment) of out and, unless NULL, of hout (pinned host memory). direct: every
+// group has at most one scan block. hmiss (pinned, may be NULL) receives *miss.
+hipError_t launch_scan(const CBlockDesc* cblocks, uint32_t ncblocks, const GroupDesc* groups, uint32_t ngroups,
+                       int nside, bool direct, uint32_t* hist, uint32_t* cbsum, uint32_t* ccount, uint64_t* cstart,
+                       const uint64_t* gmin, const uint64_t* gmax, ChildRec* out, ChildRec* hout,
+                       const uint32_t* miss, uint64_t* hmiss, hipStream_t st);
+// out_key_bytes < key_bytes (8 -> 4) writes narrowed keys (see k_scatter). skip (may be NULL): nothing is
+// moved when the word it points to is nonzero.
 hipError_t launch_scatter(int key_bytes, int out_key_bytes, bool rids, bool keys, const ChunkDesc* chunks,
                           uint32_t nchunks, const GroupDesc* groups, const uint32_t* hist,
-                          const uint32_t* cbsum, const uint64_t* cstart, BufSet bufs, hipStream_t st);
+                          const uint32_t* cbsum, const uint64_t* cstart, BufSet bufs, const uint32_t* skip,
+                          hipStream_t st);
 // Scatter of the learned pass: digits are read from bkt (no narrowing).
 hipError_t launch_learned_scatter(int key_bytes, bool rids, const ChunkDesc* chunks, uint32_t nchunks,
                                   const GroupDesc* groups, const uint32_t* hist, const uint32_t* cbsum,
                                   const uint64_t* cstart, BufSet bufs, BktSet bkt, hipStream_t st);
-// Folds each segment's per-side child tables into ChildRec records, written at
-// group.child0 / nside (groups come in side order per segment).
-hipError_t launch_children(const GroupDesc* groups, uint32_t ngroups, int nside,
-                           const uint32_t* ccount, const uint64_t* gmin, const uint64_t* gmax,
-                           ChildRec* out, hipStream_t st);
 // pass 0 counts each segment's leaves into seg_count; pass 1 writes them and
 // adds to summary[0..2] (which the caller clears first).
 hipError_t launch_batch_leaves(const GroupDesc* groups, const ChildRec* crec, const BatchArgs& a,
@@ -221,8 +293,8 @@ hipError_t launch_leaf_sort(int key_bytes, bool wide, const LeafDesc* leaves, ui
                             BufSet bufs, void* out_k, int32_t* out_r, hipStream_t st);
 // Count mode adds the leaves' pair counts to *total. Materialise mode needs
 // status[0] = inclusive-flagged carry-in offset, status[1..n] = 0, *ticket = 0;
-// afterwards status[n] holds the inclusive pair total and *err != 0 flags an
-// expired look-back.
+// afterwards *total holds the inclusive pair total (carry-in included) and *err
+// is 1 if a look-back expired.
 hipError_t launch_leaf_join(int key_bytes, bool wide, bool materialize, const LeafDesc* leaves,
                             uint32_t n, BufSet bufs, uint64_t* status, uint32_t* ticket,
                             uint64_t* total, uint32_t* err, int32_t* out_r, int32_t* out_s,

@@ -159,6 +159,25 @@ __device__ __forceinline__ uint64_t block_sum64(uint64_t v, uint64_t* tmp)
     return tot;
 }
 
+// Smallest and largest ordinal of the block's rows, from each thread's own.
+template <int NT>
+__device__ __forceinline__ void block_minmax64(uint64_t& lo, uint64_t& hi, uint64_t* tmp)
+{
+    constexpr int NW = NT / 64;
+    lo = wave_min64(lo);
+    hi = wave_max64(hi);
+    if ((threadIdx.x & 63) == 0) tmp[threadIdx.x / 64] = lo;
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < NW; i++) lo = tmp[i] < lo ? tmp[i] : lo;
+    lds_barrier();
+    if ((threadIdx.x & 63) == 0) tmp[threadIdx.x / 64] = hi;
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < NW; i++) hi = tmp[i] > hi ? tmp[i] : hi;
+    lds_barrier();
+}
+
 // Inclusive running maximum across the wave (same DPP pattern as the sum; 0 is
 // the identity, values are non-negative).
 __device__ __forceinline__ uint32_t wave_incl_max(uint32_t v)
@@ -291,6 +310,47 @@ hipError_t launch_wave_scan_test(const uint32_t* in, uint32_t* out, uint64_t n, 
     return hipGetLastError();
 }
 
+// Copies the planner's tables from pinned host memory into the workspace (16
+// bytes a lane) and sets the regions a launch needs cleared: one launch in
+// place of a copy per table and a fill per region, each of which costs about
+// as much as the launch (10 us between two small launches).
+__device__ __forceinline__ void stage_slice(const StageArgs& a, uint64_t i0, uint64_t step)
+{
+    for (uint64_t i = i0; i < a.n16; i += step) ((uint4*)a.dst)[i] = ((const uint4*)a.src)[i];
+#pragma unroll
+    for (int f = 0; f < STAGE_FILLS; f++)
+        for (uint64_t i = i0; i < a.fill_n[f]; i += step) a.fill_p[f][i] = a.fill_v[f];
+}
+
+__global__ __launch_bounds__(256) void k_stage(StageArgs a)
+{
+    stage_slice(a, blockIdx.x * 256ull + threadIdx.x, (uint64_t)gridDim.x * 256);
+}
+
+hipError_t launch_stage(const StageArgs& a, hipStream_t st)
+{
+    uint64_t n = a.n16;
+    for (int f = 0; f < STAGE_FILLS; f++) n = a.fill_n[f] > n ? a.fill_n[f] : n;
+    if (n == 0) return hipSuccess;
+    uint64_t blocks = (n + 255) / 256;
+    if (blocks > 2048) blocks = 2048;
+    hipLaunchKernelGGL(k_stage, dim3((uint32_t)blocks), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
+// dst[i] = src[i] (a few words; dst is pinned host memory)
+__global__ void k_publish(uint64_t* __restrict__ dst, const uint64_t* __restrict__ src, uint32_t n)
+{
+    if (threadIdx.x < n) dst[threadIdx.x] = src[threadIdx.x];
+}
+
+hipError_t launch_publish(uint64_t* dst, const uint64_t* src, uint32_t n, hipStream_t st)
+{
+    if (n > 64) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, st, dst, src, n);
+    return hipGetLastError();
+}
+
 // ---------------------------------------------------------------------------
 // range probe: minimum and maximum ordinal over one or two key columns
 // ---------------------------------------------------------------------------
@@ -374,6 +434,60 @@ hipError_t launch_probe(int key_bytes, const void* a, uint64_t na, const void* b
     return launch_probe_step(key_bytes, a, na, b, nb, 1, minmax, st);
 }
 
+// The probe of a call whose first pass plans its digit on the device: each
+// block leaves its minimum and maximum in parts[2 * block], which the histogram
+// reduces (k_hist, ROOT), and stages its slice of the pass's tables.
+template <typename K>
+__global__ __launch_bounds__(256) void k_probe_root(const K* __restrict__ a, uint64_t na,
+                                                    const K* __restrict__ b, uint64_t nb,
+                                                    uint64_t* __restrict__ parts, StageArgs sa)
+{
+    __shared__ uint64_t tmp[4];
+    const uint64_t stride = (uint64_t)gridDim.x * 256, t0 = blockIdx.x * 256ull + threadIdx.x;
+    uint64_t mn = ~0ull, mx = 0;
+    constexpr int U = 8;
+    auto column = [&](const K* __restrict__ p, uint64_t n) {
+        for (uint64_t i0 = t0; i0 < n; i0 += stride * U) {
+            K v[U];
+#pragma unroll
+            for (int u = 0; u < U; u++) v[u] = ld_clamp(p, i0 + u * stride, n);
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const uint64_t o = ord_of(v[u]);
+                mn = o < mn ? o : mn;
+                mx = o > mx ? o : mx;
+            }
+        }
+    };
+    stage_slice(sa, t0, stride);
+    column(a, na);
+    column(b, nb);
+    block_minmax64<256>(mn, mx, tmp);
+    if (threadIdx.x == 0) {
+        parts[2 * blockIdx.x] = mn;
+        parts[2 * blockIdx.x + 1] = mx;
+    }
+}
+
+uint32_t probe_root_blocks(uint64_t na, uint64_t nb)
+{
+    const uint64_t n = na > nb ? na : nb, blocks = (n + 256 * 8 - 1) / (256 * 8);
+    return (uint32_t)(blocks < 1 ? 1 : blocks > PROBE_PARTS ? PROBE_PARTS : blocks);
+}
+
+hipError_t launch_probe_root(int key_bytes, const void* a, uint64_t na, const void* b, uint64_t nb, uint64_t* parts,
+                             const StageArgs& sa, hipStream_t st)
+{
+    const dim3 grid(probe_root_blocks(na, nb)), block(256);
+    if (key_bytes == 4)
+        hipLaunchKernelGGL(k_probe_root<int32_t>, grid, block, 0, st, (const int32_t*)a, na, (const int32_t*)b, nb,
+                           parts, sa);
+    else
+        hipLaunchKernelGGL(k_probe_root<int64_t>, grid, block, 0, st, (const int64_t*)a, na, (const int64_t*)b, nb,
+                           parts, sa);
+    return hipGetLastError();
+}
+
 // Every step-th key of a column, as its ordinal: out[i] = ord(a[i * step]) for
 // i < ceil(n / step).
 template <typename K>
@@ -435,21 +549,49 @@ __device__ __forceinline__ uint32_t group_digit(uint64_t o, uint64_t base, uint3
 // LDS), and every row's bucket is stored in bkt for the scatter. The learned
 // variant runs 1024-thread blocks: its 34 KiB of LDS per block would cap
 // 256-thread blocks at half the waves a CU can hold.
-template <typename K, bool LEARNED, int NT = PART_THREADS>
+// ROOT: the pass's one segment takes its digit here, from the probe's partial
+// extremes (every block reduces them and plans the same digit); the first
+// block of each group writes it to the group for the kernels that follow, and
+// block 0 the extremes to root.hdr (pinned) for the host. The host then plans
+// no launch before the probe is done: a call of 10^5 rows saves the wait.
+template <typename K, bool LEARNED, int NT = PART_THREADS, bool ROOT = false>
 __global__ __launch_bounds__(NT) void k_hist(const ChunkDesc* __restrict__ chunks,
-                                                       const GroupDesc* __restrict__ groups,
+                                                       GroupDesc* __restrict__ groups,
                                                        BufSet bufs, uint32_t* __restrict__ hist,
                                                        uint64_t* __restrict__ gmin,
                                                        uint64_t* __restrict__ gmax,
                                                        const tj_rmi_t* __restrict__ model, BktSet bkt,
-                                                       uint32_t* __restrict__ range_miss)
+                                                       uint32_t* __restrict__ range_miss, RootArgs root)
 {
     __shared__ uint32_t cnt[NB];
     __shared__ uint64_t mn[NB], mx[NB];
     __shared__ __align__(16) char lm_raw[LEARNED ? sizeof(tj_rmi_t) : 16];
     const tj_rmi_t& lm = *(const tj_rmi_t*)lm_raw;
     const ChunkDesc ch = chunks[blockIdx.x];
-    const GroupDesc g = groups[ch.group];
+    GroupDesc g = groups[ch.group];
+    if constexpr (ROOT) {
+        __shared__ uint64_t rtmp[NT / 64];
+        static_assert((uint32_t)NT >= PROBE_PARTS, "one partial a thread");
+        uint64_t lo = ~0ull, hi = 0;
+        if (threadIdx.x < root.nparts) {
+            lo = root.parts[2 * threadIdx.x];
+            hi = root.parts[2 * threadIdx.x + 1];
+        }
+        block_minmax64<NT>(lo, hi, rtmp);
+        plan_digit(hi - lo, root.rows, true, g.shift, g.bits);
+        g.base = lo;
+        if (threadIdx.x == 0 && blockIdx.x == g.chunk0) {  // (no block of this launch uses what another one writes here)
+            GroupDesc* w = groups + ch.group;
+            w->base = lo;
+            w->shift = g.shift;
+            w->bits = g.bits;
+            w->flags = root.flags | (root.narrow && g.shift > 32 ? GROUP_WIDE : 0u);
+            if (blockIdx.x == 0) {
+                root.hdr[0] = lo;
+                root.hdr[1] = hi;
+            }
+        }
+    }
     const K* __restrict__ src = (const K*)bufs.key[g.src][g.side] + g.src_koff + ch.start;
     uint16_t* __restrict__ bk = LEARNED ? bkt.b[g.side] + ch.start : nullptr;
     const uint32_t nbins = 1u << g.bits;
@@ -536,35 +678,44 @@ __global__ __launch_bounds__(NT) void k_hist(const ChunkDesc* __restrict__ chunk
 }
 
 hipError_t launch_hist(int key_bytes, const ChunkDesc* chunks, uint32_t nchunks,
-                       const GroupDesc* groups, BufSet bufs, uint32_t* hist, uint64_t* gmin,
-                       uint64_t* gmax, uint32_t* range_miss, hipStream_t st)
+                       GroupDesc* groups, BufSet bufs, uint32_t* hist, uint64_t* gmin,
+                       uint64_t* gmax, uint32_t* range_miss, const RootArgs* root, hipStream_t st)
 {
     if (nchunks == 0) return hipSuccess;
     const BktSet none{};
+    if (root) {
+        if (key_bytes == 4)
+            hipLaunchKernelGGL((k_hist<int32_t, false, PART_THREADS, true>), dim3(nchunks), dim3(PART_THREADS), 0, st,
+                               chunks, groups, bufs, hist, gmin, gmax, nullptr, none, range_miss, *root);
+        else
+            hipLaunchKernelGGL((k_hist<int64_t, false, PART_THREADS, true>), dim3(nchunks), dim3(PART_THREADS), 0, st,
+                               chunks, groups, bufs, hist, gmin, gmax, nullptr, none, range_miss, *root);
+        return hipGetLastError();
+    }
     if (key_bytes == 4)
         hipLaunchKernelGGL((k_hist<int32_t, false>), dim3(nchunks), dim3(PART_THREADS), 0, st, chunks, groups,
-                           bufs, hist, gmin, gmax, nullptr, none, range_miss);
+                           bufs, hist, gmin, gmax, nullptr, none, range_miss, RootArgs{});
     else
         hipLaunchKernelGGL((k_hist<int64_t, false>), dim3(nchunks), dim3(PART_THREADS), 0, st, chunks, groups,
-                           bufs, hist, gmin, gmax, nullptr, none, range_miss);
+                           bufs, hist, gmin, gmax, nullptr, none, range_miss, RootArgs{});
     return hipGetLastError();
 }
 
 constexpr int LEARNED_HIST_THREADS = 1024;
 
 hipError_t launch_learned_hist(int key_bytes, const ChunkDesc* chunks, uint32_t nchunks,
-                               const GroupDesc* groups, BufSet bufs, const tj_rmi_t* model, BktSet bkt,
+                               GroupDesc* groups, BufSet bufs, const tj_rmi_t* model, BktSet bkt,
                                uint32_t* hist, uint64_t* gmin, uint64_t* gmax, hipStream_t st)
 {
     if (nchunks == 0) return hipSuccess;
     if (key_bytes == 4)
         hipLaunchKernelGGL((k_hist<int32_t, true, LEARNED_HIST_THREADS>), dim3(nchunks), dim3(LEARNED_HIST_THREADS), 0, st,
                            chunks, groups,
-                           bufs, hist, gmin, gmax, model, bkt, nullptr);
+                           bufs, hist, gmin, gmax, model, bkt, nullptr, RootArgs{});
     else
         hipLaunchKernelGGL((k_hist<int64_t, true, LEARNED_HIST_THREADS>), dim3(nchunks), dim3(LEARNED_HIST_THREADS), 0, st,
                            chunks, groups,
-                           bufs, hist, gmin, gmax, model, bkt, nullptr);
+                           bufs, hist, gmin, gmax, model, bkt, nullptr, RootArgs{});
     return hipGetLastError();
 }
 
@@ -581,6 +732,21 @@ hipError_t launch_learned_hist(int key_bytes, const ChunkDesc* chunks, uint32_t 
 constexpr int SCAN_THREADS = 256;
 constexpr int SCAN_DPT = NB / SCAN_THREADS;
 
+// Exclusive prefix of digit d over `n` chunks from hist row `c0`, in place; returns the total.
+__device__ __forceinline__ uint32_t scan_chunks(uint32_t* __restrict__ hist, uint64_t c0, uint32_t n, uint32_t d)
+{
+    uint32_t run = 0;
+    uint32_t v[CBLOCK];
+#pragma unroll
+    for (int c = 0; c < CBLOCK; c++) v[c] = (uint32_t)c < n ? hist[(c0 + c) * NB + d] : 0u;
+#pragma unroll
+    for (int c = 0; c < CBLOCK; c++) {
+        if ((uint32_t)c < n) hist[(c0 + c) * NB + d] = run;
+        run += v[c];
+    }
+    return run;
+}
+
 __global__ __launch_bounds__(SCAN_THREADS) void k_scan_l1(const CBlockDesc* __restrict__ cblocks,
                                                           uint32_t* __restrict__ hist,
                                                           uint32_t* __restrict__ cbsum)
@@ -589,89 +755,84 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_l1(const CBlockDesc* __re
 #pragma unroll
     for (int i = 0; i < SCAN_DPT; i++) {
         const uint32_t d = threadIdx.x + i * SCAN_THREADS;
-        uint32_t run = 0;
-        uint32_t v[CBLOCK];
-#pragma unroll
-        for (int c = 0; c < CBLOCK; c++)
-            v[c] = (uint32_t)c < cb.nchunks ? hist[(uint64_t)(cb.chunk0 + c) * NB + d] : 0u;
-#pragma unroll
-        for (int c = 0; c < CBLOCK; c++) {
-            if ((uint32_t)c < cb.nchunks) hist[(uint64_t)(cb.chunk0 + c) * NB + d] = run;
-            run += v[c];
-        }
-        cbsum[(uint64_t)blockIdx.x * NB + d] = run;
+        cbsum[(uint64_t)blockIdx.x * NB + d] = scan_chunks(hist, cb.chunk0, cb.nchunks, d);
     }
 }
 
-__global__ __launch_bounds__(SCAN_THREADS) void k_scan_l2(const GroupDesc* __restrict__ groups,
+// One block per segment: level 2 of the scan for each of its sides, and its
+// children folded into one record each (rows per side, key range), written to
+// the device table `out` and, when the host plans them, to pinned host memory
+// `hout` as well. It runs before the scatter, so that the host reads the
+// records and prepares what follows while the scatter runs. direct: every
+// group has one scan block, whose chunks are scanned here instead of by
+// k_scan_l1.
+__global__ __launch_bounds__(SCAN_THREADS) void k_scan_l2(const GroupDesc* __restrict__ groups, int nside, int direct,
+                                                          uint32_t* __restrict__ hist,
                                                           uint32_t* __restrict__ cbsum,
                                                           uint32_t* __restrict__ ccount,
-                                                          uint64_t* __restrict__ cstart)
+                                                          uint64_t* __restrict__ cstart,
+                                                          const uint64_t* __restrict__ gmin,
+                                                          const uint64_t* __restrict__ gmax,
+                                                          ChildRec* __restrict__ out, ChildRec* __restrict__ hout,
+                                                          const uint32_t* __restrict__ miss,
+                                                          uint64_t* __restrict__ hmiss)
 {
     __shared__ uint32_t tmp[SCAN_THREADS / 64];
-    const GroupDesc g = groups[blockIdx.x];
-    const uint32_t nbins = 1u << g.bits;
-    uint32_t tot[SCAN_DPT];
-    uint32_t local = 0;
+    ChildRec rec[SCAN_DPT];
+#pragma unroll
+    for (int i = 0; i < SCAN_DPT; i++) rec[i] = ChildRec{0, 0, ~0ull, 0};
+    uint32_t nbins = 0;
+    uint64_t at0 = 0;
+    for (int side = 0; side < nside; side++) {
+        const GroupDesc g = groups[blockIdx.x * nside + side];
+        nbins = 1u << g.bits;
+        if (side == 0) at0 = g.child0 / nside;
+        uint32_t tot[SCAN_DPT];
+        uint32_t local = 0;
+#pragma unroll
+        for (int i = 0; i < SCAN_DPT; i++) {
+            // contiguous digits per thread keep the block scan in digit order
+            const uint32_t d = threadIdx.x * SCAN_DPT + i;
+            uint32_t run = 0;
+            if (direct) {
+                run = scan_chunks(hist, g.chunk0, g.nchunks, d);
+                if (g.nchunks) cbsum[(uint64_t)g.cblock0 * NB + d] = 0;
+            } else {
+                for (uint32_t b = 0; b < g.ncblocks; b++) {
+                    const uint64_t at = (uint64_t)(g.cblock0 + b) * NB + d;
+                    const uint32_t v = cbsum[at];
+                    cbsum[at] = run;
+                    run += v;
+                }
+            }
+            tot[i] = d < nbins ? run : 0u;
+            local += tot[i];
+        }
+        uint32_t all;
+        uint64_t ex = block_excl_scan<SCAN_THREADS>(local, tmp, &all);
+#pragma unroll
+        for (int i = 0; i < SCAN_DPT; i++) {
+            const uint32_t d = threadIdx.x * SCAN_DPT + i;
+            if (d < nbins) {
+                ccount[g.child0 + d] = tot[i];
+                cstart[g.child0 + d] = g.dst_start + ex;
+                const uint64_t lo = gmin[g.child0 + d], hi = gmax[g.child0 + d];
+                if (side == 0) rec[i].rn = tot[i];
+                else rec[i].sn = tot[i];
+                rec[i].lo = lo < rec[i].lo ? lo : rec[i].lo;
+                rec[i].hi = hi > rec[i].hi ? hi : rec[i].hi;
+            }
+            ex += tot[i];
+        }
+    }
 #pragma unroll
     for (int i = 0; i < SCAN_DPT; i++) {
-        // contiguous digits per thread keep the block scan in digit order
         const uint32_t d = threadIdx.x * SCAN_DPT + i;
-        uint32_t run = 0;
-        for (uint32_t b = 0; b < g.ncblocks; b++) {
-            const uint64_t at = (uint64_t)(g.cblock0 + b) * NB + d;
-            const uint32_t v = cbsum[at];
-            cbsum[at] = run;
-            run += v;
-        }
-        tot[i] = d < nbins ? run : 0u;
-        local += tot[i];
+        if (d >= nbins) continue;
+        out[at0 + d] = rec[i];
+        if (hout) hout[at0 + d] = rec[i];
     }
-    uint32_t all;
-    uint64_t ex = block_excl_scan<SCAN_THREADS>(local, tmp, &all);
-#pragma unroll
-    for (int i = 0; i < SCAN_DPT; i++) {
-        const uint32_t d = threadIdx.x * SCAN_DPT + i;
-        if (d < nbins) {
-            ccount[g.child0 + d] = tot[i];
-            cstart[g.child0 + d] = g.dst_start + ex;
-        }
-        ex += tot[i];
-    }
-}
-
-// one block per segment, one thread per digit
-__global__ __launch_bounds__(NB) void k_children(const GroupDesc* __restrict__ groups, int nside,
-                                                 const uint32_t* __restrict__ ccount,
-                                                 const uint64_t* __restrict__ gmin,
-                                                 const uint64_t* __restrict__ gmax,
-                                                 ChildRec* __restrict__ out)
-{
-    const GroupDesc g0 = groups[blockIdx.x * nside];
-    const uint32_t d = threadIdx.x;
-    if (d >= (1u << g0.bits)) return;
-    ChildRec c;
-    c.rn = ccount[g0.child0 + d];
-    c.lo = gmin[g0.child0 + d];
-    c.hi = gmax[g0.child0 + d];
-    c.sn = 0;
-    if (nside == 2) {
-        const uint32_t c1 = groups[blockIdx.x * 2 + 1].child0 + d;
-        c.sn = ccount[c1];
-        c.lo = gmin[c1] < c.lo ? gmin[c1] : c.lo;
-        c.hi = gmax[c1] > c.hi ? gmax[c1] : c.hi;
-    }
-    out[g0.child0 / nside + d] = c;
-}
-
-hipError_t launch_children(const GroupDesc* groups, uint32_t ngroups, int nside,
-                           const uint32_t* ccount, const uint64_t* gmin, const uint64_t* gmax,
-                           ChildRec* out, hipStream_t st)
-{
-    if (ngroups == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_children, dim3(ngroups / nside), dim3(NB), 0, st, groups, nside, ccount, gmin,
-                       gmax, out);
-    return hipGetLastError();
+    if (hmiss && blockIdx.x == 0 && threadIdx.x == 0) *hmiss = *miss;
 }
 
 // ---------------------------------------------------------------------------
@@ -897,15 +1058,19 @@ hipError_t launch_batch_leaves(const GroupDesc* groups, const ChildRec* crec, co
     return hipGetLastError();
 }
 
-hipError_t launch_scan(const CBlockDesc* cblocks, uint32_t ncblocks, const GroupDesc* groups,
-                       uint32_t ngroups, uint32_t* hist, uint32_t* cbsum, uint32_t* ccount,
-                       uint64_t* cstart, hipStream_t st)
+hipError_t launch_scan(const CBlockDesc* cblocks, uint32_t ncblocks, const GroupDesc* groups, uint32_t ngroups,
+                       int nside, bool direct, uint32_t* hist, uint32_t* cbsum, uint32_t* ccount, uint64_t* cstart,
+                       const uint64_t* gmin, const uint64_t* gmax, ChildRec* out, ChildRec* hout,
+                       const uint32_t* miss, uint64_t* hmiss, hipStream_t st)
 {
     if (ncblocks == 0 || ngroups == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_scan_l1, dim3(ncblocks), dim3(SCAN_THREADS), 0, st, cblocks, hist, cbsum);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_scan_l2, dim3(ngroups), dim3(SCAN_THREADS), 0, st, groups, cbsum, ccount, cstart);
+    if (!direct) {
+        hipLaunchKernelGGL(k_scan_l1, dim3(ncblocks), dim3(SCAN_THREADS), 0, st, cblocks, hist, cbsum);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_scan_l2, dim3(ngroups / nside), dim3(SCAN_THREADS), 0, st, groups, nside, direct ? 1 : 0, hist,
+                       cbsum, ccount, cstart, gmin, gmax, out, hout, miss, hmiss);
     return hipGetLastError();
 }
 
@@ -937,8 +1102,10 @@ __global__ __launch_bounds__(SC_NT) void k_scatter(const ChunkDesc* __restrict__
                                                    const uint32_t* __restrict__ hist,
                                                    const uint32_t* __restrict__ cbsum,
                                                    const uint64_t* __restrict__ cstart,
-                                                   BufSet bufs, BktSet bkt)
+                                                   BufSet bufs, BktSet bkt, const uint32_t* __restrict__ skip)
 {
+    // (a row outside the sampled digit range: the call starts again, nothing is to be moved)
+    if (skip && *skip) return;
     constexpr int NT = SC_NT, KI = SC_KI, NW = SC_NW, TILE = SC_TILE;
     __shared__ uint32_t cnt[NW * SC_STRIDE];
     __shared__ uint32_t spare[NT];  // one private counter per thread for rows that take no part
@@ -1103,7 +1270,8 @@ __global__ __launch_bounds__(SC_NT) void k_scatter(const ChunkDesc* __restrict__
 
 hipError_t launch_scatter(int key_bytes, int out_key_bytes, bool rids, bool keys, const ChunkDesc* chunks,
                           uint32_t nchunks, const GroupDesc* groups, const uint32_t* hist,
-                          const uint32_t* cbsum, const uint64_t* cstart, BufSet bufs, hipStream_t st)
+                          const uint32_t* cbsum, const uint64_t* cstart, BufSet bufs, const uint32_t* skip,
+                          hipStream_t st)
 {
     if (nchunks == 0) return hipSuccess;
     if (out_key_bytes > key_bytes) return hipErrorInvalidValue;
@@ -1111,7 +1279,7 @@ hipError_t launch_scatter(int key_bytes, int out_key_bytes, bool rids, bool keys
     const BktSet none{};
 #define TJ_SC(K, KO, R, W)                                                                           \
     hipLaunchKernelGGL((k_scatter<K, KO, R, W, false>), grid, block, 0, st, chunks, groups, hist, cbsum, cstart, \
-                       bufs, none)
+                       bufs, none, skip)
     if (key_bytes == 4) {
         if (!keys) TJ_SC(int32_t, int32_t, true, false);
         else if (rids) TJ_SC(int32_t, int32_t, true, true);
@@ -1136,7 +1304,7 @@ hipError_t launch_learned_scatter(int key_bytes, bool rids, const ChunkDesc* chu
     const dim3 grid(nchunks), block(SC_NT);
 #define TJ_SCL(K, R)                                                                                  \
     hipLaunchKernelGGL((k_scatter<K, K, R, true, true>), grid, block, 0, st, chunks, groups, hist, cbsum,  \
-                       cstart, bufs, bkt)
+                       cstart, bufs, bkt, nullptr)
     if (key_bytes == 4) {
         if (rids) TJ_SCL(int32_t, true);
         else TJ_SCL(int32_t, false);
@@ -1588,25 +1756,6 @@ hipError_t launch_leaf_sort(int key_bytes, bool wide, const LeafDesc* leaves, ui
     return hipGetLastError();
 }
 
-// Smallest and largest ordinal of the block's rows, from each thread's own.
-template <int NT>
-__device__ __forceinline__ void block_minmax64(uint64_t& lo, uint64_t& hi, uint64_t* tmp)
-{
-    constexpr int NW = NT / 64;
-    lo = wave_min64(lo);
-    hi = wave_max64(hi);
-    if ((threadIdx.x & 63) == 0) tmp[threadIdx.x / 64] = lo;
-    lds_barrier();
-#pragma unroll
-    for (int i = 0; i < NW; i++) lo = tmp[i] < lo ? tmp[i] : lo;
-    lds_barrier();
-    if ((threadIdx.x & 63) == 0) tmp[threadIdx.x / 64] = hi;
-    lds_barrier();
-#pragma unroll
-    for (int i = 0; i < NW; i++) hi = tmp[i] > hi ? tmp[i] : hi;
-    lds_barrier();
-}
-
 // ---------------------------------------------------------------------------
 // sort of an input that fits one block: the key range, the sort and the output
 // in one launch, so that the call waits once. The time is the block's own
@@ -1706,7 +1855,9 @@ hipError_t launch_small_sort(int key_bytes, const void* keys, const int32_t* rid
 // Count mode adds the block's pair count to *total. Materialise mode takes a
 // ticket (so blocks handle buckets in key order), publishes its pair count,
 // and finds its output offset by decoupled look-back over the published
-// counts of the buckets before it; status[0] holds the offset carried in.
+// counts of the buckets before it; status[0] holds the offset carried in, and
+// the last bucket stores the pairs so far to *total. (*total and *err are then
+// pinned host memory, so that the call reads them when the stream is done.)
 // Pairs at or beyond `capacity` are not written.
 // ---------------------------------------------------------------------------
 constexpr uint64_t ST_AGG = 1ull << 62, ST_INC = 2ull << 62, ST_VAL = (1ull << 62) - 1;
@@ -1761,7 +1912,7 @@ __device__ uint64_t look_back(uint64_t* status, uint32_t slot, uint32_t* err)
         const uint64_t need = first >= 63 ? ~0ull : ((2ull << first) - 1);
         if (pending & need) {
             if (++spins > LOOKBACK_SPIN_LIMIT) {
-                if (l == 0) atomicOr(err, 1u);
+                if (l == 0) *err = 1u;
                 return 0;
             }
             __builtin_amdgcn_s_sleep(1);
@@ -1949,6 +2100,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_leaf_join(const LeafDesc* __restr
         const uint64_t excl = look_back(status, li + 1, err);
         if (threadIdx.x == 0) {
             status_store(&status[li + 1], ST_INC | (excl + ltot));
+            if (li == gridDim.x - 1) *total = excl + ltot;
             s_base = excl + L.out;
         }
     }

@@ -138,6 +138,13 @@ struct tj_server {
     std::vector<hipStream_t> streams;
     uint64_t fuse_rows = kFuseDefaultRows;       // 0: no fusion
     uint32_t fuse_requests = kFuseDefaultRequests;
+    int small_running = 0;                       // slots that run fusable requests
+
+    // Slots that run fusable requests at once, at most. A small call is over in
+    // about 0.1 ms, most of it launches and waits, and the streams share a few
+    // hardware queues: with half of the slots the others stay free for larger
+    // requests, and small ones that arrive meanwhile find partners for one call.
+    int small_limit() const { return std::max(1, slots / 2); }
 
     // Rows a request brings (both sides of a join).
     static uint64_t rows_of(const tj_request_t& r) { return r.n_r + (r.op == TJ_OP_SORT ? 0 : r.n_s); }
@@ -203,13 +210,19 @@ struct tj_server {
     // Next work a worker may start (lock held), in arrival order: the head of
     // the queue, with the queued requests it can be fused with (same op and
     // key type, small) when the arena holds the fused call; the first job of
-    // a fused batch holds the batch's arena block.
-    bool admit(std::vector<Job*>& batch)
+    // a fused batch holds the batch's arena block. While small_limit() slots
+    // run fusable requests, those at the head wait (for one of these short
+    // calls) and the first other request is the head.
+    bool admit(std::vector<Job*>& batch, bool& small)
     {
         batch.clear();
-        if (fresh.empty()) return false;
-        Job* j = fresh.front();
-        if (fusable(j)) {
+        auto head = fresh.begin();
+        if (small_running >= small_limit())
+            head = std::find_if(fresh.begin(), fresh.end(), [&](Job* k) { return !fusable(k); });
+        if (head == fresh.end()) return false;
+        Job* j = *head;
+        small = fusable(j);
+        if (small) {
             batch.push_back(j);
             uint64_t rows = rows_of(j->req);
             const uint64_t max_rows = fuse_rows * 16;
@@ -234,7 +247,7 @@ struct tj_server {
             batch.clear();
         }
         if (!reserve(j)) return false;  // the head waits for memory; nothing overtakes it
-        fresh.pop_front();
+        fresh.erase(head);
         batch.push_back(j);
         return true;
     }
@@ -398,13 +411,14 @@ struct tj_server {
         std::unique_lock<std::mutex> lk(mu);
         std::vector<Job*> batch;
         for (;;) {
-            bool got = false;
-            cv_work.wait(lk, [&] { return (got = admit(batch)) || (stopping && fresh.empty()); });
+            bool got = false, small = false;
+            cv_work.wait(lk, [&] { return (got = admit(batch, small)) || (stopping && fresh.empty()); });
             if (!got) {
                 lk.unlock();
                 tj::release_thread_staging();  // the thread ends: its pinned staging goes with it
                 return;
             }
+            if (small) small_running++;
             const auto start = Clock::now();
             for (Job* j : batch) {
                 j->admitted = start;
@@ -422,6 +436,7 @@ struct tj_server {
             }
             const auto end = Clock::now();
             lk.lock();
+            if (small) small_running--;
             arena.give(batch[0]->ws);
             batch[0]->ws = nullptr;
             for (Job* j : batch) {

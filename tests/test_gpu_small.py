@@ -43,7 +43,7 @@ def test_small_sort(tj, n, kind):
     ko, ro, st = tj.sort(dev(k), dev(r), stats=True)
     ek, er = oracle.sort(k, r)
     assert np.array_equal(ko.cpu().numpy(), ek) and np.array_equal(ro.cpu().numpy(), er)
-    assert st["passes"] == (1 if n > 8192 and kind != "equal" else 0), st
+    assert st["passes"] == (1 if n > 8192 else 0), st
 
 
 @pytest.mark.parametrize("force", [False, True])
