@@ -199,6 +199,47 @@ uint64_t min_data_bytes(const Shape& s)
 
 const uint64_t kMaxRows = (1ull << 31) - 1;
 
+// Passes whose scatter writes whole lines (k_scatter_lines) cut a segment's key
+// range into equal parts. Levels of at least LINES_MIN_ROWS rows take them,
+// when at least 3/4 of the rows are in segments of LINES_SEG_ROWS or more that
+// two levels of LN_D digits bring down to leaves.
+// leaf_fill: rows a leaf bucket is planned for where keys are even: 5 standard
+// deviations and more below LEAF_CAP, for the sort (sd 87) and for the join of
+// foreign keys of about 4 rows each (sd 180). Elsewhere half of it, so that a
+// bucket of twice the density still fits.
+constexpr uint64_t LINES_MIN_ROWS = 16ull << 20, LINES_SEG_ROWS = 1ull << 18;
+inline uint64_t leaf_fill(bool join) { return join ? 7300 : 7600; }
+inline bool lines_seg(uint64_t rows, bool even, uint64_t fill)
+{
+    if (rows < LINES_SEG_ROWS || rows > LN_D * LN_D * fill) return false;
+    const uint64_t fit = LN_D * fill;  // rows that one level brings down to leaves
+    return rows <= (even ? fit : fit / 2) || rows > 2 * fit;
+}
+
+// Digit of such a segment: shift, multiplier, digits in use. A key range of
+// few values has no multiplier; its digits are a power of two of at most 2^8.
+inline void plan_lines(uint64_t span, uint64_t rows, bool even, uint64_t fill, uint32_t& shift, uint32_t& bits,
+                       uint32_t& mul, uint32_t& ndig)
+{
+    const uint64_t leaves = (rows + fill - 1) / fill;
+    const uint64_t want = std::min<uint64_t>(LN_D, std::max<uint64_t>(2, even ? leaves : 2 * leaves));
+    shift = nbits64(span) > 32 ? nbits64(span) - 32 : 0;
+    const uint64_t t = (span >> shift) + 1;
+    mul = 0;
+    if (t >= 4096 && rows >= LINES_SEG_ROWS) {
+        mul = (uint32_t)((want << 32) / t);
+        ndig = (uint32_t)(((t - 1) * mul) >> 32) + 1;
+        bits = std::max<uint32_t>(1, nbits64(ndig - 1));
+        return;
+    }
+    plan_digit(span, rows, false, shift, bits);
+    while (bits > 8) {
+        shift++;
+        bits--;
+    }
+    ndig = 1u << bits;
+}
+
 // A child bucket is crowded (Seg::skew) when it holds more than SKEW_FACTOR
 // times the rows its parent's digit gave each bucket on average; at most
 // MAX_PIVOT_SEGS crowded buckets of a level are sampled for a pivot key.
@@ -266,6 +307,9 @@ struct Seg {
     // (buffer B): row in B minus row in buffer A of the same data, for side 0
     // (the sort's rows, R) and side 1 (S); 0 everywhere else.
     int64_t wdisp = 0, wdisp_s = 0;
+    // Its neighbours under its parent's digit hold about as many rows: keys
+    // spread evenly, so digits of equal width get about equal rows.
+    bool even = false;
     // Far more rows than its radix digit gave each bucket of its parent on
     // average: likely crowded by one frequent key (see Exec::pick_pivots).
     bool skew = false;
@@ -650,6 +694,7 @@ struct Exec {
         // per segment digit choice
         struct Plan {
             uint32_t shift, bits, kb_out;
+            uint32_t mul, ndig;  // see GroupDesc
             bool pivot;
             uint64_t key;  // the pivot's ordinal
         };
@@ -657,14 +702,32 @@ struct Exec {
         // (calls that may not allocate keep their radix digits: their launches
         // stay the ones checked for an unchanged device memory footprint)
         if (pivots && !filter && !learned && !t_noalloc) TJ_RET(pick_pivots(segs, plan));
-        uint64_t total_rows = 0;
+        uint64_t total_rows = 0, line_rows = 0;
+        for (const Seg& s : segs) {
+            total_rows += s.rn + s.sn;
+            if (lines_seg(s.rn + s.sn, s.even, leaf_fill(sh.join))) line_rows += s.rn + s.sn;
+        }
+        const bool lines = !filter && !learned && !root && write_keys && total_rows >= LINES_MIN_ROWS &&
+                           line_rows >= total_rows / 4 * 3;
+        if (filter) total_rows = sh.n_r + sh.n_s;
+        bool all_narrow = true;  // (lines) every segment of 8-byte keys can narrow them
         for (size_t i = 0; i < segs.size(); i++) {
             const Seg& s = segs[i];
+            plan[i].mul = 0;
             if (plan[i].pivot) {  // three children: below, equal to, above the pivot; keys keep their width
                 plan[i].shift = 0;
                 plan[i].bits = 2;
+                plan[i].ndig = 4;
                 plan[i].kb_out = s.kb;
-                total_rows += s.rn + s.sn;
+                all_narrow = all_narrow && s.kb == 4;
+                continue;
+            }
+            if (lines) {
+                Plan& pl = plan[i];
+                plan_lines(s.hi - s.lo, s.rn + s.sn, s.even, leaf_fill(sh.join), pl.shift, pl.bits, pl.mul, pl.ndig);
+                const bool fits = pl.shift <= 32 && (((pl.mul ? (1ull << 32) / pl.mul + 1 : 1) << pl.shift) <= (1ull << 32));
+                pl.kb_out = sh.join && s.kb == 8 && fits ? 4u : s.kb;
+                all_narrow = all_narrow && pl.kb_out == 4;
                 continue;
             }
             plan_digit(s.hi - s.lo, s.rn + s.sn, segs.size() <= FEW_SEGS, plan[i].shift, plan[i].bits);
@@ -682,8 +745,11 @@ struct Exec {
                 plan[i].shift = 0;
                 plan[i].kb_out = s.kb;
             }
-            total_rows += filter ? (uint64_t)(i == 0 ? sh.n_r + sh.n_s : 0) : s.rn + s.sn;
+            plan[i].ndig = 1u << plan[i].bits;
         }
+        // (one written key width a launch, in key order)
+        if (lines && !all_narrow)
+            for (size_t i = 0; i < segs.size(); i++) plan[i].kb_out = segs[i].kb;
         // Device batching pays where the children are many: one wave per
         // segment batches them (tens of microseconds for a level), while the
         // host needs about 5 ns per child. Children too large for a leaf are
@@ -693,6 +759,12 @@ struct Exec {
             if (sg.wdisp || sg.wdisp_s) dev_ok = false;  // device leaves: one buffer mapping
         uint64_t ch_rows = align_up((total_rows + TARGET_CHUNKS - 1) / TARGET_CHUNKS, PART_TILE);
         if (ch_rows < PART_TILE) ch_rows = PART_TILE;
+        if (lines) {
+            // several tiles a chunk (its first and last lines of each digit are
+            // written in part), but two chunks for every CU
+            ch_rows = align_up((total_rows + TARGET_CHUNKS - 1) / TARGET_CHUNKS, LN_TILE);
+            ch_rows = std::max<uint64_t>(ch_rows, std::min<uint64_t>(4 * LN_TILE, align_up(total_rows / 512, LN_TILE)));
+        }
         // make sure the largest group fits the chunk table
         for (size_t i = 0; i < segs.size(); i++) {
             const uint64_t lr = filter ? sh.n_r : segs[i].rn;
@@ -759,6 +831,8 @@ struct Exec {
                     g.fhi = filter ? filter[1] : ~0ull;
                     g.shift = plan[si].shift;
                     g.bits = plan[si].bits;
+                    g.mul = plan[si].mul;
+                    g.ndig = plan[si].ndig;
                     g.side = (uint32_t)side;
                     g.src = src;
                     g.dst = dst;
@@ -968,6 +1042,9 @@ struct Exec {
                 }));
             } else {
                 TJ_CK(timed(F_SCATTER, scanned * rb + written, [&] {
+                    if (lines)
+                        return launch_scatter_lines((int)kb_in, (int)kb_out, sh.rids, dc, nc, dg, d_hist, d_cbsum, d_cstart,
+                                                    bufs, spec ? d_miss : nullptr, st);
                     return launch_scatter((int)kb_in, (int)kb_out, sh.rids, write_keys, dc, nc, dg, d_hist, d_cbsum,
                                           d_cstart, bufs, spec ? d_miss : nullptr, st);
                 }));
@@ -987,6 +1064,7 @@ struct Exec {
                     groups[gi].base = hdr->lo;
                     groups[gi].shift = pl.shift;
                     groups[gi].bits = pl.bits;
+                    groups[gi].ndig = 1u << pl.bits;
                 }
                 written = 0;
                 for (const GroupDesc& g : groups)
@@ -997,7 +1075,7 @@ struct Exec {
             // narrowed by this pass; a child with more than SKEW_FACTOR times its
             // share of the parent's rows under this digit (and more than a leaf
             // holds) is crowded, except below a pivot split (those go radix).
-            auto emit_child = [&](uint32_t gi, const ChildRec& cr, uint64_t r0, uint64_t s0) {
+            auto emit_child = [&](uint32_t gi, const ChildRec& cr, uint64_t r0, uint64_t s0, bool even) {
                 const GroupDesc& g0 = groups[gi];
                 const Seg& par = segs[gseg[gi]];
                 const uint32_t seg_kb = plan[gseg[gi]].kb_out;
@@ -1015,15 +1093,18 @@ struct Exec {
                 c.koff_s = nside == 2 ? groups[gi + 1].dst_koff : 0;
                 c.wdisp = par.wdisp;
                 c.wdisp_s = par.wdisp_s;
-                const uint64_t rows = c.rn + c.sn, share = (par.rn + par.sn) >> g0.bits;
+                c.even = even;
+                const uint64_t rows = c.rn + c.sn, share = (par.rn + par.sn) / g0.ndig;
                 c.skew = !(g0.flags & GROUP_PIVOT) && c.lo < c.hi && rows > (uint64_t)LEAF_CAP &&
                          rows > SKEW_FACTOR * share;
                 if (seg_kb < kb_in && c.lo <= c.hi) {
-                    // keys now hold (ord - g.base) mod 2^32 (see k_scatter)
+                    // keys now hold (ord - g.base) mod 2^32 (see k_scatter), or count
+                    // from the child's own first key
                     const uint64_t off = c.lo - g0.base;
-                    c.win = g0.base + (off & ~0xffffffffull);
-                    c.lo = off & 0xffffffffull;
-                    c.hi = (c.hi - g0.base) & 0xffffffffull;
+                    c.win = g0.base + (g0.mul ? digit_start((uint32_t)(((off >> g0.shift) * g0.mul) >> 32), g0.shift, g0.mul)
+                                              : off & ~0xffffffffull);
+                    c.lo -= c.win;
+                    c.hi -= c.win;
                 }
                 sink(c);
             };
@@ -1058,7 +1139,7 @@ struct Exec {
                         if (b.seg >= ng / (uint32_t)nside) return TJ_E_INTERNAL;
                         const ChildRec cr{b.rn, b.sn, b.lo, b.hi};
                         emit_child(gi, cr, groups[gi].dst_start + b.r_off,
-                                   nside == 2 ? groups[gi + 1].dst_start + b.s_off : 0);
+                                   nside == 2 ? groups[gi + 1].dst_start + b.s_off : 0, false);
                     }
                     continue;
                 }
@@ -1087,9 +1168,16 @@ struct Exec {
                 const uint32_t nbins = 1u << g0.bits;
                 const ChildRec* cr = rec + g0.child0 / (uint32_t)nside;
                 uint64_t r0 = g0.dst_start, s0 = nside == 2 ? groups[gi + 1].dst_start : 0;
+                auto rows_of = [&](uint32_t d) { return (uint64_t)cr[d].rn + cr[d].sn; };
+                auto alike = [&](uint32_t d, uint32_t e) {
+                    const uint64_t a = rows_of(d), b = rows_of(e);
+                    return (a > b ? a - b : b - a) <= a / 16;
+                };
                 for (uint32_t d = 0; d < nbins; d++) {
                     if (cr[d].rn == 0 && cr[d].sn == 0) continue;  // no rows: every sink ignores it
-                    emit_child(gi, cr[d], r0, s0);
+                    const bool even = !learned && !(g0.flags & GROUP_PIVOT) && (d == 0 || alike(d, d - 1)) &&
+                                      (d + 1 >= g0.ndig || alike(d, d + 1));
+                    emit_child(gi, cr[d], r0, s0, even);
                     r0 += cr[d].rn;
                     s0 += cr[d].sn;
                 }
@@ -2141,6 +2229,14 @@ int sampled_range(Exec& x, const void* a, uint64_t na, const void* b, uint64_t n
     x.stats.bytes_read += sampled * (uint64_t)x.sh.kb;
     hi = mm[1];
     lo = mm[0];
+    if (na + nb >= LINES_MIN_ROWS && hi > lo) {
+        // digits of any width (plan_lines): both ends move out to multiples of
+        // a 64th to a 128th of the range
+        const uint32_t g = nbits64(hi - lo) > 7 ? nbits64(hi - lo) - 7 : 0;
+        lo &= ~((1ull << g) - 1);
+        hi |= (1ull << g) - 1;
+        return TJ_OK;
+    }
     // the digit width depends on the span, which depends on the rounded minimum
     for (int it = 0; it < 3; it++) {
         uint32_t shift, bits;
@@ -2799,6 +2895,7 @@ static int partition_pass_body(const int64_t* keys, const int32_t* rids, uint64_
     g.fhi = ~0ull;
     g.shift = shift;
     g.bits = bits;
+    g.ndig = 1u << bits;
     g.src = BUF_IN;
     g.dst = BUF_A;
     g.flags = (flags & TJ_DEBUG_FORCE_REORDER) ? GROUP_FORCE_REORDER : 0u;

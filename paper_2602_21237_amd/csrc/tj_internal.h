@@ -20,6 +20,8 @@ constexpr int NB = 1 << MAX_DIGIT_BITS;       // digit bins per group (table str
 constexpr int PART_THREADS = 1024;            // histogram block
 constexpr int PART_TILE = 9216;               // rows per scatter tile (chunks are multiples)
 constexpr int CBLOCK = 32;                    // chunks per first-level scan block
+constexpr int LN_D = 320;                     // digits of a group that is scattered in whole lines, at most
+constexpr int LN_TILE = 8192;                 // rows per tile of that scatter
 
 enum Buf : uint32_t { BUF_IN = 0, BUF_A = 1, BUF_B = 2 };
 
@@ -70,12 +72,20 @@ struct GroupDesc {
     uint32_t cblock0, ncblocks;
     uint32_t child0;     // first entry of this group's children in the packed child tables
     uint32_t flags;      // GROUP_* bits
+    uint32_t mul;        // nonzero: digit = ((ord - base) >> shift) * mul >> 32, the first factor below 2^32
+    uint32_t ndig;       // digits in use (at most 1 << bits)
     uint32_t pad;
     // Key arrays are addressed at (row + koff). Keys narrowed to 4 bytes are
     // kept inside the byte footprint of the 8-byte keys of the bucket that
     // narrowed them: koff = that bucket's first row (see the planner).
     uint64_t src_koff, dst_koff;
 };
+
+// First (ord - base) of digit d of a group with a multiplier.
+__host__ __device__ inline uint64_t digit_start(uint32_t d, uint32_t shift, uint32_t mul)
+{
+    return ((((uint64_t)d << 32) + mul - 1) / mul) << shift;
+}
 
 // One per-bucket LDS block: a run of adjacent final buckets of one level.
 struct LeafDesc {
@@ -280,6 +290,11 @@ hipError_t launch_scatter(int key_bytes, int out_key_bytes, bool rids, bool keys
                           uint32_t nchunks, const GroupDesc* groups, const uint32_t* hist,
                           const uint32_t* cbsum, const uint64_t* cstart, BufSet bufs, const uint32_t* skip,
                           hipStream_t st);
+// The same, written in whole lines (k_scatter_lines): every group has at most LN_D digits in use, no filter
+// (flo, fhi), and the same written key width (no GROUP_WIDE); keys are written.
+hipError_t launch_scatter_lines(int key_bytes, int out_key_bytes, bool rids, const ChunkDesc* chunks, uint32_t nchunks,
+                                const GroupDesc* groups, const uint32_t* hist, const uint32_t* cbsum,
+                                const uint64_t* cstart, BufSet bufs, const uint32_t* skip, hipStream_t st);
 // Scatter of the learned pass: digits are read from bkt (no narrowing).
 hipError_t launch_learned_scatter(int key_bytes, bool rids, const ChunkDesc* chunks, uint32_t nchunks,
                                   const GroupDesc* groups, const uint32_t* hist, const uint32_t* cbsum,

@@ -69,6 +69,14 @@ __device__ __forceinline__ T ld_clamp(const T* __restrict__ p, uint64_t q, uint6
     return p[q < n ? q : n - 1];
 }
 
+// p[i] for a byte offset below 2^32: a uniform base and a 32-bit offset a lane,
+// where 64-bit addresses would take two registers for every load in flight.
+template <typename T>
+__device__ __forceinline__ T at32(const T* __restrict__ p, uint32_t i)
+{
+    return *(const T*)((const char*)p + (uint32_t)(i * (uint32_t)sizeof(T)));
+}
+
 // Inclusive prefix sum across the 64 lanes with DPP: shifts of 1, 2, 4, 8
 // inside each row of 16 lanes, then row_bcast:15 carries row totals into rows
 // 1 and 3 and row_bcast:31 carries the first half's total into rows 2 and 3.
@@ -534,10 +542,14 @@ hipError_t launch_read_ords(const KeyRef* refs, uint32_t n, uint64_t* out, hipSt
 
 // Digit of ordinal o in a group: its radix digit, or in a pivot group
 // (GROUP_PIVOT) its side of the pivot key `base`: 0 below, 1 equal, 2 above.
+// With a multiplier (GroupDesc::mul) the digits cut the key range into any
+// number of equal parts instead of a power of two.
 __device__ __forceinline__ uint32_t group_digit(uint64_t o, uint64_t base, uint32_t shift, uint32_t mask,
-                                                bool pivot)
+                                                bool pivot, uint32_t mul = 0)
 {
-    return pivot ? (uint32_t)(o >= base) + (uint32_t)(o > base) : (uint32_t)((o - base) >> shift) & mask;
+    if (pivot) return (uint32_t)(o >= base) + (uint32_t)(o > base);
+    const uint64_t t = (o - base) >> shift;
+    return (mul ? __umulhi((uint32_t)t, mul) : (uint32_t)t) & mask;
 }
 
 // ---------------------------------------------------------------------------
@@ -640,8 +652,12 @@ __global__ __launch_bounds__(NT) void k_hist(const ChunkDesc* __restrict__ chunk
             const bool valid = q < ch.len && o >= g.flo && o <= g.fhi;
             uint32_t d;
             if (LEARNED) d = valid ? lb[LEARNED ? u : 0] : 0u;
-            else d = valid ? group_digit(o, g.base, g.shift, nbins - 1u, pivot) : 0u;
-            if (check) miss = miss || (valid && (o < g.base || ((o - g.base) >> g.shift) >= nbins));
+            else d = valid ? group_digit(o, g.base, g.shift, nbins - 1u, pivot, g.mul) : 0u;
+            if (check) {
+                const uint64_t t = (o - g.base) >> g.shift;
+                miss = miss || (valid && (o < g.base || t > 0xffffffffull ||
+                                          (g.mul ? __umulhi((uint32_t)t, g.mul) : (uint32_t)t) >= g.ndig));
+            }
             const uint64_t vm = ballot(valid);
             if (vm == 0) continue;
             const int first = __ffsll((unsigned long long)vm) - 1;
@@ -886,10 +902,17 @@ __global__ __launch_bounds__(64) void k_batch_leaves(const GroupDesc* __restrict
         uint64_t clo = c.lo, chi = c.hi;
         win[j] = 0;
         if (a.narrowing && rows[j]) {
-            const uint64_t off = clo - g0.base;
-            win[j] = (uint32_t)(off >> 32);
-            clo = off & 0xffffffffull;
-            chi = (chi - g0.base) & 0xffffffffull;
+            if (g0.mul) {  // each child has its own window, from the child's first key
+                const uint64_t w0 = g0.base + digit_start(d, g0.shift, g0.mul);
+                win[j] = d;
+                clo -= w0;
+                chi -= w0;
+            } else {
+                const uint64_t off = clo - g0.base;
+                win[j] = (uint32_t)(off >> 32);
+                clo = off & 0xffffffffull;
+                chi = (chi - g0.base) & 0xffffffffull;
+            }
         }
         lo[j] = clo;
         const uint32_t both = c.rn > 0 && c.sn > 0 ? 1u : 0u;
@@ -1266,6 +1289,354 @@ __global__ __launch_bounds__(SC_NT) void k_scatter(const ChunkDesc* __restrict__
             lds_barrier();
         }
     }
+}
+
+// ---------------------------------------------------------------------------
+// scatter in whole lines, for passes whose chunks are several tiles long and
+// whose groups have at most LN_D digits. What bounds a scatter is its writes:
+// at 512 digits a 9216-row tile ends 18 rows a digit, and runs that begin and
+// end inside 128-byte lines reach 2.7 TB/s (reads and writes together) whatever
+// the tile does meanwhile, while the same rows cut at line boundaries (16 keys
+// of 8 bytes, 32 of 4, 32 row ids) reach 5.0, at any number of digits. So the
+// rows of a digit that do not fill a line stay behind in LDS until the next
+// tile: each digit has room for one line of keys and one of row ids (256
+// bytes; 320 digits: 80 KiB), and only a chunk's first and last line of a
+// digit are written in part. Keys and row ids are staged one after the other
+// in the same 64 KiB.
+//
+// One block fills a CU, so nothing else hides its waits, and a wave's loads and
+// stores count in one counter, so that a load which stores follow is waited for
+// together with them. So a tile's rows are loaded while the tile before leaves,
+// a third of them at a time, and waited for once, at the tile's start. (Loads
+// issued where they are next used, with a wait for keys and one for row ids a
+// tile: 3.2 TB/s; all at once: 3.4; in thirds: 3.7. Half of the waves loading
+// and half writing: 16-row threads spill, 0.8.)
+//
+// Measured, 2^29 rows of a 64-bit key and a row id, a pass: 4.80 ms in
+// k_scatter, 3.50 here (3.7 TB/s of 24 bytes a row); 2^27 + 2^29 join rows, two
+// passes (8-byte keys narrowed, then 4-byte ones): 10.3 -> 9.0 ms. What is left
+// over the 5.0 TB/s is the tile's LDS work, mostly of the ranking and staging.
+//
+// Ranks, stability and narrowed keys as in k_scatter, with 16-bit counters (in
+// the staging space, which is free then); a row's order is checked on staged
+// (digit, index) words, which increase strictly over the whole tile.
+// Destination rows are counted from the line boundary at or before the column's
+// start: v = row + phase. Line v / G of a digit is written by consecutive
+// lanes, from the carried rows (v below the digit's cursor) and the staged ones.
+// ---------------------------------------------------------------------------
+constexpr int LN_NT = 1024, LN_KI = 8, LN_NW = LN_NT / 64;
+constexpr int LN_CS = LN_D + 2;  // 16-bit counters of a wave
+static_assert(LN_TILE == LN_NT * LN_KI, "chunk sizes are planned in tiles");
+static_assert(LN_D * LN_NW % LN_NT == 0 && LN_D <= LN_NT && LN_D % 2 == 0, "counters split evenly over the block");
+
+// One line of a tile's output, for G = 2^LG rows of one column:
+//   x: line number << LG | first slot that is this chunk's;
+//   y: digit | (staged position of slot 0 + 32) << 9 | carried slots << 23.
+// The thread t of digit t writes its lines' words; `at`, `n`: its first line in
+// the tile's list and their number; cur, first: destination rows of its first
+// staged row and of the chunk's first row; tex: its first staged position.
+template <int LG>
+__device__ __forceinline__ void list_lines(uint2* lin, uint32_t at, uint32_t n, uint32_t cur, uint32_t first,
+                                           uint32_t tex, uint32_t phase, uint32_t t, uint32_t l)
+{
+    constexpr uint32_t G = 1u << LG;
+    const uint32_t line = (cur + phase) >> LG, c = (cur + phase) & (G - 1);
+    const uint32_t skip = (first + phase) >> LG == line ? (first + phase) & (G - 1) : 0u;
+    const uint32_t pos = tex + 32u - c;
+    auto put = [&](uint32_t i, uint32_t at_, uint32_t line_, uint32_t skip_, uint32_t pos_, uint32_t c_, uint32_t d) {
+        lin[at_ + i] = uint2{(line_ + i) << LG | (i ? 0u : skip_), d | (pos_ + (i << LG)) << 9 | (i ? 0u : c_) << 23};
+    };
+    constexpr uint32_t OWN = 6;
+    for (uint32_t i = 0; i < OWN && i < n; i++) put(i, at, line, skip, pos, c, t);
+    uint64_t m = ballot(n > OWN);  // a digit of many lines: by its whole wave
+    while (m) {
+        const int src = __ffsll((unsigned long long)m) - 1;
+        m &= m - 1;
+        const uint32_t n_ = __shfl(n, src, 64), at_ = __shfl(at, src, 64), line_ = __shfl(line, src, 64),
+                       pos_ = __shfl(pos, src, 64), d = __shfl(t, src, 64);
+        for (uint32_t i = OWN + l; i < n_; i += 64) put(i, at_, line_, 0, pos_, 0, d);
+    }
+}
+
+// The listed lines of one column leave. The staged rows and the carried ones
+// are both in `lds` (carry: the latter's offset), so that each row is one read.
+template <typename T, int LG>
+__device__ __forceinline__ void write_lines(T* __restrict__ dst, uint32_t phase, const T* lds, uint32_t carry,
+                                            const uint2* lin, uint32_t lines, const uint32_t* s_end, bool last,
+                                            bool redo, uint32_t t)
+{
+    constexpr int U = 2;
+    constexpr uint32_t G = 1u << LG;
+    const uint32_t n = lines << LG;
+    for (uint32_t q0 = t; q0 < n; q0 += LN_NT * U) {
+        uint32_t at[U];
+        T val[U];
+        bool ok[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const uint32_t q = q0 + u * LN_NT, qc = q < n ? q : n - 1, j = qc & (G - 1);
+            const uint2 L = lin[qc >> LG];
+            const uint32_t d = L.y & 0x1ffu, row = (L.x & ~(G - 1)) + j - phase;
+            const bool staged = j >= L.y >> 23;
+            ok[u] = q < n && j >= (L.x & (G - 1)) && (!last || row < s_end[d]) && (staged || !redo);
+            val[u] = lds[staged ? min(((L.y >> 9) & 0x3fffu) + j - 32u, (uint32_t)LN_TILE - 1u) : carry + (d << LG) + j];
+            at[u] = row;
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++)
+            if (ok[u]) dst[at[u]] = val[u];
+    }
+}
+
+template <typename K, typename KO, bool RIDS>
+__global__ __launch_bounds__(LN_NT) void k_scatter_lines(const ChunkDesc* __restrict__ chunks,
+                                                         const GroupDesc* __restrict__ groups,
+                                                         const uint32_t* __restrict__ hist,
+                                                         const uint32_t* __restrict__ cbsum,
+                                                         const uint64_t* __restrict__ cstart, BufSet bufs,
+                                                         const uint32_t* __restrict__ skip)
+{
+    if (skip && *skip) return;
+    constexpr int NT = LN_NT, KI = LN_KI, NW = LN_NW, TILE = LN_TILE, D = LN_D, CS = LN_CS;
+    constexpr int LGK = sizeof(KO) == 8 ? 4 : 5, LGR = 5;
+    constexpr int GK = 1 << LGK, GR = 1 << LGR;
+    constexpr bool NARROW = sizeof(KO) < sizeof(K);
+    // staged keys, or staged row ids and order words, or the rank counters;
+    // then each digit's carried line of keys, and of row ids
+    constexpr int STAGE = TILE * (RIDS || sizeof(KO) == 8 ? 8 : 4);
+    __shared__ __align__(16) char lds[STAGE + D * 128 + (RIDS ? D * 128 : 0)];
+    // lines: a digit's n rows, up to G - 1 carried and, at a chunk's end, up to G - 1 that are not there
+    __shared__ uint2 lin[TILE / GK + 2 * D];
+    __shared__ uint32_t s_first[D], s_end[D], s_keep[D];
+    __shared__ uint32_t s_sub[NARROW ? D : 1];
+    __shared__ uint32_t tmp[NW];
+    __shared__ uint32_t s_unordered;
+    static_assert(STAGE >= NW * CS * 2, "the counters share the staging space");
+    uint16_t* const cnt = (uint16_t*)lds;
+    KO* const skey = (KO*)lds;
+    int32_t* const srid = (int32_t*)lds;
+    uint32_t* const stag = (uint32_t*)lds + TILE;
+    constexpr uint32_t CK = STAGE / sizeof(KO), CR = (STAGE + D * 128) / 4;  // offsets of the carried rows
+
+    const ChunkDesc ch = chunks[blockIdx.x];
+    const GroupDesc g = groups[ch.group];
+    const K* __restrict__ src_k = (const K*)bufs.key[g.src][g.side] + g.src_koff + ch.start;
+    const int32_t* __restrict__ src_r = RIDS ? bufs.rid[g.src][g.side] + ch.start : nullptr;
+    KO* __restrict__ dst_k = (KO*)bufs.key[g.dst][g.side] + g.dst_koff;
+    int32_t* __restrict__ dst_r = (int32_t*)bufs.rid[g.dst][g.side];
+    const uint32_t phk = (uint32_t)((uintptr_t)dst_k % 128 / sizeof(KO));
+    const uint32_t phr = RIDS ? (uint32_t)((uintptr_t)dst_r % 128 / 4) : 0u;
+    const uint32_t nbins = min(1u << g.bits, (uint32_t)D);
+    const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
+    uint32_t t = threadIdx.x, l = t & 63;
+    const bool pivot = (g.flags & GROUP_PIVOT) != 0, force = (g.flags & GROUP_FORCE_REORDER) != 0;
+
+    // thread d keeps digit d's cursor
+    uint32_t cur = 0;
+    if (t < nbins)
+        cur = (uint32_t)(cstart[g.child0 + t] + cbsum[(uint64_t)ch.cblock * NB + t] + hist[(uint64_t)blockIdx.x * NB + t]);
+    if (t < nbins) s_first[t] = cur;
+    if (NARROW && t < D)
+        s_sub[t] = (uint32_t)(g.base + (g.mul ? digit_start(t, g.shift, g.mul) : 0));
+
+    K key[KI];
+    int32_t rid[RIDS ? KI : 1], next_rid[RIDS ? KI : 1];
+    auto load_keys = [&](uint32_t t0, int r0, int r1) {
+#pragma unroll
+        for (int r = r0; r < r1; r++) key[r] = at32(src_k, min(t0 + (w * KI + r) * 64 + l, ch.len - 1));
+    };
+    auto load_rids = [&](int32_t (&to)[RIDS ? KI : 1], uint32_t t0) {
+        if constexpr (RIDS) {
+#pragma unroll
+            for (int r = 0; r < KI; r++) to[r] = at32(src_r, min(t0 + (w * KI + r) * 64 + l, ch.len - 1));
+        }
+    };
+    load_keys(0, 0, KI);
+    load_rids(rid, 0);
+    for (uint32_t t0 = 0; t0 < ch.len; t0 += TILE) {
+        const uint32_t rows = ch.len - t0 < (uint32_t)TILE ? ch.len - t0 : (uint32_t)TILE;
+        const bool last = t0 + TILE >= ch.len;
+        for (int redo = 0;; redo++) {
+            // (addresses derived from t and l are formed anew for every tile:
+            // kept across tiles, they would take the registers the rows need)
+            asm volatile("" : "+v"(t), "+v"(l));
+            uint32_t pd[KI];  // digit << 16 | rank in the wave, then | staged position
+            // rank inside the wave (redo: by ballots)
+            for (uint32_t i = l; i < CS / 2; i += 64) ((uint32_t*)cnt)[w * (CS / 2) + i] = 0;
+            if (redo) lds_barrier();  // (the ballots' counters are read as 16-bit words)
+            uint32_t* const cw = (uint32_t*)cnt + w * (CS / 2);
+#pragma unroll
+            for (int r = 0; r < KI; r++)
+                pd[r] = min(group_digit(ord_of(key[r]), g.base, g.shift, (1u << g.bits) - 1u, pivot, g.mul), (uint32_t)D - 1u);
+            if (!redo) {
+                uint32_t old[KI];
+#pragma unroll
+                for (int r = 0; r < KI; r++) {
+                    old[r] = 0;
+                    if ((w * KI + r) * 64 + l < rows) old[r] = atomicAdd(cw + pd[r] / 2, 1u << (pd[r] & 1) * 16);
+                }
+#pragma unroll
+                for (int r = 0; r < KI; r++) pd[r] = pd[r] << 16 | (old[r] >> (pd[r] & 1) * 16 & 0xffffu);
+            } else {
+#pragma unroll
+                for (int r = 0; r < KI; r++) {
+                    const bool val = (w * KI + r) * 64 + l < rows;
+                    const uint32_t d = pd[r];
+                    uint64_t peers = ballot(val);
+#pragma unroll 1
+                    for (int b = 0; b < MAX_DIGIT_BITS; b++) {
+                        const bool bit = (d >> b) & 1u;
+                        const uint64_t m = ballot(bit);
+                        peers &= bit ? m : ~m;
+                    }
+                    const uint32_t below = mbcnt(peers);
+                    const uint32_t base = val ? cnt[w * CS + d] : 0u;
+                    if (val && below == 0) cnt[w * CS + d] = (uint16_t)(base + __popcll(peers));
+                    pd[r] = d << 16 | (base + below);
+                }
+            }
+            // The next tile's rows arrive while this one leaves: a third of the
+            // loads here and two more below, so that they do not queue at once.
+            if (!last) load_rids(next_rid, t0 + TILE);
+            lds_barrier();
+            if (t == 0) s_unordered = 0;
+            {
+                // offsets of (digit, wave) inside the tile
+                constexpr int EPT = D * NW / NT;
+                uint32_t v[EPT], sum = 0, total;
+#pragma unroll
+                for (int i = 0; i < EPT; i++) {
+                    const int e = t * EPT + i;
+                    v[i] = cnt[(e % NW) * CS + e / NW];
+                    sum += v[i];
+                }
+                uint32_t ex = block_excl_scan<NT>(sum, tmp, &total);
+#pragma unroll
+                for (int i = 0; i < EPT; i++) {
+                    const int e = t * EPT + i;
+                    cnt[(e % NW) * CS + e / NW] = (uint16_t)ex;
+                    ex += v[i];
+                }
+            }
+            lds_barrier();
+#pragma unroll
+            for (int r = 0; r < KI; r++) pd[r] += cnt[w * CS + (pd[r] >> 16)];
+            uint32_t tex = 0, end = 0, ngk = 0, ngr = 0;
+            if (t < nbins) {
+                tex = cnt[t];
+                end = cur + (t + 1 < (uint32_t)D ? cnt[t + 1] : rows) - tex;
+                ngk = (end + phk + (last ? GK - 1 : 0)) / GK - (cur + phk) / GK;
+                if (RIDS) ngr = (end + phr + (last ? GR - 1 : 0)) / GR - (cur + phr) / GR;
+            }
+            uint32_t lines;
+            const uint32_t g0 = block_excl_scan<NT>(ngk | ngr << 16, tmp, &lines);  // barriers: the counters are read
+            asm volatile("" : "+v"(t), "+v"(l));
+            list_lines<LGK>(lin, g0 & 0xffffu, ngk, cur, t < nbins ? s_first[t] : 0u, tex, phk, t, l);
+            if (t < nbins) {
+                // rows from these staged positions (+ 32) on do not fill a line
+                const uint32_t kk = tex + 32u + (end + phk) / GK * GK - (cur + phk);
+                const uint32_t kr = RIDS ? tex + 32u + (end + phr) / GR * GR - (cur + phr) : 0u;
+                s_keep[t] = kk | kr << 16;
+                s_end[t] = end;
+            }
+#pragma unroll
+            for (int r = 0; r < KI; r++) {
+                if ((w * KI + r) * 64 + l < rows) {
+                    if constexpr (NARROW) skey[pd[r] & 0xffffu] = (KO)(((uint32_t)ord_of(key[r]) - s_sub[pd[r] >> 16]) ^ 0x80000000u);
+                    else skey[pd[r] & 0xffffu] = (KO)key[r];
+                }
+            }
+            if (!last) load_keys(t0 + TILE, 0, KI / 2);
+            lds_barrier();
+            write_lines<KO, LGK>(dst_k, phk, skey, CK, lin, lines & 0xffffu, s_end, last, redo != 0, t);
+            lds_barrier();
+            if (!last) {
+                load_keys(t0 + TILE, KI / 2, KI);
+                // (a tile that is not the last is full)
+#pragma unroll
+                for (int r = 0; r < KI; r++) {
+                    const uint32_t d = pd[r] >> 16, p = pd[r] & 0xffffu, s = p + 32u - (s_keep[d] & 0xffffu);
+                    if ((int32_t)s >= 0) skey[CK + d * GK + s] = skey[p];
+                }
+            }
+            if constexpr (!RIDS) {
+                lds_barrier();
+                break;  // (a count does not depend on the order of equal digits)
+            }
+            if constexpr (RIDS) {
+                asm volatile("" : "+v"(t), "+v"(l));
+                lds_barrier();
+                {
+                    // (formed again from LDS: kept, they would cost registers)
+                    uint32_t n = 0, at = 0, f = 0;
+                    if (t < nbins) {
+                        const uint32_t e = s_end[t];
+                        n = (e + phr + (last ? GR - 1 : 0)) / GR - (cur + phr) / GR;
+                        at = (s_keep[t] >> 16) - 32u - (e + phr) / GR * GR + (cur + phr);  // its first staged position
+                        f = s_first[t];
+                    }
+                    list_lines<LGR>(lin, g0 >> 16, n, cur, f, at, phr, t, l);
+                }
+#pragma unroll
+                for (int r = 0; r < KI; r++) {
+                    const uint32_t x = (w * KI + r) * 64 + l;
+                    if (x < rows) {
+                        srid[pd[r] & 0xffffu] = rid[r];
+                        stag[pd[r] & 0xffffu] = (pd[r] & 0xffff0000u) | x;
+                    }
+                }
+                lds_barrier();
+                bool unordered = false;
+#pragma unroll
+                for (int r = 0; r < KI; r++) {
+                    const uint32_t p = r * NT + t;
+                    const uint32_t tag = stag[p];
+                    uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)tag, 0x138, 0xf, 0xf, false);  // wave_shr:1
+                    if (l == 0 && p) prev = stag[p - 1];
+                    unordered = unordered || (p > 0 && p < rows && prev >= tag);
+                }
+                if (unordered) s_unordered = 1;
+                write_lines<int32_t, LGR>(dst_r, phr, srid, CR, lin, lines >> 16, s_end, last, redo != 0, t);
+                lds_barrier();
+                if (!last) {
+#pragma unroll
+                    for (int r = 0; r < KI; r++) {
+                        const uint32_t d = pd[r] >> 16, s = (pd[r] & 0xffffu) + 32u - (s_keep[d] >> 16);
+                        if ((int32_t)s >= 0) srid[CR + d * GR + s] = rid[r];
+                    }
+                }
+                if (redo || !(s_unordered || force)) break;
+                load_keys(t0, 0, KI);
+            }
+        }
+        if constexpr (RIDS) {
+#pragma unroll
+            for (int r = 0; r < KI; r++) rid[r] = next_rid[r];
+        }
+        if (t < nbins) cur = s_end[t];
+    }
+}
+
+hipError_t launch_scatter_lines(int key_bytes, int out_key_bytes, bool rids, const ChunkDesc* chunks, uint32_t nchunks,
+                                const GroupDesc* groups, const uint32_t* hist, const uint32_t* cbsum,
+                                const uint64_t* cstart, BufSet bufs, const uint32_t* skip, hipStream_t st)
+{
+    if (nchunks == 0) return hipSuccess;
+    if (out_key_bytes > key_bytes) return hipErrorInvalidValue;
+#define TJ_SL(K, KO, R) \
+    hipLaunchKernelGGL((k_scatter_lines<K, KO, R>), dim3(nchunks), dim3(LN_NT), 0, st, chunks, groups, hist, cbsum, cstart, bufs, skip)
+    if (key_bytes == 4) {
+        if (rids) TJ_SL(int32_t, int32_t, true);
+        else TJ_SL(int32_t, int32_t, false);
+    } else if (out_key_bytes == 8) {
+        if (rids) TJ_SL(int64_t, int64_t, true);
+        else TJ_SL(int64_t, int64_t, false);
+    } else {
+        if (rids) TJ_SL(int64_t, int32_t, true);
+        else TJ_SL(int64_t, int32_t, false);
+    }
+#undef TJ_SL
+    return hipGetLastError();
 }
 
 hipError_t launch_scatter(int key_bytes, int out_key_bytes, bool rids, bool keys, const ChunkDesc* chunks,
