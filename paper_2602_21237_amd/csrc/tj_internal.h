@@ -67,19 +67,19 @@ struct GroupDesc {
     uint32_t shift;      // digit = (ord - base) >> shift (GROUP_PIVOT: the side of base)
     uint32_t bits;       // digit width, nbins = 1 << bits
     uint32_t side;       // column set: 0 = R / sorted relation, 1 = S
-    uint32_t src, dst;   // buffers
+    uint16_t src, dst;   // buffers
     uint32_t chunk0, nchunks;
     uint32_t cblock0, ncblocks;
     uint32_t child0;     // first entry of this group's children in the packed child tables
     uint32_t flags;      // GROUP_* bits
     uint32_t mul;        // nonzero: digit = ((ord - base) >> shift) * mul >> 32, the first factor below 2^32
     uint32_t ndig;       // digits in use (at most 1 << bits)
-    uint32_t pad;
     // Key arrays are addressed at (row + koff). Keys narrowed to 4 bytes are
     // kept inside the byte footprint of the 8-byte keys of the bucket that
     // narrowed them: koff = that bucket's first row (see the planner).
     uint64_t src_koff, dst_koff;
 };
+static_assert(sizeof(GroupDesc) == 112, "workspace sizes count on it");
 
 // First (ord - base) of digit d of a group with a multiplier.
 __host__ __device__ inline uint64_t digit_start(uint32_t d, uint32_t shift, uint32_t mul)
