@@ -77,6 +77,15 @@ __device__ __forceinline__ T at32(const T* __restrict__ p, uint32_t i)
     return *(const T*)((const char*)p + (uint32_t)(i * (uint32_t)sizeof(T)));
 }
 
+// at32, issued where it stands: the compiler moves plain loads to their first
+// use and waits on each one there.
+template <typename T>
+__device__ __forceinline__ T ld_now(const T* __restrict__ p, uint32_t i)
+{
+    return __hip_atomic_load((const T*)((const char*)p + (uint32_t)(i * (uint32_t)sizeof(T))), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+
 // Inclusive prefix sum across the 64 lanes with DPP: shifts of 1, 2, 4, 8
 // inside each row of 16 lanes, then row_bcast:15 carries row totals into rows
 // 1 and 3 and row_bcast:31 carries the first half's total into rows 2 and 3.
@@ -1723,8 +1732,9 @@ constexpr int LBINS = 256, LSTRIDE = LBINS + 1;
 // 1024 threads x 8 rows (97 KB, one block of 16 waves per CU). The smaller
 // capacities are for inputs of one block, where nothing but the block's own
 // latency counts: 4 rows a thread.
-template <typename KW, int C = LEAF_CAP> struct LeafShape {
-    static constexpr int NT = C < LEAF_CAP ? C / 4 : sizeof(KW) == 4 ? 512 : 1024;
+// (A join block has 1024 threads x 8 rows with either key word: FULL.)
+template <typename KW, int C = LEAF_CAP, bool FULL = false> struct LeafShape {
+    static constexpr int NT = C < LEAF_CAP ? C / 4 : sizeof(KW) == 4 && !FULL ? 512 : 1024;
     static constexpr int KI = C / NT;
     static constexpr int NW = NT / 64;
     static constexpr int NBB = C == 1024 ? 10 : C == 4096 ? 12 : sizeof(KW) == 4 ? 12 : 13;  // bin bits of block_bin_sort
@@ -2216,12 +2226,14 @@ hipError_t launch_small_sort(int key_bytes, const void* keys, const int32_t* rid
 }
 
 // ---------------------------------------------------------------------------
-// per-bucket join. The block loads R's rows (positions 0..rn-1) and then S's
-// rows (rn..rn+sn-1) of its co-partition and sorts them together, stably, by
-// key: every key then forms one run [R rows in input order][S rows in input
-// order]. A run with a R rows and b S rows contributes a*b pairs; R row i of
-// the run owns the b consecutive output slots of its pairs, so the output is
-// key-ascending, R-major, S in input order.
+// per-bucket join of one block: R's rows and S's rows of its co-partition. The
+// rows of one key form a run; a run with a R rows and b S rows contributes a*b
+// pairs, and R row i of the run owns the b consecutive output slots of its
+// pairs, so the output is key-ascending, R-major, S in input order. k_leaf_join
+// sorts the side of fewer rows and looks the other side's rows up in it;
+// join_sorted sorts both together, stably, by key (R's rows at positions
+// 0..rn-1, S's at rn..rn+sn-1), which makes every run
+// [R rows in input order][S rows in input order].
 //
 // Count mode adds the block's pair count to *total. Materialise mode takes a
 // ticket (so blocks handle buckets in key order), publishes its pair count,
@@ -2234,16 +2246,6 @@ hipError_t launch_small_sort(int key_bytes, const void* keys, const int32_t* rid
 constexpr uint64_t ST_AGG = 1ull << 62, ST_INC = 2ull << 62, ST_VAL = (1ull << 62) - 1;
 constexpr uint64_t LOOKBACK_SPIN_LIMIT = 1ull << 22;
 constexpr uint32_t COOP_PAIRS = 16;  // R rows with more pairs are written by their whole wave
-
-template <typename KW>
-__device__ __forceinline__ uint32_t lds_upper_bound(const KW* a, uint32_t lo, uint32_t hi, KW k)
-{
-    while (lo < hi) {
-        const uint32_t m = (lo + hi) >> 1;
-        if (a[m] <= k) lo = m + 1; else hi = m;
-    }
-    return lo;
-}
 
 // A status word carries its whole message (flag and value in one 64-bit word)
 // and no other data is published through it, so relaxed device-scope atomics
@@ -2295,67 +2297,83 @@ __device__ uint64_t look_back(uint64_t* status, uint32_t slot, uint32_t* err)
     }
 }
 
-// SELF (a whole input that fits one block): the leaf is `self`, whose key
-// range the block finds itself; its pairs start at 0 and their number is
-// stored to *total (in either mode). One launch then serves the whole call.
-template <typename K, typename KW, bool MAT, bool SELF = false, int C = LEAF_CAP>
-__global__ __launch_bounds__((LeafShape<KW, C>::NT))
-__attribute__((amdgpu_waves_per_eu(4))) void k_leaf_join(const LeafDesc* __restrict__ leaves,
-                                                            BufSet bufs, uint64_t* __restrict__ status,
-                                                            uint32_t* __restrict__ ticket,
-                                                            uint64_t* __restrict__ total,
-                                                            uint32_t* __restrict__ err,
-                                                            int32_t* __restrict__ out_r,
-                                                            int32_t* __restrict__ out_s,
-                                                            uint64_t capacity, LeafDesc self)
-{
-    constexpr int NT = LeafShape<KW, C>::NT, KI = LeafShape<KW, C>::KI, NW = LeafShape<KW, C>::NW;
+// Rows of a run ranked by looking at all of them; larger runs are ranked by
+// counters at a fixed cost, about that of looking at 30 rows.
+constexpr uint32_t RUN_SCAN = 32;
+
+// LDS of a join block: one pool, laid out by each of its two ways.
+template <typename KW, bool MAT, int C> struct JoinLds {
+    using SH = LeafShape<KW, C, true>;
     // (padded for the count; the materialising block keeps the plain layout:
     // the padding's address arithmetic costs it registers it does not have)
-    using KA = typename std::conditional<MAT, KeyPlain<KW, C>, KeyLds<KW, C>>::type;
-    using IA = typename std::conditional<MAT, IdxPlain<KW, C>, IdxLds<KW, C>>::type;
-    __shared__ KW lds_key_raw[KA::size(C)];
-    __shared__ __align__(16) uint16_t lds_idx_raw[IA::size(C)];
+    using KA = typename std::conditional<MAT, LdsPad<KW, SH::KI, 0>, LdsPad<KW, SH::KI, 1>>::type;
+    using IA = typename std::conditional<MAT, LdsPad<uint16_t, SH::KI, 0>, LdsPad<uint16_t, SH::KI, 2>>::type;
+    // sorted way: keys, indices, digit counters, scan scratch, offset, flag
+    static constexpr int KEYS = KA::size(C) * sizeof(KW), IDX = IA::size(C) * 2, CNT = SH::NW * LSTRIDE * 4;
+    static constexpr int TMP64 = (KEYS + IDX + CNT + 15) / 16 * 16, TMP = TMP64 + SH::NW * 8, BASE = TMP + SH::NW * 4,
+                         FLAG = BASE + 8, SORTED = FLAG + 16;
+    // bins of the table's keys
+    static constexpr int NBB = C == 1024 ? 10 : 12, BINS = 1 << NBB, HIST = (BINS * 2 + 2 + 15) / 16 * 16;
+    // binned way, for tn rows of the table and pn probing ones: the table's row ids
+    // (MAT), bins' ends, its keys in order and PAD largest ones, its keys in bins
+    // (later its runs), its rows in bins (later the probing rows in runs and
+    // RUN_SCAN more words, MAT). Grows with tn where tn + pn is given: halves need most.
+    static constexpr uint32_t PAD = BIN_MAXC + 8;
+    static constexpr uint32_t need(uint32_t tn, uint32_t pn)
+    {
+        const uint32_t k = sizeof(KW), ti = 2 * tn, pi = MAT ? 4 * pn + 4 * RUN_SCAN : 0u;
+        return HIST + (tn + PAD) * k + tn * (k + (MAT ? 4u : 0u)) + (ti > pi ? ti : pi) + 64;
+    }
+    static constexpr int ALL = need(C / 2, C / 2);
+    // 32-bit keys: half of a CU's 160 KiB with the block's other words, so that two blocks fit
+    static constexpr int HALF = 81920 - 512;
+    static constexpr int MOST = sizeof(KW) == 4 && C == LEAF_CAP ? HALF : ALL;
+    static_assert(MOST >= ALL, "any two sides of one block fit");
+    static constexpr int BYTES = ((MOST > SORTED ? MOST : SORTED) + 15) / 16 * 16;
+};
+
+template <typename K> struct JoinIn {
+    const K *rk, *sk;
+    const int32_t *rr, *sr;
+};
+
+// The join of one block by sorting R's and S's rows together (see above), for
+// leaves that the binned way does not take. Not inlined: its registers would
+// weigh on the other way's.
+template <typename K, typename KW, bool MAT, bool SELF, int C>
+static __device__ __noinline__ void join_sorted(__attribute__((address_space(3))) char* pool3, uint32_t rn, uint32_t n,
+                                                uint64_t leaf_base, uint64_t out, int bits, bool reorder, uint32_t li,
+                                                const K* rk_, const K* sk_, const int32_t* rr_, const int32_t* sr_,
+                                                uint64_t* __restrict__ status,
+                                                uint64_t* __restrict__ total, uint32_t* __restrict__ err,
+                                                int32_t* out_r_, int32_t* out_s_,
+                                                uint64_t capacity)
+{
+    using JL = JoinLds<KW, MAT, C>;
+    using KA = typename JL::KA;
+    using IA = typename JL::IA;
+    constexpr int NT = JL::SH::NT, KI = JL::SH::KI;
+    char* const pool = (char*)pool3;
+    // (as arguments of a call they would be taken for any address space's)
+    typedef __attribute__((address_space(1))) K GK;
+    typedef __attribute__((address_space(1))) int32_t G32;
+    const GK *const rk = (const GK*)rk_, *const sk = (const GK*)sk_;
+    const G32 *const rr = (const G32*)rr_, *const sr = (const G32*)sr_;
+    G32 *const out_r = (G32*)out_r_, *const out_s = (G32*)out_s_;
+    KW* const lds_key_raw = (KW*)pool;
+    uint16_t* const lds_idx_raw = (uint16_t*)(pool + JL::KEYS);
     const KA lds_key{lds_key_raw};
     const IA lds_idx{lds_idx_raw};
-    __shared__ uint32_t cnt[NW * LSTRIDE];
-    __shared__ uint32_t tmp[NW];
-    __shared__ uint64_t tmp64[NW];
-    __shared__ uint32_t s_leaf;
-    __shared__ uint64_t s_base;
-    __shared__ uint32_t s_unordered;
-
-    if (threadIdx.x == 0) s_unordered = 0;
-    uint32_t li = blockIdx.x;
-    if (MAT && !SELF) {
-        if (threadIdx.x == 0) s_leaf = atomicAdd(ticket, 1u);
-        lds_barrier();
-        li = s_leaf;
-    }
-    LeafDesc L;
-    if constexpr (SELF) L = self;
-    else L = leaves[li];
-    const uint32_t rn = L.rn, n = L.rn + L.sn;
-    const K* __restrict__ rk = (const K*)bufs.key[L.buf][0] + L.kr0;
-    const K* __restrict__ sk = (const K*)bufs.key[L.buf][1] + L.ks0;
+    uint32_t* const cnt = (uint32_t*)(pool + JL::KEYS + JL::IDX);
+    uint32_t* const tmp = (uint32_t*)(pool + JL::TMP);
+    uint64_t* const tmp64 = (uint64_t*)(pool + JL::TMP64);
+    uint64_t& s_base = *(uint64_t*)(pool + JL::BASE);
+    uint32_t& s_unordered = *(uint32_t*)(pool + JL::FLAG);
     const uint32_t w = threadIdx.x / 64, l = threadIdx.x & 63;
-
+    lds_barrier();
+    if (threadIdx.x == 0) s_unordered = 0;
     KW key[KI];
     uint16_t idx[KI];
-    if constexpr (SELF) {
-        uint64_t lo = ~0ull, hi = 0;
-#pragma unroll
-        for (int r = 0; r < KI; r++) {
-            const uint32_t q = (w * KI + r) * 64 + l;
-            const uint32_t qc = q < n ? q : n - 1;
-            const uint64_t o = ord_of(qc < rn ? rk[qc] : sk[qc - rn]);
-            lo = o < lo ? o : lo;
-            hi = o > hi ? o : hi;
-        }
-        block_minmax64<NT>(lo, hi, tmp64);
-        L.base = lo;
-        L.bits = (uint16_t)(hi > lo ? 64 - (int)__clzll((long long)(hi - lo)) : 0);
-    }
     auto load_items = [&]() {
 #pragma unroll
         for (int r = 0; r < KI; r++) {
@@ -2369,7 +2387,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_leaf_join(const LeafDesc* __restr
                 const uint32_t q = (w * KI + r) * 64 + l;
                 const uint32_t qc = q < n ? q : n - 1;  // every lane loads a real row
                 const K v = qc < rn ? rk[qc] : sk[qc - rn];
-                if (q < n) key[r] = (KW)(ord_of(v) - L.base);
+                if (q < n) key[r] = (KW)(ord_of(v) - leaf_base);
             }
         }
     };
@@ -2378,10 +2396,10 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_leaf_join(const LeafDesc* __restr
     // in-bin ranking to pay.) Ranked by atomics, then checked; sorted again
     // with ballot ranking if the order is not exact.
     load_items();
-    block_lsd_sort<KW, NT, KI, true>(key, idx, (int)L.bits, lds_key, lds_idx, cnt, tmp);
-    if (!block_check_order<KW, NT, KI>(lds_key, lds_idx, n, &s_unordered) || (L.flags & LEAF_FORCE_REORDER)) {
+    block_lsd_sort<KW, NT, KI, true>(key, idx, bits, lds_key, lds_idx, cnt, tmp);
+    if (!block_check_order<KW, NT, KI>(lds_key, lds_idx, n, &s_unordered) || reorder) {
         load_items();
-        block_lsd_sort<KW, NT, KI, false>(key, idx, (int)L.bits, lds_key, lds_idx, cnt, tmp);
+        block_lsd_sort<KW, NT, KI, false>(key, idx, bits, lds_key, lds_idx, cnt, tmp);
     }
 
     // Run analysis on blocked positions p = tid*KI + i. A run is a maximal
@@ -2457,8 +2475,6 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_leaf_join(const LeafDesc* __restr
     // key array, then every item picks its own from LDS.
     int32_t* lds_w = (int32_t*)lds_key_raw;
     {
-        const int32_t* __restrict__ rr = bufs.rid[L.buf][0] + L.r0;
-        const int32_t* __restrict__ sr = bufs.rid[L.buf][1] + L.s0;
 #pragma unroll
         for (int r = 0; r < KI; r++) {
             const uint32_t q = threadIdx.x + r * NT;
@@ -2472,100 +2488,481 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_leaf_join(const LeafDesc* __restr
         if (threadIdx.x == 0) {
             status_store(&status[li + 1], ST_INC | (excl + ltot));
             if (li == gridDim.x - 1) *total = excl + ltot;
-            s_base = excl + L.out;
+            s_base = excl + out;
         }
     }
     lds_barrier();
     const uint64_t base = SELF ? 0 : s_base;
-    // Pair slots: R item j of a run owns E_rs + j*b .. + b (it writes out_r),
-    // S item k of a run appears at E_rs + i*b + k for its run's a R items (it
-    // writes out_s). Per item: first slot, and packed [side:1][slots:14][stride:14].
-    uint32_t firstv[KI], packv[KI];
-    uint32_t maxslots = 0;
-    {
-        uint32_t e = ex;
-#pragma unroll
-        for (int i = 0; i < KI; i++) {
-            const uint32_t ab = abv[i];
-            const bool isr = (ab >> 31) != 0;
-            const uint32_t a = (ab >> 14) & 0x3fffu, b = ab & 0x3fffu;
-            const uint32_t slots = isr ? b : (b ? a : 0u);
-            const uint32_t stride = isr ? 1u : b;
-            packv[i] = (isr ? 0x80000000u : 0u) | (slots << 14) | stride;
-            firstv[i] = isr ? e : e - a * b + kv[i];
-            maxslots = slots > maxslots ? slots : maxslots;
-            if (isr) e += b;
-        }
-    }
-    maxslots = block_max<NT>(maxslots, tmp);
+    // Pairs are written R item by R item: its b slots are consecutive, and so are
+    // their S items (kv: minus the R item's distance to its run's S part). A wave
+    // writes an item of many slots together, a lane one of few. Both columns leave
+    // in stretches: 2^21 x 2^21 rows of 21000 keys, 32-bit, 209 million pairs in
+    // 1.2 ms, from 3.6 with S items writing their slots b apart.
     int32_t rid[KI];
 #pragma unroll
     for (int i = 0; i < KI; i++) rid[i] = p0 + i < n ? lds_w[id[i]] : 0;
-    lds_barrier();  // the key array becomes the pair staging buffer
-    constexpr uint32_t SC = C * sizeof(KW) / 4;  // int32 slots of the key array
-    if (ltot <= 4 * SC && maxslots <= 64) {
-        // Staged, one output column at a time: that column's items scatter
-        // their slots of the chunk into LDS, then the chunk leaves as one
-        // coalesced run. An R item's slots are consecutive, so it visits only
-        // those inside the chunk.
-        int32_t* st = lds_w;
-        for (int side = 0; side < 2; side++) {
-            int32_t* __restrict__ dst = side ? out_s : out_r;
-            for (uint32_t c0 = 0; c0 < ltot; c0 += SC) {
-                const uint32_t c1 = c0 + SC;
+    lds_barrier();
+    int32_t* const sid = lds_w;  // row ids by sorted position
 #pragma unroll
-                for (int i = 0; i < KI; i++) {
-                    const uint32_t pk = packv[i];
-                    const uint32_t sl = (pk >> 14) & 0x3fffu, stride = pk & 0x3fffu;
-                    const uint32_t f = firstv[i];
-                    if (side == 0 && (pk >> 31)) {
-                        const uint32_t j0 = f < c0 ? c0 - f : 0u;
-                        const uint32_t j1 = f + sl < c1 ? sl : (c1 > f ? c1 - f : 0u);
-                        for (uint32_t j = j0; j < j1; j++) st[f + j - c0] = rid[i];
-                    } else if (side == 1 && !(pk >> 31)) {
-                        for (uint32_t j = 0; j < sl; j++) {
-                            const uint32_t t = f + j * stride;
-                            if (t >= c0 && t < c1) st[t - c0] = rid[i];
-                        }
-                    }
-                }
-                lds_barrier();
-                const uint32_t cn = ltot - c0 < SC ? ltot - c0 : SC;
-                for (uint32_t t = threadIdx.x; t < cn; t += NT) {
-                    const uint64_t o = base + c0 + t;
-                    if (o < capacity) dst[o] = st[t];
-                }
-                lds_barrier();
-            }
-        }
-        return;
-    }
-    // Very large outputs (hot keys inside the block): items write their own
-    // slots; items with many slots are written by their wave.
+    for (int i = 0; i < KI; i++)
+        if (p0 + i < n) sid[p0 + i] = rid[i];
+    lds_barrier();
 #pragma unroll
     for (int i = 0; i < KI; i++) {
-        const uint32_t pk = packv[i];
-        const uint32_t slots = (pk >> 14) & 0x3fffu, stride = pk & 0x3fffu, first = firstv[i];
-        int32_t* __restrict__ dst = (pk >> 31) ? out_r : out_s;
-        if (slots && slots <= COOP_PAIRS) {
-            for (uint32_t j = 0; j < slots; j++) {
-                const uint64_t t = base + first + (uint64_t)j * stride;
-                if (t < capacity) dst[t] = rid[i];
+        const uint32_t b = (abv[i] >> 31) ? abv[i] & 0x3fffu : 0u;
+        const uint32_t s0 = p0 + i - kv[i], e = ex;
+        ex += b;
+        if (b <= COOP_PAIRS) {
+#pragma unroll 1
+            for (uint32_t j = 0; j < b; j++) {
+                const uint64_t o = base + e + j;
+                if (o < capacity) {
+                    out_r[o] = sid[p0 + i];
+                    out_s[o] = sid[s0 + j];
+                }
             }
         }
-        uint64_t m = ballot(slots > COOP_PAIRS);
+        uint64_t m = ballot(b > COOP_PAIRS);
         while (m) {
             const int src = __ffsll((unsigned long long)m) - 1;
             m &= m - 1;
-            const uint32_t cpk = __shfl(pk, src, 64);
-            const uint32_t cs = (cpk >> 14) & 0x3fffu, cst = cpk & 0x3fffu;
-            const uint32_t cf = __shfl(first, src, 64);
-            const int32_t cr = __shfl(rid[i], src, 64);
-            int32_t* __restrict__ cdst = (cpk >> 31) ? out_r : out_s;
-            for (uint32_t j = l; j < cs; j += 64) {
-                const uint64_t t = base + cf + (uint64_t)j * cst;
-                if (t < capacity) cdst[t] = cr;
+            const uint32_t cb = (uint32_t)__builtin_amdgcn_readlane((int)b, src);
+            const uint32_t cs = (uint32_t)__builtin_amdgcn_readlane((int)s0, src);
+            const uint64_t ce = base + (uint32_t)__builtin_amdgcn_readlane((int)e, src);
+            const int32_t cr = sid[(uint32_t)__builtin_amdgcn_readlane((int)(p0 + i), src)];
+#pragma unroll 1
+            for (uint32_t j = l; j < cb; j += 64) {
+                if (ce + j < capacity) {
+                    out_r[ce + j] = cr;
+                    out_s[ce + j] = sid[cs + j];
+                }
             }
+        }
+    }
+}
+
+// The join of one block. The side of fewer rows is the table: its keys are
+// binned by their top bits (a quarter to one row a bin where keys are even),
+// placed, and ranked exactly inside their bin, so that it is in (key, position)
+// order; every row of the other side, which probes, then finds its table rows by
+// looking through one bin. Probing rows of one key (a run of the table) are
+// collected run by run and ranked by position within the run, so nothing depends
+// on the order of atomics. Pairs: R item i of a run and S item k have slot
+// E + i * b + k, with E the pairs before the run and b its S items; the probing
+// rows write both columns into LDS, from where they leave coalesced.
+// What bounds the block is its LDS work and its waits, not memory. Only the
+// table's rows are sorted, which are the fewer, where sorting both sides together
+// took three to five digit passes over all rows and a check of the order; and with
+// 32-bit keys two blocks of 64 VGPRs and half of the LDS share a CU, so that one
+// works while the other waits. 2^27 x 2^29 rows, 32-bit keys: 4.2 ms (2.1 TB/s)
+// from 9.0; counting 2^28 of Zipf keys: 0.92 ms from 3.9. With the plain sides'
+// roles (R always the table) blocks of many R rows fell to the sorted way: 2^24 x
+// 2^18 rows, 1.59 ms for the whole join and now 0.82.
+// Blocks whose table rows crowd one bin (over BIN_MAXC of them, so both sides
+// have many rows a key there) are sorted (join_sorted).
+// SELF (a whole input that fits one block): the leaf is `self`, whose key
+// range the block finds itself; its pairs start at 0 and their number is
+// stored to *total (in either mode). One launch then serves the whole call.
+template <typename K, typename KW, bool MAT, bool SELF = false, int C = LEAF_CAP>
+__global__ __launch_bounds__((JoinLds<KW, MAT, C>::SH::NT))
+__attribute__((amdgpu_waves_per_eu(sizeof(KW) == 4 && !SELF ? 8 : 4))) void k_leaf_join(const LeafDesc* __restrict__ leaves,
+                                                            BufSet bufs, uint64_t* __restrict__ status,
+                                                            uint32_t* __restrict__ ticket,
+                                                            uint64_t* __restrict__ total,
+                                                            uint32_t* __restrict__ err,
+                                                            int32_t* __restrict__ out_r,
+                                                            int32_t* __restrict__ out_s,
+                                                            uint64_t capacity, LeafDesc self)
+{
+    using JL = JoinLds<KW, MAT, C>;
+    constexpr int NT = JL::SH::NT, KI = JL::SH::KI, NW = JL::SH::NW;
+    __shared__ __align__(16) char pool[JL::BYTES];
+    __shared__ uint32_t tmp[NW];
+    __shared__ uint64_t tmp64[NW];
+    __shared__ uint32_t s_leaf, s_all;
+    __shared__ uint32_t s_spare[64];  // a counter per lane for rows that take no part
+    __shared__ uint64_t s_base;
+
+    uint32_t li = blockIdx.x;
+    if (MAT && !SELF) {
+        if (threadIdx.x == 0) s_leaf = atomicAdd(ticket, 1u);
+        lds_barrier();
+        li = s_leaf;
+    }
+    LeafDesc L;
+    if constexpr (SELF) L = self;
+    else L = leaves[li];
+    JoinIn<K> in;
+    in.rk = (const K*)bufs.key[L.buf][0] + L.kr0;
+    in.sk = (const K*)bufs.key[L.buf][1] + L.ks0;
+    in.rr = MAT ? bufs.rid[L.buf][0] + L.r0 : nullptr;
+    in.sr = MAT ? bufs.rid[L.buf][1] + L.s0 : nullptr;
+    // the table: the side of fewer rows (R, if alike)
+    const bool swap = L.rn > L.sn;
+    const uint32_t tn = swap ? L.sn : L.rn, pn = swap ? L.rn : L.sn;
+    // (every load below is made without a branch, so that all are in flight at
+    // once; an empty side reads the other's first row, an empty leaf its record)
+    const K* const pk = !pn ? (const K*)leaves : swap ? in.rk : in.sk;
+    const K* const tk = !tn ? pk : swap ? in.sk : in.rk;
+    const int32_t* const pr = !pn ? (const int32_t*)leaves : swap ? in.rr : in.sr;
+    const int32_t* const tr = !tn ? pr : swap ? in.sr : in.rr;
+    const uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)threadIdx.x / 64) * (KI * 64);
+    uint32_t l = threadIdx.x & 63, t = threadIdx.x;
+    // row r of the thread, formed anew in each step (kept over the steps, the
+    // rows' numbers and what is compared with them take registers twice over)
+    auto row = [&](int r) { return w0 + r * 64 + l; };
+    auto fresh = [&]() { asm volatile("" : "+v"(l), "+v"(t)); };
+    // packed words stay packed (their parts would be kept beside them: 64 VGPRs
+    // are all that two blocks a CU leave, and spills made the block 1.7 times slower)
+    auto packed = [](uint32_t(&w)[KI]) {
+#pragma unroll
+        for (int r = 0; r < KI; r++) asm volatile("" : "+v"(w[r]));
+    };
+
+    // The probing rows stay in registers (row r of the thread: row(r)); the
+    // table's are loaded with them (row t + i * NT).
+    constexpr int TI = C / 2 / NT;
+    const uint32_t tlast = tn ? tn - 1 : 0u, plast = pn ? pn - 1 : 0u;
+    K tv[TI];
+#pragma unroll
+    for (int i = 0; i < TI; i++) tv[i] = ld_now(tk, min(t + i * NT, tlast));
+    KW key[KI];
+    {
+        K v[KI];
+#pragma unroll
+        for (int r = 0; r < KI; r++) v[r] = ld_now(pk, min(row(r), plast));
+        if constexpr (SELF) {
+            uint64_t lo = ~0ull, hi = 0;
+#pragma unroll
+            for (int r = 0; r < KI; r++) {
+                const uint64_t o = ord_of(v[r]);
+                lo = o < lo ? o : lo;
+                hi = o > hi ? o : hi;
+            }
+#pragma unroll
+            for (int i = 0; i < TI; i++) {
+                const uint64_t o = ord_of(tv[i]);
+                lo = o < lo ? o : lo;
+                hi = o > hi ? o : hi;
+            }
+            block_minmax64<NT>(lo, hi, tmp64);
+            L.base = lo;
+            L.bits = (uint16_t)(hi > lo ? 64 - (int)__clzll((long long)(hi - lo)) : 0);
+        }
+#pragma unroll
+        for (int r = 0; r < KI; r++) key[r] = (KW)(ord_of(v[r]) - L.base);
+    }
+    const uint32_t tn4 = (tn + 3) & ~3u;
+    int32_t* const trid = (int32_t*)pool;                            // the table's places by row, then its row ids in key order
+    uint16_t* const bend = (uint16_t*)(pool + (MAT ? tn4 * 4 : 0));  // end of each bin in the table's order
+    KW* const tkey = (KW*)((char*)bend + JL::HIST);                  // the table's keys in order
+    KW* const bkey = tkey + tn4 + JL::PAD;                           // its keys in their bins, in any order
+    uint16_t* const bidx = (uint16_t*)(bkey + tn4);                  // their rows
+    const int sh = (int)L.bits > JL::NBB ? (int)L.bits - JL::NBB : 0;
+    auto bin_of = [&](KW k) { return (uint32_t)(k >> sh) & (JL::BINS - 1u); };
+    auto bin_add = [&](uint32_t b) { return atomicAdd((uint32_t*)bend + b / 2, 1u << (b & 1) * 16) >> (b & 1) * 16 & 0xffffu; };
+
+    bool fast = !(L.flags & LEAF_FORCE_REORDER);
+    if (fast) {
+        for (uint32_t i = t; i < JL::BINS / 2; i += NT) ((uint32_t*)bend)[i] = 0;
+        lds_barrier();
+#pragma unroll
+        for (int i = 0; i < TI; i++) {
+            if (i * NT >= (int)tn) break;
+            const uint32_t q = t + i * NT;
+            const KW k = (KW)(ord_of(tv[i]) - L.base);
+            if (q < tn) {
+                tkey[q] = k;  // (in row order so far)
+                bin_add(bin_of(k));
+            }
+        }
+        lds_barrier();
+        constexpr int BPT = JL::BINS / NT;
+        uint32_t c[BPT], sum = 0, mx = 0;
+#pragma unroll
+        for (int i = 0; i < BPT; i += 2) {
+            const uint32_t x = ((const uint32_t*)bend)[(t * BPT + i) / 2];
+            c[i] = x & 0xffffu;
+            c[i + 1] = x >> 16;
+        }
+#pragma unroll
+        for (int i = 0; i < BPT; i++) {
+            sum += c[i];
+            mx = c[i] > mx ? c[i] : mx;
+        }
+        fast = block_max<NT>(mx, tmp) <= BIN_MAXC;
+        if (fast) {
+            uint32_t all;
+            uint32_t ex = block_excl_scan<NT>(sum, tmp, &all);
+#pragma unroll
+            for (int i = 0; i < BPT; i += 2) {
+                ((uint32_t*)bend)[(t * BPT + i) / 2] = ex | (ex + c[i]) << 16;
+                ex += c[i] + c[i + 1];
+            }
+        }
+    }
+    if (!fast) {
+        join_sorted<K, KW, MAT, SELF, C>((__attribute__((address_space(3))) char*)pool, L.rn, L.rn + L.sn, L.base, L.out,
+                                         (int)L.bits, L.flags & LEAF_FORCE_REORDER, li, in.rk, in.sk, in.rr, in.sr,
+                                         status, total, err, out_r, out_s, capacity);
+        return;
+    }
+    lds_barrier();
+    for (uint32_t q = t; q < tn; q += NT) {
+        const KW k = tkey[q];
+        const uint32_t p = bin_add(bin_of(k));  // bend[b] moves from the bin's start to its end
+        bkey[p] = k;
+        bidx[p] = (uint16_t)q;
+    }
+    lds_barrier();
+    auto bin_start = [&](uint32_t b) { return b ? (uint32_t)bend[b - 1] : 0u; };
+    for (uint32_t p = t; p < tn; p += NT) {
+        const KW k = bkey[p];
+        const uint32_t q = bidx[p], b = bin_of(k), s0 = bin_start(b), e0 = bend[b];
+        uint32_t at = s0;
+        for (uint32_t j = s0; j < e0; j++) {
+            const KW kj = bkey[j];
+            at += kj < k || (kj == k && bidx[j] < q) ? 1u : 0u;
+        }
+        tkey[at] = k;
+        if constexpr (MAT) trid[q] = (int32_t)at;
+    }
+    if (t < JL::PAD) tkey[tn + t] = (KW)~(KW)0;
+    lds_barrier();
+    // the table's row ids, on their way during the search
+    int32_t tid[MAT ? TI : 1] = {};
+    uint32_t tat[MAT ? TI : 1] = {};
+    if constexpr (MAT) {
+#pragma unroll
+        for (int i = 0; i < TI; i++) {
+            tat[i] = (uint32_t)trid[min(t + i * NT, tlast)];
+            tid[i] = ld_now(tr, min(t + i * NT, tlast));
+        }
+    }
+    // Every probing row looks through the table's keys from its bin's start on,
+    // all rows of the thread in step: keys smaller than its own are counted (they
+    // end where the bin does at the latest), and equal ones.
+    fresh();
+    uint32_t info[KI], seen[KI], cbmax = 0;
+#pragma unroll
+    for (int r = 0; r < KI; r++) {
+        const uint32_t b = bin_of(key[r]), s0 = bin_start(b), cb = bend[b] - s0;
+        info[r] = s0;
+        seen[r] = 0;  // smaller | same << 8
+        cbmax = cb > cbmax ? cb : cbmax;
+    }
+#pragma unroll 1
+    for (uint32_t j = 0; j < cbmax; j += 2) {
+#pragma unroll
+        for (int r = 0; r < KI; r++) {
+            const KW* const at = tkey + info[r] + j;
+            const KW k0 = at[0], k1 = at[1];
+            seen[r] += (k0 < key[r] ? 1u : 0u) + (k1 < key[r] ? 1u : 0u);
+            seen[r] += (k0 == key[r] ? 0x100u : 0u) + (k1 == key[r] ? 0x100u : 0u);
+        }
+    }
+    if ((int)L.bits == (int)sizeof(KW) * 8) {
+        // the largest key of all also met the padding
+        const uint32_t it = (cbmax + 1) / 2 * 2;
+#pragma unroll
+        for (int r = 0; r < KI; r++)
+            if (key[r] == (KW)~(KW)0 && info[r] + it > tn) seen[r] -= (info[r] + it - tn) << 8;
+    }
+    fresh();
+#pragma unroll
+    for (int r = 0; r < KI; r++)  // first table position of the row's run, table rows there (0: no match)
+        info[r] = (info[r] + (seen[r] & 0xffu)) | (row(r) < pn ? seen[r] >> 8 << 13 : 0u);
+    packed(info);
+    if constexpr (!MAT) {
+        uint32_t local = 0;
+#pragma unroll
+        for (int r = 0; r < KI; r++) local += info[r] >> 13;
+        const uint64_t c = block_sum64<NT>((uint64_t)local, tmp64);
+        if (SELF && t == 0) *total = c;
+        if (!SELF && t == 0 && c) atomicAdd((unsigned long long*)total, (unsigned long long)c);
+        return;
+    } else {
+        // run[p]: probing rows found so far | table rows << 16 at a run's first position, 0 at its others
+        uint32_t* const run = (uint32_t*)bkey;
+        uint32_t* const prow = (uint32_t*)(bkey + tn4);  // run << 13 | probing row, by run
+        for (uint32_t p = t; p < tn; p += NT) {
+            const KW k = tkey[p];
+            uint32_t a = 0;
+            if (p == 0 || tkey[p - 1] != k)
+                do a++; while (p + a < tn && tkey[p + a] == k);
+            run[p] = a << 16;
+        }
+        lds_barrier();
+#pragma unroll
+        for (int i = 0; i < TI; i++)
+            if (i * NT < (int)tn && t + i * NT < tn) trid[tat[i]] = tid[i];
+        fresh();
+        uint32_t at[KI];
+#pragma unroll
+        for (int r = 0; r < KI; r++)
+            at[r] = atomicAdd(info[r] >> 13 ? &run[info[r] & 0x1fffu] : &s_spare[l], 1u) & 0xffffu;
+        packed(info);
+        lds_barrier();
+        // exclusive prefix over table positions of pairs << 13 | probing rows (at
+        // most 48 * 8191 pairs: 19 bits)
+        uint32_t ltot, maxb = 0;
+        {
+            const uint32_t ppt = (tn + NT - 1) / NT, p0 = t * ppt;
+            uint32_t sum = 0;
+            for (uint32_t i = 0; i < ppt; i++) {
+                const uint32_t x = p0 + i < tn ? run[p0 + i] : 0u, b = x & 0xffffu;
+                sum += ((x >> 16) * b << 13) + b;
+                maxb = b > maxb ? b : maxb;
+            }
+            uint32_t all;
+            uint32_t ex = block_excl_scan<NT>(sum, tmp, &all);
+            for (uint32_t i = 0; i < ppt && p0 + i < tn; i++) {
+                const uint32_t x = run[p0 + i], b = x & 0xffffu;
+                run[p0 + i] = ex;
+                ex += ((x >> 16) * b << 13) + b;
+            }
+            ltot = all >> 13;
+            maxb = block_max<NT>(maxb, tmp);
+            // (the word after the last position: read for the last run's size)
+            if (t == 0) s_all = all;
+            // a row looks past its run's end: the words after the last run's
+            if (t < RUN_SCAN) prow[(all & 0x1fffu) + t] = ~0u;
+        }
+        if (SELF && t == 0) *total = ltot;
+        if (!SELF && t == 0) status_store(&status[li + 1], ST_AGG | (uint64_t)ltot);
+        lds_barrier();
+        // the run's probing rows together, in any order
+        fresh();
+        uint32_t bmax = 0;
+#pragma unroll
+        for (int r = 0; r < KI; r++) {
+            const uint32_t rs = info[r] & 0x1fffu;
+            const bool m = info[r] >> 13;
+            const uint32_t x = run[m ? rs : 0u], y = *(m && rs + 1 < tn ? &run[rs + 1] : &s_all);
+            const uint32_t g = x & 0x1fffu, b = m ? (y & 0x1fffu) - g : 0u;
+            if (m) prow[g + at[r]] = rs << 13 | row(r);
+            at[r] = g | b << 13;  // the run's first place, its probing rows
+            bmax = b <= RUN_SCAN && b > bmax ? b : bmax;
+        }
+        packed(info);
+        packed(at);
+        lds_barrier();
+        int32_t rid[KI];
+#pragma unroll
+        for (int r = 0; r < KI; r++) rid[r] = ld_now(pr, min(row(r), plast));
+        // (the row ids are loaded during the ranking; wave 0 waits for the look-back's answer while the others rank)
+        if (!SELF && t < 64) {
+            const uint64_t excl = look_back(status, li + 1, err);
+            if (t == 0) {
+                status_store(&status[li + 1], ST_INC | (excl + ltot));
+                if (li == gridDim.x - 1) *total = excl + ltot;
+                s_base = excl + L.out;
+            }
+        }
+        // a row's place in its run: the run's rows before its own (words of later
+        // runs are larger)
+        uint32_t rank[KI];
+#pragma unroll
+        for (int r = 0; r < KI; r++) rank[r] = 0;
+#pragma unroll 1
+        for (uint32_t j = 0; j < bmax; j += 2) {
+            fresh();
+#pragma unroll
+            for (int r = 0; r < KI; r++) {
+                const uint32_t* const x = prow + (at[r] & 0x1fffu) + j;
+                const uint32_t mine = (info[r] & 0x1fffu) << 13 | row(r);
+                rank[r] += (x[0] < mine ? 1u : 0u) + (x[1] < mine ? 1u : 0u);
+            }
+        }
+        if (maxb > RUN_SCAN) {
+            // Runs of more rows: a counter per run and wave, numbered by the run's
+            // first place (runs of over RUN_SCAN rows start in different stretches
+            // of RUN_SCAN places); a row comes after its run's rows of earlier waves,
+            // of the wave's earlier rows and of earlier lanes.
+            constexpr uint32_t NRUN = C / RUN_SCAN;
+            constexpr int RBITS = 31 - __builtin_clz(NRUN);
+            static_assert(NRUN == 1u << RBITS && NRUN * NW * 2 <= JL::HIST, "the counters fit the bins' place");
+            static_assert(NRUN <= NT, "a run a thread");
+            uint16_t* const cnt = bend;
+            const uint32_t w = w0 / (KI * 64);
+            for (uint32_t i = t; i < NRUN * NW / 2; i += NT) ((uint32_t*)cnt)[i] = 0;
+            lds_barrier();
+            fresh();
+#pragma unroll
+            for (int r = 0; r < KI; r++) {
+                const bool big = at[r] >> 13 > RUN_SCAN;
+                const uint32_t id = (at[r] & 0x1fffu) / RUN_SCAN;
+                uint64_t same = ballot(big);
+#pragma unroll
+                for (int i = 0; i < RBITS; i++) {
+                    const uint64_t on = ballot(id >> i & 1u);
+                    same &= (id >> i & 1u) ? on : ~on;
+                }
+                if (big) {
+                    const uint32_t c = cnt[id * NW + w];
+                    rank[r] = c + (uint32_t)__popcll(same & ((1ull << l) - 1));
+                    if ((same & ((1ull << l) - 1)) == 0) cnt[id * NW + w] = (uint16_t)(c + (uint32_t)__popcll(same));
+                }
+            }
+            lds_barrier();
+            if (t < NRUN) {
+                uint32_t sum = 0;
+#pragma unroll 1
+                for (int i = 0; i < NW; i++) {
+                    const uint32_t c = cnt[t * NW + i];
+                    cnt[t * NW + i] = (uint16_t)sum;
+                    sum += c;
+                }
+            }
+            lds_barrier();
+#pragma unroll
+            for (int r = 0; r < KI; r++)
+                if (at[r] >> 13 > RUN_SCAN) rank[r] += cnt[(at[r] & 0x1fffu) / RUN_SCAN * NW + w];
+        }
+        fresh();
+#pragma unroll
+        for (int r = 0; r < KI; r++)  // first slot, stride
+            at[r] = ((run[info[r] >> 13 ? info[r] & 0x1fffu : 0u] >> 13) + rank[r] * (swap ? info[r] >> 13 : 1u)) |
+                    (swap ? 1u : at[r] >> 13) << 19;
+        lds_barrier();
+        const uint64_t base = SELF ? 0 : s_base;
+        // all but the table's row ids is free: a stretch of both output columns at a time
+        const uint32_t slots = (JL::BYTES - tn4 * 4) / 8;
+        int32_t* const col_t = (int32_t*)(pool + tn4 * 4);
+        int32_t* const col_p = col_t + slots;
+        int32_t* const out_t = swap ? out_s : out_r;
+        int32_t* const out_p = swap ? out_r : out_s;
+        for (uint32_t c0 = 0; c0 < ltot; c0 += slots) {
+            const uint32_t cn = ltot - c0 < slots ? ltot - c0 : slots;
+#pragma unroll
+            for (int r = 0; r < KI; r++) {
+                asm volatile("" : "+v"(info[r]), "+v"(at[r]));  // (unpacked here, not kept unpacked over the loop)
+                const uint32_t a = info[r] >> 13, rs = info[r] & 0x1fffu, b = at[r] >> 19;
+                uint32_t x = (at[r] & 0x7ffffu) - c0;
+                if (a && x < cn) {
+                    col_t[x] = trid[rs];
+                    col_p[x] = rid[r];
+                }
+                if (ballot(a > 1)) {
+#pragma unroll 1
+                    for (uint32_t i = 1; i < a; i++) {
+                        x += b;
+                        if (x < cn) {
+                            col_t[x] = trid[rs + i];
+                            col_p[x] = rid[r];
+                        }
+                    }
+                }
+            }
+            lds_barrier();
+            for (uint32_t x = t; x < cn; x += NT) {
+                const uint64_t o = base + c0 + x;
+                if (o < capacity) {
+                    out_t[o] = col_t[x];
+                    out_p[o] = col_p[x];
+                }
+            }
+            lds_barrier();
         }
     }
 }
@@ -2576,7 +2973,7 @@ hipError_t launch_leaf_join(int key_bytes, bool wide, bool materialize, const Le
                             uint64_t capacity, hipStream_t st)
 {
     if (n == 0) return hipSuccess;
-    const dim3 grid(n), block(wide ? LeafShape<uint64_t>::NT : LeafShape<uint32_t>::NT);
+    const dim3 grid(n), block(LeafShape<uint32_t, LEAF_CAP, true>::NT);
 #define TJ_LJ(K, KW, M)                                                                              \
     hipLaunchKernelGGL((k_leaf_join<K, KW, M>), grid, block, 0, st, leaves, bufs, status, ticket,    \
                        total, err, out_r, out_s, capacity, LeafDesc{})
@@ -2603,7 +3000,7 @@ hipError_t launch_small_join(int key_bytes, bool materialize, uint32_t rn, uint3
     self.flags = flags;
 #define TJ_SJ(K, M, C)                                                                                              \
     hipLaunchKernelGGL((k_leaf_join<K, typename std::make_unsigned<K>::type, M, true, C>), dim3(1),                 \
-                       dim3(LeafShape<typename std::make_unsigned<K>::type, C>::NT), 0, st, nullptr, bufs, nullptr, \
+                       dim3(LeafShape<typename std::make_unsigned<K>::type, C, true>::NT), 0, st, nullptr, bufs, nullptr, \
                        nullptr, total, nullptr, out_r, out_s, capacity, self)
 #define TJ_SJC(K, M)                     \
     do {                                 \
