@@ -105,6 +105,7 @@ struct LeafDesc {
 // ranking (exercises the path taken when the atomic-ranked order fails its
 // check; set by the self-test hook only).
 constexpr uint16_t LEAF_FORCE_REORDER = 1u;
+constexpr uint16_t LEAF_CROWDED = 2u;  // set by the sort block that leaves its leaf to the digit passes
 
 // A bucket whose rows all hold one key: join output is the full cross product.
 // Its first pair goes to out + (pair prefix of the per-bucket joins before it).
@@ -304,7 +305,7 @@ hipError_t launch_learned_scatter(int key_bytes, bool rids, const ChunkDesc* chu
 hipError_t launch_batch_leaves(const GroupDesc* groups, const ChildRec* crec, const BatchArgs& a,
                                uint32_t* seg_count, LeafDesc* leaves, uint64_t* summary, int pass,
                                hipStream_t st);
-hipError_t launch_leaf_sort(int key_bytes, bool wide, const LeafDesc* leaves, uint32_t n,
+hipError_t launch_leaf_sort(int key_bytes, bool wide, LeafDesc* leaves, uint32_t n,
                             BufSet bufs, void* out_k, int32_t* out_r, hipStream_t st);
 // Count mode adds the leaves' pair counts to *total. Materialise mode needs
 // status[0] = inclusive-flagged carry-in offset, status[1..n] = 0, *ticket = 0;

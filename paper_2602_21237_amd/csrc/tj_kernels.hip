@@ -86,6 +86,21 @@ __device__ __forceinline__ T ld_now(const T* __restrict__ p, uint32_t i)
                              __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
+// A value that is the same in all lanes, for scalar registers (arguments of a
+// call that is not inlined arrive in vector registers).
+template <typename T>
+__device__ __forceinline__ T uniform(T x)
+{
+    if constexpr (sizeof(T) == 8) {
+        const uint64_t v = (uint64_t)x;
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+        return (T)((uint64_t)hi << 32 | lo);
+    } else {
+        return (T)__builtin_amdgcn_readfirstlane((int)x);
+    }
+}
+
 // Inclusive prefix sum across the 64 lanes with DPP: shifts of 1, 2, 4, 8
 // inside each row of 16 lanes, then row_bcast:15 carries row totals into rows
 // 1 and 3 and row_bcast:31 carries the first half's total into rows 2 and 3.
@@ -1900,7 +1915,8 @@ __device__ __forceinline__ bool block_bin_sort(const KW (&key)[KI], int bits, ui
 // ATOMIC ranks with one LDS atomic per item (in lane order on this hardware,
 // which makes every pass stable); the caller must then check that the result
 // is ordered by (key, idx) and sort again with ATOMIC = false if it is not.
-template <typename KW, int NT, int KI, bool ATOMIC = false, typename KA, typename IA>
+// SHARED: cnt and tmp lie inside lds_key / lds_idx (two more barriers a pass).
+template <typename KW, int NT, int KI, bool ATOMIC = false, bool SHARED = false, typename KA, typename IA>
 __device__ __forceinline__ void block_lsd_sort(KW (&key)[KI], uint16_t (&idx)[KI], int bits,
                                                KA lds_key, IA lds_idx, uint32_t* cnt,
                                                uint32_t* tmp, int lo_bit = 0)
@@ -1937,9 +1953,13 @@ __device__ __forceinline__ void block_lsd_sort(KW (&key)[KI], uint16_t (&idx)[KI
         scan_counts<NT, NW, LBINS>(cnt, tmp);
 #pragma unroll
         for (int r = 0; r < KI; r++) {
-            const uint32_t pos = cnt[w * LSTRIDE + dig[r]] + rk[r];
-            lds_key[pos] = key[r];
-            lds_idx[pos] = idx[r];
+            rk[r] += cnt[w * LSTRIDE + dig[r]];
+        }
+        if (SHARED) lds_barrier();
+#pragma unroll
+        for (int r = 0; r < KI; r++) {
+            lds_key[rk[r]] = key[r];
+            lds_idx[rk[r]] = idx[r];
         }
         lds_barrier();
         // (reloaded after the last pass too: a conditional reload would make
@@ -1950,6 +1970,7 @@ __device__ __forceinline__ void block_lsd_sort(KW (&key)[KI], uint16_t (&idx)[KI
             key[r] = lds_key[q];
             idx[r] = lds_idx[q];
         }
+        if (SHARED) lds_barrier();
     }
 }
 
@@ -1982,6 +2003,55 @@ __device__ __forceinline__ bool block_check_order(KA lds_key, IA lds_idx, uint32
     return ok;
 }
 
+// The thread's share of the places whose key's bits from H on are those of the
+// place before (ties), and << 32 of all places out of (key, index) order. Rows of
+// one key are ties, but in order: input with many rows a key is done without its
+// lower bits.
+template <int NT, int KI, typename KA, typename IA>
+__device__ __forceinline__ uint64_t count_ties(KA lds_key, IA lds_idx, uint32_t n, int H)
+{
+    uint64_t ties = 0;
+#pragma unroll
+    for (int r = 0; r < KI; r++) {
+        const uint32_t q = threadIdx.x + r * NT;
+        if (q > 0 && q < n) {
+            const auto k0 = lds_key[q - 1], k1 = lds_key[q];
+            const bool out = k0 > k1 || (k0 == k1 && lds_idx[q - 1] > lds_idx[q]);
+            ties += ((k0 >> H) == (k1 >> H) ? 1u : 0u) + (out ? 1ull << 32 : 0ull);
+        }
+    }
+    return ties;
+}
+
+// Puts runs of ties in (key, index) order, one thread a run (insertion sort).
+// Ends with a barrier.
+template <typename KW, int NT, int KI, typename KA, typename IA>
+__device__ __forceinline__ void sort_ties(KA lds_key, IA lds_idx, uint32_t n, int H)
+{
+#pragma unroll 1
+    for (int r = 0; r < KI; r++) {
+        const uint32_t q = threadIdx.x + r * NT;
+        const bool head = q + 1 < n && (lds_key[q] >> H) == (lds_key[q + 1] >> H) &&
+                          (q == 0 || (lds_key[q] >> H) != (lds_key[q - 1] >> H));
+        if (!head) continue;
+        uint32_t e = q + 1;
+        while (e < n && (lds_key[e] >> H) == (lds_key[q] >> H)) e++;
+        for (uint32_t i = q + 1; i < e; i++) {
+            const KW kv = lds_key[i];
+            const uint16_t iv = lds_idx[i];
+            uint32_t j = i;
+            while (j > q && (lds_key[j - 1] > kv || (lds_key[j - 1] == kv && lds_idx[j - 1] > iv))) {
+                lds_key[j] = lds_key[j - 1];
+                lds_idx[j] = lds_idx[j - 1];
+                j--;
+            }
+            lds_key[j] = kv;
+            lds_idx[j] = iv;
+        }
+    }
+    lds_barrier();
+}
+
 // Stable sort of a leaf block's items (see block_bin_sort for their layout) into
 // lds_key / lds_idx: one counting pass, or digit passes when a bin is too full.
 // reload() gives the items their keys and indices again.
@@ -2000,36 +2070,10 @@ __device__ __forceinline__ void block_sort(KW (&key)[KI], uint16_t (&idx)[KI], i
         // input order); many ties fall back to the full sort.
         const int H = bits - 32;
         block_lsd_sort<KW, NT, KI>(key, idx, 32, lds_key, lds_idx, cnt, tmp, H);
-        uint32_t ties = 0;
-#pragma unroll
-        for (int r = 0; r < KI; r++) {
-            const uint32_t q = threadIdx.x * KI + r;
-            if (q > 0 && q < n && (lds_key[q] >> H) == (lds_key[q - 1] >> H)) ties++;
-        }
-        ties = (uint32_t)block_sum64<NT>((uint64_t)ties, tmp64);
+        const uint64_t c = block_sum64<NT>(count_ties<NT, KI>(lds_key, lds_idx, n, H), tmp64);
+        const uint32_t ties = c >> 32 ? (uint32_t)c : 0u;
         if (ties > 0 && ties <= 256) {
-#pragma unroll
-            for (int r = 0; r < KI; r++) {
-                const uint32_t q = threadIdx.x * KI + r;
-                const bool head = q + 1 < n && (lds_key[q] >> H) == (lds_key[q + 1] >> H) &&
-                                  (q == 0 || (lds_key[q] >> H) != (lds_key[q - 1] >> H));
-                if (!head) continue;
-                uint32_t e = q + 1;
-                while (e < n && (lds_key[e] >> H) == (lds_key[q] >> H)) e++;
-                for (uint32_t i = q + 1; i < e; i++) {  // stable insertion sort of [q, e)
-                    const KW kv = lds_key[i];
-                    const uint16_t iv = lds_idx[i];
-                    uint32_t j = i;
-                    while (j > q && lds_key[j - 1] > kv) {
-                        lds_key[j] = lds_key[j - 1];
-                        lds_idx[j] = lds_idx[j - 1];
-                        j--;
-                    }
-                    lds_key[j] = kv;
-                    lds_idx[j] = iv;
-                }
-            }
-            lds_barrier();
+            sort_ties<KW, NT, KI>(lds_key, lds_idx, n, H);
         } else if (ties > 256) {
             reload();
             block_lsd_sort<KW, NT, KI>(key, idx, bits, lds_key, lds_idx, cnt, tmp);
@@ -2039,12 +2083,274 @@ __device__ __forceinline__ void block_sort(KW (&key)[KI], uint16_t (&idx)[KI], i
     }
 }
 
+// Leaves up to which each has a CU of its own, and may use all of its registers
+// (beyond, two blocks a CU pay: see k_leaf_sort).
+constexpr uint32_t DENSE_LEAVES = 256;
+
+// Shape of a sort leaf: 1024 threads x 8 rows within 64 VGPRs and half of a
+// CU's LDS, so that two blocks share a CU.
+template <typename KW> struct SortLeaf {
+    static constexpr int NT = 1024, KI = LEAF_CAP / NT, NBB = 13, NBIN = 1 << NBB;
+    static constexpr int WORDS = LEAF_CAP * sizeof(KW);  // words in bins, then sorted keys
+    static constexpr int HIST = NBIN * 2;                // bin counters, or indices (digit passes)
+    static constexpr int BYTES = sizeof(KW) == 8 ? WORDS + HIST : 2 * WORDS;
+    static_assert(BYTES <= 81920 && LEAF_CAP * 2 <= HIST && KI * NT == LEAF_CAP, "two blocks a CU");
+};
+
+// The sort of one leaf by digit passes, for leaves with too many rows in one bin.
 template <typename K, typename KW>
-__global__ __launch_bounds__(LeafShape<KW>::NT)
-__attribute__((amdgpu_waves_per_eu(4))) void k_leaf_sort(const LeafDesc* __restrict__ leaves,
+__device__ __forceinline__ void leaf_sort_passes(char* pool, uint32_t n, uint64_t base, int bits,
+                                                 const K* __restrict__ src_k, const int32_t* __restrict__ src_r,
+                                                 K* __restrict__ out_k, int32_t* __restrict__ out_r)
+{
+    using SL = SortLeaf<KW>;
+    constexpr int NT = SL::NT, KI = SL::KI;
+    const LdsPad<KW, KI, 0> lds_key{(KW*)pool};
+    const LdsPad<uint16_t, KI, 0> lds_idx{(uint16_t*)(pool + SL::WORDS)};
+    uint32_t* const cnt = (uint32_t*)pool;
+    uint32_t* const tmp = cnt + NT / 64 * LSTRIDE;
+    uint64_t* const tmp64 = (uint64_t*)(pool + SL::WORDS);
+    const uint32_t w = threadIdx.x / 64, l = threadIdx.x & 63;
+    KW key[KI];
+    uint16_t idx[KI];
+    auto load_items = [&]() {
+#pragma unroll
+        for (int r = 0; r < KI; r++) {
+            const uint32_t q = (w * KI + r) * 64 + l;
+            const K v = ld_clamp(src_k, q, n);
+            key[r] = q < n ? (KW)(ord_of(v) - base) : (KW)~(KW)0;
+            idx[r] = (uint16_t)q;
+        }
+    };
+    lds_barrier();
+    load_items();
+    // Wide keys: by the top 32 bits of the relative key first (4 digit passes
+    // instead of up to 8). That order is final unless rows share those bits and
+    // differ below; few such ties are put in order by one thread a run, more take
+    // the passes over all bits.
+    for (int H = bits > 32 ? bits - 32 : 0;; H = 0) {
+        block_lsd_sort<KW, NT, KI, false, true>(key, idx, bits - H, lds_key, lds_idx, cnt, tmp, H);
+        if (H == 0) break;
+        uint64_t c = count_ties<NT, KI>(lds_key, lds_idx, n, H);
+        lds_barrier();
+        c = uniform(block_sum64<NT>(c, tmp64));
+#pragma unroll
+        for (int r = 0; r < KI; r++) lds_idx[(w * KI + r) * 64 + l] = idx[r];
+        lds_barrier();
+        if (c >> 32 == 0) break;
+        if ((uint32_t)c <= 256) {
+            sort_ties<KW, NT, KI>(lds_key, lds_idx, n, H);
+            break;
+        }
+        load_items();
+    }
+    // Keys go out first. The bucket may be sorted in place (its rows already
+    // sit in the output columns), so its row ids are all read (coalesced, into
+    // the now free key array) before any of them is overwritten.
+#pragma unroll
+    for (int r = 0; r < KI; r++) {
+        const uint32_t q = (w * KI + r) * 64 + l;
+        if (q < n) out_k[q] = key_of<K>(base + (uint64_t)lds_key[q]);
+    }
+    lds_barrier();
+    int32_t* const lds_rid = (int32_t*)pool;
+#pragma unroll
+    for (int r = 0; r < KI; r++) {
+        const uint32_t q = threadIdx.x + r * NT;
+        if (q < n) lds_rid[q] = src_r[q];
+    }
+    lds_barrier();
+#pragma unroll
+    for (int r = 0; r < KI; r++) {
+        const uint32_t q = (w * KI + r) * 64 + l;
+        if (q < n) out_r[q] = lds_rid[lds_idx[q]];
+    }
+}
+
+// The sort of one leaf. Each row is one word [key below its bin's bits | row] in
+// its bin of 2^13 (at most two rows a bin where keys are even), so that one
+// comparison of words decides the order (key, row) inside a bin whatever order
+// the bins were filled in. A row's key and row id stay with its thread, which
+// puts them in their places in LDS, from where they leave coalesced.
+// Bound by the memory traffic of its rows once two blocks share a CU: 2^29 rows
+// of 64-bit keys, 2.8 ms (4.6 TB/s; a copy reaches 4.7) from 4.3 ms with one block
+// of 148 KiB a CU, whose loads, LDS steps and stores followed one another.
+// DENSE: two blocks a CU, which leaves 64 VGPRs; a leaf with too many rows in one
+// bin is marked, for k_leaf_sort_passes (as a call from here the passes would make
+// this way spill). Otherwise, with a CU for every leaf, the leaf is sorted that way
+// at once: 100k rows, 14 us from 29; 1M Zipf rows, 92 us from 131.
+template <typename K, typename KW, bool DENSE>
+__global__ __launch_bounds__(SortLeaf<KW>::NT)
+__attribute__((amdgpu_waves_per_eu(DENSE ? 8 : 4))) void k_leaf_sort(LeafDesc* __restrict__ leaves, BufSet bufs,
+                                                                     K* __restrict__ out_k,
+                                                                     int32_t* __restrict__ out_r)
+{
+    using SL = SortLeaf<KW>;
+    constexpr int NT = SL::NT, KI = SL::KI;
+    __shared__ __align__(16) char pool[SL::BYTES];
+    KW* const word = (KW*)pool;
+    uint16_t* const start = (uint16_t*)(pool + SL::WORDS);  // rows of a bin, then its first place
+    uint32_t* const tmp = (uint32_t*)pool;
+
+    const LeafDesc L = leaves[blockIdx.x];
+    const uint32_t n = L.rn;
+    if (n == 0) return;
+    const K* __restrict__ src_k = (const K*)bufs.key[L.buf][0] + L.kr0;
+    const int32_t* __restrict__ src_r = bufs.rid[L.buf][0] + L.r0;
+    const uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)threadIdx.x / 64) * (KI * 64);
+    const uint32_t t = threadIdx.x;
+    uint32_t l = t & 63;
+    auto row = [&](int r) { return w0 + r * 64 + l; };
+    auto fresh = [&]() { asm volatile("" : "+v"(l)); };
+    // rows beyond n take no part: nothing of theirs is stored in LDS
+    KW key[KI];
+    uint32_t info[KI];
+    {
+        K v[KI];
+#pragma unroll
+        for (int r = 0; r < KI; r++) v[r] = ld_now(src_k, min(row(r), n - 1));
+#pragma unroll
+        for (int r = 0; r < KI; r++) key[r] = (KW)(ord_of(v[r]) - L.base);
+    }
+    const int sh = (int)L.bits > SL::NBB ? (int)L.bits - SL::NBB : 0;
+    static_assert(SL::HIST == NT * 16, "16 bytes of counters a thread");
+    ((uint4*)start)[t] = uint4{0, 0, 0, 0};
+    lds_barrier();
+    fresh();
+#pragma unroll
+    for (int r = 0; r < KI; r++) {
+        const uint32_t b = (uint32_t)(key[r] >> sh) & (SL::NBIN - 1u);
+        uint32_t slot = 0;
+        if (row(r) < n) slot = atomicAdd((uint32_t*)start + b / 2, 1u << (b & 1) * 16) >> (b & 1) * 16;
+        info[r] = b | slot << 16;
+    }
+    lds_barrier();
+    {
+        uint4 x = ((const uint4*)start)[t];
+        uint32_t c[4] = {x.x, x.y, x.z, x.w}, sum = 0, mx = 0, all;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const uint32_t a = c[i] & 0xffffu, b = c[i] >> 16;
+            sum += a + b;
+            mx = max(mx, max(a, b));
+        }
+        if (uniform(block_max<NT>(mx, tmp)) > BIN_MAXC) {
+            if constexpr (DENSE) {
+                if (t == 0) leaves[blockIdx.x].flags = L.flags | LEAF_CROWDED;
+            } else {
+                leaf_sort_passes<K, KW>(pool, n, L.base, (int)L.bits, src_k, src_r, out_k + L.out, out_r + L.out);
+            }
+            return;
+        }
+        uint32_t ex = block_excl_scan<NT>(sum, tmp, &all);
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const uint32_t a = c[i] & 0xffffu, b = c[i] >> 16;
+            c[i] = ex | (ex + a) << 16;
+            ex += a + b;
+        }
+        ((uint4*)start)[t] = uint4{c[0], c[1], c[2], c[3]};
+    }
+    lds_barrier();
+    fresh();
+    uint32_t cbmax = 0;
+#pragma unroll
+    for (int r = 0; r < KI; r++) {
+        const uint32_t b = info[r] & 0xffffu, slot = info[r] >> 16;
+        const uint32_t s0 = start[b], e0 = b + 1 < (uint32_t)SL::NBIN ? start[b + 1] : n, cb = e0 - s0;
+        const bool valid = row(r) < n;
+        key[r] = (key[r] & (((KW)1 << sh) - 1)) << 13 | (KW)row(r);
+        if (valid) word[s0 + slot] = key[r];
+        info[r] = valid ? s0 | cb << 13 | b << 19 : 0u;  // first place, rows and number of its bin
+        cbmax = valid && cb > 1 && cb > cbmax ? cb : cbmax;
+    }
+#pragma unroll
+    for (int r = 0; r < KI; r++) asm volatile("" : "+v"(info[r]));  // (packed, see k_leaf_join)
+    lds_barrier();
+    // The thread's rows walk their bins in step (past a shorter bin's end, still
+    // in the pool: ignored).
+    uint32_t rank[KI];
+#pragma unroll
+    for (int r = 0; r < KI; r++) rank[r] = 0;
+#pragma unroll 1
+    for (uint32_t j = 0; j < cbmax; j++) {
+#pragma unroll
+        for (int r = 0; r < KI; r++) {
+            const KW x = word[(info[r] & 0x1fffu) + j];
+            rank[r] += j < (info[r] >> 13 & 63u) && x < key[r] ? 1u : 0u;
+        }
+    }
+    // (row ids: on their way while the keys leave)
+    fresh();
+    int32_t rid[KI];
+#pragma unroll
+    for (int r = 0; r < KI; r++) rid[r] = ld_now(src_r, min(row(r), n - 1));
+#pragma unroll
+    for (int r = 0; r < KI; r++) rank[r] += info[r] & 0x1fffu;
+    lds_barrier();
+    int32_t* const lds_rid = (int32_t*)(sizeof(KW) == 8 ? pool : pool + SL::WORDS);
+    const bool together = sizeof(KW) == 4;
+#pragma unroll
+    for (int r = 0; r < KI; r++) {
+        if (info[r]) {
+            word[rank[r]] = (KW)(info[r] >> 19) << sh | key[r] >> 13;
+            if (together) lds_rid[rank[r]] = rid[r];
+        }
+    }
+    lds_barrier();
+#pragma unroll
+    for (int r = 0; r < KI; r++) {
+        const uint32_t q = t + r * NT;
+        if (q < n) out_k[L.out + q] = key_of<K>(L.base + (uint64_t)word[q]);
+    }
+    if (!together) {
+        lds_barrier();
+#pragma unroll
+        for (int r = 0; r < KI; r++)
+            if (info[r]) lds_rid[rank[r]] = rid[r];
+        lds_barrier();
+    }
+#pragma unroll
+    for (int r = 0; r < KI; r++) {
+        const uint32_t q = t + r * NT;
+        if (q < n) out_r[L.out + q] = lds_rid[q];
+    }
+}
+
+// The wide leaves that k_leaf_sort has marked, by digit passes: one block a CU,
+// each with every 256th leaf (crowded leaves are often neighbours).
+template <typename K, typename KW>
+__global__ __launch_bounds__(SortLeaf<KW>::NT)
+__attribute__((amdgpu_waves_per_eu(4))) void k_leaf_sort_passes(const LeafDesc* __restrict__ leaves, uint32_t count,
+                                                                BufSet bufs, K* __restrict__ out_k,
+                                                                int32_t* __restrict__ out_r)
+{
+    __shared__ __align__(16) char pool[SortLeaf<KW>::BYTES];
+    for (uint32_t i0 = blockIdx.x; i0 < count; i0 += DENSE_LEAVES * 64) {
+        const uint32_t i = i0 + (threadIdx.x & 63) * DENSE_LEAVES;
+        uint64_t marked = ballot(i < count && (leaves[min(i, count - 1)].flags & LEAF_CROWDED));
+        while (marked) {
+            const LeafDesc L = leaves[i0 + (uint32_t)(__ffsll((unsigned long long)marked) - 1) * DENSE_LEAVES];
+            marked &= marked - 1;
+            leaf_sort_passes<K, KW>(pool, L.rn, L.base, (int)L.bits, (const K*)bufs.key[L.buf][0] + L.kr0,
+                                    bufs.rid[L.buf][0] + L.r0, out_k + L.out, out_r + L.out);
+        }
+    }
+}
+
+// The sort of many leaves of 32-bit keys: one block does both ways, a counting
+// pass, or digit passes for crowded leaves. Narrow keys are often few with many
+// rows each, and a marked leaf has been read in vain: 2^28 rows of 2^20 keys take
+// 1.8 ms here, 2^27 rows with 64 a key 1.5; with k_leaf_sort and
+// k_leaf_sort_passes the latter took 2.5 (even keys would gain: 2^27 uniform ones
+// 2.7 ms the whole sort there, 3.1 here).
+template <typename K>
+__global__ __launch_bounds__(LeafShape<uint32_t>::NT)
+__attribute__((amdgpu_waves_per_eu(4))) void k_leaf_sort_narrow(const LeafDesc* __restrict__ leaves,
                                                             BufSet bufs, K* __restrict__ out_k,
                                                             int32_t* __restrict__ out_r)
 {
+    using KW = uint32_t;
     constexpr int NT = LeafShape<KW>::NT, KI = LeafShape<KW>::KI, NW = LeafShape<KW>::NW, C = LEAF_CAP;
     __shared__ KW lds_key_raw[C];
     __shared__ __align__(16) uint16_t lds_idx_raw[C];
@@ -2054,31 +2360,17 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_leaf_sort(const LeafDesc* __restr
     __shared__ uint32_t tmp[NW];
     __shared__ uint64_t tmp64[NW];
 
-    // Wide leaves (one block per CU either way) also park their row ids in
-    // LDS, loaded together with the keys: one memory latency instead of two.
-    constexpr bool PARK = sizeof(KW) == 8;
-    __shared__ int32_t lds_rid_park[PARK ? C : 1];
-
     const LeafDesc L = leaves[blockIdx.x];
     if (L.rn == 0) return;
     const K* __restrict__ src_k = (const K*)bufs.key[L.buf][0] + L.kr0;
     const int32_t* __restrict__ src_r = bufs.rid[L.buf][0] + L.r0;
     const uint32_t w = threadIdx.x / 64, l = threadIdx.x & 63;
     KW key[KI];
-    int32_t prid[PARK ? KI : 1];
 #pragma unroll
     for (int r = 0; r < KI; r++) {
         const uint32_t q = (w * KI + r) * 64 + l;
         const K v = ld_clamp(src_k, q, L.rn);
-        if (PARK) prid[PARK ? r : 0] = ld_clamp(src_r, threadIdx.x + r * NT, L.rn);
         key[r] = q < L.rn ? (KW)(ord_of(v) - L.base) : (KW)~(KW)0;
-    }
-    if (PARK) {
-#pragma unroll
-        for (int r = 0; r < KI; r++) {
-            const uint32_t q = threadIdx.x + r * NT;
-            if (q < L.rn) lds_rid_park[q] = prid[PARK ? r : 0];
-        }
     }
     uint16_t idx[KI];
 #pragma unroll
@@ -2100,17 +2392,15 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_leaf_sort(const LeafDesc* __restr
         const uint32_t q = (w * KI + r) * 64 + l;
         if (q < L.rn) out_k[L.out + q] = key_of<K>(L.base + (uint64_t)lds_key[q]);
     }
-    int32_t* lds_rid = PARK ? lds_rid_park : (int32_t*)lds_key_raw;
-    if (!PARK) {
-        lds_barrier();
+    int32_t* lds_rid = (int32_t*)lds_key_raw;
+    lds_barrier();
 #pragma unroll
-        for (int r = 0; r < KI; r++) {
-            const uint32_t q = threadIdx.x + r * NT;
-            const int32_t v = ld_clamp(src_r, q, L.rn);
-            if (q < L.rn) lds_rid[q] = v;
-        }
-        lds_barrier();
+    for (int r = 0; r < KI; r++) {
+        const uint32_t q = threadIdx.x + r * NT;
+        const int32_t v = ld_clamp(src_r, q, L.rn);
+        if (q < L.rn) lds_rid[q] = v;
     }
+    lds_barrier();
 #pragma unroll
     for (int r = 0; r < KI; r++) {
         const uint32_t q = (w * KI + r) * 64 + l;
@@ -2118,22 +2408,28 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_leaf_sort(const LeafDesc* __restr
     }
 }
 
-hipError_t launch_leaf_sort(int key_bytes, bool wide, const LeafDesc* leaves, uint32_t n,
+hipError_t launch_leaf_sort(int key_bytes, bool wide, LeafDesc* leaves, uint32_t n,
                             BufSet bufs, void* out_k, int32_t* out_r, hipStream_t st)
 {
     if (n == 0) return hipSuccess;
-    const dim3 grid(n), block(wide ? LeafShape<uint64_t>::NT : LeafShape<uint32_t>::NT);
-    if (key_bytes == 4) {
-        if (wide)
-            hipLaunchKernelGGL((k_leaf_sort<int32_t, uint64_t>), grid, block, 0, st, leaves, bufs, (int32_t*)out_k, out_r);
-        else
-            hipLaunchKernelGGL((k_leaf_sort<int32_t, uint32_t>), grid, block, 0, st, leaves, bufs, (int32_t*)out_k, out_r);
-    } else {
-        if (wide)
-            hipLaunchKernelGGL((k_leaf_sort<int64_t, uint64_t>), grid, block, 0, st, leaves, bufs, (int64_t*)out_k, out_r);
-        else
-            hipLaunchKernelGGL((k_leaf_sort<int64_t, uint32_t>), grid, block, 0, st, leaves, bufs, (int64_t*)out_k, out_r);
-    }
+    const dim3 grid(n), block(SortLeaf<uint64_t>::NT), narrow(LeafShape<uint32_t>::NT);
+#define TJ_LS(K)                                                                                                   \
+    do {                                                                                                           \
+        if (n <= DENSE_LEAVES && wide) {                                                                           \
+            hipLaunchKernelGGL((k_leaf_sort<K, uint64_t, false>), grid, block, 0, st, leaves, bufs, (K*)out_k, out_r); \
+        } else if (n <= DENSE_LEAVES) {                                                                            \
+            hipLaunchKernelGGL((k_leaf_sort<K, uint32_t, false>), grid, block, 0, st, leaves, bufs, (K*)out_k, out_r); \
+        } else if (wide) {                                                                                         \
+            hipLaunchKernelGGL((k_leaf_sort<K, uint64_t, true>), grid, block, 0, st, leaves, bufs, (K*)out_k, out_r); \
+            hipLaunchKernelGGL((k_leaf_sort_passes<K, uint64_t>), dim3(DENSE_LEAVES), block, 0, st, leaves, n, bufs, \
+                               (K*)out_k, out_r);                                                                  \
+        } else {                                                                                                   \
+            hipLaunchKernelGGL((k_leaf_sort_narrow<K>), grid, narrow, 0, st, leaves, bufs, (K*)out_k, out_r);      \
+        }                                                                                                          \
+    } while (0)
+    if (key_bytes == 4) TJ_LS(int32_t);
+    else TJ_LS(int64_t);
+#undef TJ_LS
     return hipGetLastError();
 }
 
