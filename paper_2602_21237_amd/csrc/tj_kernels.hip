@@ -769,8 +769,11 @@ hipError_t launch_learned_hist(int key_bytes, const ChunkDesc* chunks, uint32_t 
 // A row of chunk c with digit d and rank r inside the chunk goes to
 // cstart[d] + cbsum[b][d] + hist[c][d] + r.
 // ---------------------------------------------------------------------------
-constexpr int SCAN_THREADS = 256;
-constexpr int SCAN_DPT = NB / SCAN_THREADS;
+// A digit a thread, and all loads of a step before its stores: both levels are
+// chains of memory latencies (level 2 of a 2^29-row pass, 64 scan blocks: 30 us
+// with two digits a thread, each block's total loaded after the last one's prefix
+// was stored, 11 so; one pass of 100k rows, scan blocks scanned here: 9 -> 6 us).
+constexpr int SCAN_THREADS = NB;
 
 // Exclusive prefix of digit d over `n` chunks from hist row `c0`, in place; returns the total.
 __device__ __forceinline__ uint32_t scan_chunks(uint32_t* __restrict__ hist, uint64_t c0, uint32_t n, uint32_t d)
@@ -792,11 +795,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_l1(const CBlockDesc* __re
                                                           uint32_t* __restrict__ cbsum)
 {
     const CBlockDesc cb = cblocks[blockIdx.x];
-#pragma unroll
-    for (int i = 0; i < SCAN_DPT; i++) {
-        const uint32_t d = threadIdx.x + i * SCAN_THREADS;
-        cbsum[(uint64_t)blockIdx.x * NB + d] = scan_chunks(hist, cb.chunk0, cb.nchunks, d);
-    }
+    cbsum[(uint64_t)blockIdx.x * NB + threadIdx.x] = scan_chunks(hist, cb.chunk0, cb.nchunks, threadIdx.x);
 }
 
 // One block per segment: level 2 of the scan for each of its sides, and its
@@ -818,59 +817,58 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_l2(const GroupDesc* __res
                                                           uint64_t* __restrict__ hmiss)
 {
     __shared__ uint32_t tmp[SCAN_THREADS / 64];
-    ChildRec rec[SCAN_DPT];
+    const uint32_t d = threadIdx.x;
+    ChildRec rec{0, 0, ~0ull, 0};
+    GroupDesc g[2];
+    uint32_t tot[2];
+    uint64_t lo[2], hi[2];
+    g[0] = groups[blockIdx.x * nside];
+    g[1] = groups[blockIdx.x * nside + nside - 1];
+    const uint32_t nbins = 1u << g[0].bits, dc = min(d, nbins - 1);
+    const uint64_t at0 = g[0].child0 / nside;
+    // both sides' memory first, then their scans
 #pragma unroll
-    for (int i = 0; i < SCAN_DPT; i++) rec[i] = ChildRec{0, 0, ~0ull, 0};
-    uint32_t nbins = 0;
-    uint64_t at0 = 0;
-    for (int side = 0; side < nside; side++) {
-        const GroupDesc g = groups[blockIdx.x * nside + side];
-        nbins = 1u << g.bits;
-        if (side == 0) at0 = g.child0 / nside;
-        uint32_t tot[SCAN_DPT];
-        uint32_t local = 0;
+    for (int side = 0; side < 2; side++) {
+        if (side >= nside) break;
+        lo[side] = ld_now(gmin + g[side].child0, dc);
+        hi[side] = ld_now(gmax + g[side].child0, dc);
+        uint32_t run = 0;
+        if (direct) {
+            run = scan_chunks(hist, g[side].chunk0, g[side].nchunks, d);
+            if (g[side].nchunks) cbsum[(uint64_t)g[side].cblock0 * NB + d] = 0;
+        } else {
+            uint32_t* const cs = cbsum + (uint64_t)g[side].cblock0 * NB;
+            const uint32_t n = g[side].ncblocks;
+            for (uint32_t b0 = 0; b0 < n; b0 += 16) {  // (16 loads in flight: a store stops the next load)
+                uint32_t v[16];
 #pragma unroll
-        for (int i = 0; i < SCAN_DPT; i++) {
-            // contiguous digits per thread keep the block scan in digit order
-            const uint32_t d = threadIdx.x * SCAN_DPT + i;
-            uint32_t run = 0;
-            if (direct) {
-                run = scan_chunks(hist, g.chunk0, g.nchunks, d);
-                if (g.nchunks) cbsum[(uint64_t)g.cblock0 * NB + d] = 0;
-            } else {
-                for (uint32_t b = 0; b < g.ncblocks; b++) {
-                    const uint64_t at = (uint64_t)(g.cblock0 + b) * NB + d;
-                    const uint32_t v = cbsum[at];
-                    cbsum[at] = run;
-                    run += v;
+                for (int b = 0; b < 16; b++) v[b] = b0 + b < n ? cs[(uint64_t)(b0 + b) * NB + d] : 0u;
+#pragma unroll
+                for (int b = 0; b < 16; b++) {
+                    if (b0 + b < n) cs[(uint64_t)(b0 + b) * NB + d] = run;
+                    run += v[b];
                 }
             }
-            tot[i] = d < nbins ? run : 0u;
-            local += tot[i];
         }
-        uint32_t all;
-        uint64_t ex = block_excl_scan<SCAN_THREADS>(local, tmp, &all);
-#pragma unroll
-        for (int i = 0; i < SCAN_DPT; i++) {
-            const uint32_t d = threadIdx.x * SCAN_DPT + i;
-            if (d < nbins) {
-                ccount[g.child0 + d] = tot[i];
-                cstart[g.child0 + d] = g.dst_start + ex;
-                const uint64_t lo = gmin[g.child0 + d], hi = gmax[g.child0 + d];
-                if (side == 0) rec[i].rn = tot[i];
-                else rec[i].sn = tot[i];
-                rec[i].lo = lo < rec[i].lo ? lo : rec[i].lo;
-                rec[i].hi = hi > rec[i].hi ? hi : rec[i].hi;
-            }
-            ex += tot[i];
-        }
+        tot[side] = d < nbins ? run : 0u;
     }
 #pragma unroll
-    for (int i = 0; i < SCAN_DPT; i++) {
-        const uint32_t d = threadIdx.x * SCAN_DPT + i;
-        if (d >= nbins) continue;
-        out[at0 + d] = rec[i];
-        if (hout) hout[at0 + d] = rec[i];
+    for (int side = 0; side < 2; side++) {
+        if (side >= nside) break;
+        uint32_t all;
+        const uint64_t ex = block_excl_scan<SCAN_THREADS>(tot[side], tmp, &all);
+        if (d < nbins) {
+            ccount[g[side].child0 + d] = tot[side];
+            cstart[g[side].child0 + d] = g[side].dst_start + ex;
+            if (side == 0) rec.rn = tot[side];
+            else rec.sn = tot[side];
+            rec.lo = lo[side] < rec.lo ? lo[side] : rec.lo;
+            rec.hi = hi[side] > rec.hi ? hi[side] : rec.hi;
+        }
+    }
+    if (d < nbins) {
+        out[at0 + d] = rec;
+        if (hout) hout[at0 + d] = rec;
     }
     if (hmiss && blockIdx.x == 0 && threadIdx.x == 0) *hmiss = *miss;
 }
