@@ -1005,10 +1005,12 @@ struct Exec {
                 if (!hdr) {
                     // (one pageable buffer holds both)
                     hdr = (Header*)pinned_down(sizeof(Header) + (dev_ok ? 0 : nrec * sizeof(ChildRec)));
+                    if (!hdr) return TJ_E_HIP;
                     TJ_CK(hipMemcpyAsync(hdr->sum, d_sum, 5 * 8, hipMemcpyDeviceToHost, st));
-                    hrec = (ChildRec*)(hdr + 1);
-                    if (!dev_ok)
+                    if (!dev_ok) {  // (no records otherwise: hrec stays null, and a level that goes back reads them)
+                        hrec = (ChildRec*)(hdr + 1);
                         TJ_CK(hipMemcpyAsync(hrec, d_crec, nrec * sizeof(ChildRec), hipMemcpyDeviceToHost, st));
+                    }
                 }
                 TJ_CK(hipStreamSynchronize(st));
                 if (t_noalloc) hdr->miss = hdr->sum[3];
