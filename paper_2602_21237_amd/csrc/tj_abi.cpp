@@ -2487,8 +2487,13 @@ static int sort_body(int key_type, const void* keys_in, const int32_t* rids_in, 
             }
         }
         if (!spec && !learned) {
-            if (unlimited && !want_learned && !t_noalloc) x.root_probe = true;
-            else TJ_RET(probe(x, keys_in, n, nullptr, 0, lo, hi));
+            if (unlimited && !want_learned && !t_noalloc) {
+                x.root_probe = true;
+                lo = 0;  // (unknown: a sample of one key must not pass for the range)
+                hi = ~0ull;
+            } else {
+                TJ_RET(probe(x, keys_in, n, nullptr, 0, lo, hi));
+            }
         }
     }
     if (unlimited) {
@@ -2636,8 +2641,13 @@ static int join_body(int key_type, const void* r_keys, const int32_t* r_rids, ui
             }
         }
         if (!spec && !learned) {
-            if (unlimited && !want_learned) x.root_probe = true;  // (see sort_body)
-            else TJ_RET(probe(x, r_keys, n_r, s_keys, n_s, lo, hi));
+            if (unlimited && !want_learned) {  // (see sort_body)
+                x.root_probe = true;
+                lo = 0;
+                hi = ~0ull;
+            } else {
+                TJ_RET(probe(x, r_keys, n_r, s_keys, n_s, lo, hi));
+            }
         }
     }
     uint64_t total = 0;
