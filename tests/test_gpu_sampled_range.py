@@ -51,12 +51,13 @@ def test_sort(tj, n, kind, dtype):
 
 @pytest.mark.parametrize("dtype", [np.int32, np.int64])
 @pytest.mark.parametrize("kind", ["one row", "rare", "period"])
-@pytest.mark.parametrize("n_r,n_s", [(3, N + 100), (N, 2)])
+@pytest.mark.parametrize("n_r,n_s", [(3, N + 4097), (N + 1, 3)])
 def test_join(tj, n_r, n_s, kind, dtype):
-    # (the short side holds the sampled key first: its only sampled row)
+    # (the sample takes the last row too: each side ends with the sampled key)
     big = column(kind, max(n_r, n_s), dtype)
     rest = np.unique(big)
-    short = np.concatenate([big[:1], rest[rest != big[0]][-(min(n_r, n_s) - 1):]]).astype(dtype)[:min(n_r, n_s)]
+    short = np.array([big[0], rest[rest != big[0]][-1], big[0]], dtype=dtype)
+    assert big[-1] == big[0]
     rk, sk = (short, big) if n_r < n_s else (big, short)
     rng = np.random.default_rng(n_r + n_s)
     rr, sr = rng.permutation(rk.size).astype(np.int32), rng.permutation(sk.size).astype(np.int32)
