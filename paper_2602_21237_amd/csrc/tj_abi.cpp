@@ -1048,7 +1048,7 @@ struct Exec {
                         return launch_scatter_lines((int)kb_in, (int)kb_out, sh.rids, dc, nc, dg, d_hist, d_cbsum, d_cstart,
                                                     bufs, spec ? d_miss : nullptr, st);
                     return launch_scatter((int)kb_in, (int)kb_out, sh.rids, write_keys, dc, nc, dg, d_hist, d_cbsum,
-                                          d_cstart, bufs, spec ? d_miss : nullptr, st);
+                                          d_cstart, bufs, spec || root ? d_miss : nullptr, st);
                 }));
             }
             if (ready) TJ_CK(hipEventSynchronize(ready));
@@ -1057,6 +1057,14 @@ struct Exec {
                 // caller probes the exact range and starts again
                 stats.passes--;
                 return TJ_RANGE_MISS;
+            }
+            if (root && hdr->lo == hdr->hi) {
+                // one key: nothing was counted or moved, the segment itself goes on
+                stats.bytes_read -= scanned * (2 * (uint64_t)kb_in + (sh.rids ? 4 : 0));
+                Seg one = segs[0];
+                one.lo = one.hi = hdr->lo;
+                sink(one);
+                continue;
             }
             if (root) {
                 Plan& pl = plan[0];
@@ -1779,6 +1787,11 @@ struct Exec {
         if (!mat) {
             uint64_t cross_pairs = 0;
             for (const CrossDesc& c : crosses) cross_pairs += c.a * c.b;
+            if (leaves.empty()) {  // the host knows every pair already
+                crosses.clear();
+                *total_out = cross_pairs;
+                return TJ_OK;
+            }
             ht.stop();
             TJ_CK(launch_fill_u64(d_total, 1, 0, st));
             // leaves grouped by key width (order does not matter for a count)

@@ -591,6 +591,9 @@ __device__ __forceinline__ uint32_t group_digit(uint64_t o, uint64_t base, uint3
 // block of each group writes it to the group for the kernels that follow, and
 // block 0 the extremes to root.hdr (pinned) for the host. The host then plans
 // no launch before the probe is done: a call of 10^5 rows saves the wait.
+// Inputs of one key need no pass: nothing is counted (the scan adds up stale
+// counts, which nobody reads) and range_miss stops the scatter. (Counting a join
+// of 10^4 x 10^4 rows of one key: 56 us with the wait, 64 with the whole pass, 39 so.)
 template <typename K, bool LEARNED, int NT = PART_THREADS, bool ROOT = false>
 __global__ __launch_bounds__(NT) void k_hist(const ChunkDesc* __restrict__ chunks,
                                                        GroupDesc* __restrict__ groups,
@@ -626,8 +629,10 @@ __global__ __launch_bounds__(NT) void k_hist(const ChunkDesc* __restrict__ chunk
             if (blockIdx.x == 0) {
                 root.hdr[0] = lo;
                 root.hdr[1] = hi;
+                if (lo == hi) *range_miss = 1u;  // stops the scatter
             }
         }
+        if (lo == hi) return;
     }
     const K* __restrict__ src = (const K*)bufs.key[g.src][g.side] + g.src_koff + ch.start;
     uint16_t* __restrict__ bk = LEARNED ? bkt.b[g.side] + ch.start : nullptr;
