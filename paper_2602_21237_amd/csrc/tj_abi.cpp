@@ -20,6 +20,7 @@
 // workspace, and each range is processed on its own; its first pass scans the
 // whole input and keeps only the range's rows. The extra input scans are the
 // GPU counterpart of the spill term alpha(N, M).
+#include "tj_events.h"
 #include "tj_internal.h"
 #include "../../include/tj.h"
 
@@ -456,20 +457,12 @@ void give_event(hipEvent_t e)
     t_events->push_back({dev, e});
 }
 
-// Events that the host waits for (no timing): one per thread and device.
-thread_local std::vector<std::pair<int, hipEvent_t>>* t_waits = nullptr;
+thread_local WaitEvents* t_waits = nullptr;  // never freed, like the pinned staging
 
-hipEvent_t wait_event()
+hipEvent_t wait_event(hipStream_t st)
 {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return nullptr;
-    if (!t_waits) t_waits = new std::vector<std::pair<int, hipEvent_t>>();
-    for (auto& pe : *t_waits)
-        if (pe.first == dev) return pe.second;
-    hipEvent_t e = nullptr;
-    if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return nullptr;
-    t_waits->push_back({dev, e});
-    return e;
+    if (!t_waits) t_waits = new WaitEvents();
+    return t_waits->of(st);
 }
 
 void free_thread_staging()
@@ -489,12 +482,13 @@ void free_thread_staging()
         delete t_host_vecs;
         t_host_vecs = nullptr;
     }
-    for (auto** pool : {&t_events, &t_waits}) {
-        if (!*pool) continue;
-        for (auto& pe : **pool) (void)hipEventDestroy(pe.second);
-        delete *pool;
-        *pool = nullptr;
+    if (t_events) {
+        for (auto& pe : *t_events) (void)hipEventDestroy(pe.second);
+        delete t_events;
+        t_events = nullptr;
     }
+    delete t_waits;
+    t_waits = nullptr;
 }
 
 void return_host_vecs(HostVecs& hv, HostVecs* owned)
@@ -998,7 +992,7 @@ struct Exec {
             // choice of the partitioner, it reads back first.)
             hipEvent_t ready = nullptr;
             if (hdr && !auto_probe) {
-                ready = wait_event();
+                ready = wait_event(st);
                 if (!ready) return TJ_E_HIP;
                 TJ_CK(hipEventRecord(ready, st));
             } else {
