@@ -368,10 +368,10 @@ int tj_join_materialize_multi(int ncols, const int *key_types, const void *const
  * one set of kernel launches replaces one per request. The fused call takes
  * one arena block (combined columns, outputs and workspace); a join batch in
  * which some request's pairs exceed its own capacity is served one request at
- * a time in that block. result->fused reports the batch size. At most half of
- * the slots (one at least) run small requests at a time: while they do, small
- * requests at the head of the queue wait for one of those calls to end, and a
- * larger request behind them may start before.
+ * a time in that block. result->fused reports the batch size. While half of
+ * the slots (one at least) run small requests, a small request that finds no
+ * partner in the queue waits until the next of those calls ends; requests
+ * behind it may start before.
  *
  * All functions are thread-safe. Inputs must stay valid and unchanged, and
  * outputs untouched, until the request completes.
