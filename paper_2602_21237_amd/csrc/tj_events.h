@@ -20,15 +20,24 @@ public:
         for (auto& pe : events_) (void)hipEventDestroy(pe.second);
     }
 
-    // The event for waits on `st`; null if it cannot be had.
-    hipEvent_t of(hipStream_t)
+    // The event for waits on `st`, of that stream's device (not the thread's
+    // current one: a caller may pass another device's stream); null if it
+    // cannot be had. The current device stays what it was.
+    hipEvent_t of(hipStream_t st)
     {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+        int cur = 0;
+        hipDevice_t dev = 0;
+        if (hipGetDevice(&cur) != hipSuccess) return nullptr;
+        // (the null stream, and the handles that name it or the thread's own, are the current device's)
+        if ((uintptr_t)st <= 2) dev = cur;
+        else if (hipStreamGetDevice(st, &dev) != hipSuccess) return nullptr;
         for (auto& pe : events_)
             if (pe.first == dev) return pe.second;
+        if (dev != cur && hipSetDevice(dev) != hipSuccess) return nullptr;
         hipEvent_t e = nullptr;
-        if (hipEventCreateWithFlags(&e, hipEventDisableTiming | hipEventBlockingSync) != hipSuccess) return nullptr;
+        const hipError_t rc = hipEventCreateWithFlags(&e, hipEventDisableTiming | hipEventBlockingSync);
+        if (dev != cur && hipSetDevice(cur) != hipSuccess) return nullptr;
+        if (rc != hipSuccess) return nullptr;
         events_.push_back({dev, e});
         return e;
     }

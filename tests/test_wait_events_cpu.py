@@ -73,3 +73,9 @@ def test_waits_block(seen):
 
 def test_events_are_released(seen):
     assert seen["gone"] == len(seen["made_on"])
+
+
+def test_events_are_of_the_streams_device(seen):
+    # null stream, streams of devices 0, 3, 3, null stream with device 3 current, stream of device 0
+    assert [g[0] for g in seen["got"]] == [0, 0, 1, 1, 1, 0] and seen["made_on"] == [0, 3]
+    assert all(g[1] for g in seen["got"])  # the current device stays
