@@ -2841,6 +2841,70 @@ static __device__ __noinline__ void join_sorted(__attribute__((address_space(3))
     }
 }
 
+// Pairs a probing row, on average over the block, beyond which its runs are
+// written as they come (write_runs) instead of in stretches staged in LDS, where
+// each stretch looks at all pairs of its rows. Joins of 2^18 rows with `a` a key
+// and up to 2^22 with `b`, in stretches and as they come: a = b = 6, 108 and 122
+// us; a = b = 8, 127 and 126; a = 8, b = 128, 440 and 367; a = b = 16, 220 and
+// 142; a = b = 47, 820 and 174.
+constexpr uint32_t DIRECT_PAIRS = 6;
+
+// The pairs of a join block, straight from the row ids in run order: each wave
+// takes an equal share of the slots and writes 64 at a time. run[p] (at the
+// first table position of a run): slots << 13 | probing rows before it; `all`
+// the same for the whole block. trid, prid: the table's and the probing rows'
+// ids in run order; the probing rows are the outer loop of a run if `swap`.
+template <int NW>
+__device__ __forceinline__ void write_runs(const uint32_t* run, uint32_t all, uint32_t tn, uint32_t slots, bool swap,
+                                           uint64_t base, uint64_t capacity, const int32_t* trid, const int32_t* prid,
+                                           int32_t* __restrict__ out_t, int32_t* __restrict__ out_p)
+{
+    const uint32_t l = threadIdx.x & 63, w = uniform(threadIdx.x / 64);
+    const uint32_t share = (slots / NW + 64) & ~63u;
+    const uint32_t end = min((w + 1) * share, slots);
+    uint32_t x = w * share;
+    // the run of slot x: the last position whose runs before it end at or before x
+    // (a run's other positions, and runs without probing rows, end where they start)
+    auto find = [&]() {
+        uint32_t lo = 0, hi = tn;
+        while (hi - lo > 1) {
+            const uint32_t m = (lo + hi) / 2;
+            if (uniform(run[m]) >> 13 <= x) lo = m;
+            else hi = m;
+        }
+        return lo;
+    };
+    if (x >= end) return;
+    uint32_t p = find();
+    while (x < end) {
+        const uint32_t here = uniform(run[p]), next = p + 1 < tn ? uniform(run[p + 1]) : all;
+        const uint32_t e0 = here >> 13, e1 = next >> 13;
+        if (e1 <= x) {  // (behind the last run: table rows without a match)
+            p = find();
+            continue;
+        }
+        const uint32_t g = here & 0x1fffu, b = (next & 0x1fffu) - g, a = (e1 - e0) / b;
+        const uint32_t m = swap ? a : b, dq = 64 / m, dr = 64 % m;
+        const uint32_t stop = min(e1, end);
+        uint32_t y = x + l, outer = (y - e0) / m, inner = y - e0 - outer * m;
+        for (; y < stop; y += 64) {
+            const uint64_t o = base + y;
+            if (o < capacity) {
+                out_t[o] = trid[p + (swap ? inner : outer)];
+                out_p[o] = prid[g + (swap ? outer : inner)];
+            }
+            outer += dq;
+            inner += dr;
+            if (inner >= m) {
+                inner -= m;
+                outer++;
+            }
+        }
+        x = stop;
+        p += a;
+    }
+}
+
 // The join of one block. The side of fewer rows is the table: its keys are
 // binned by their top bits (a quarter to one row a bin where keys are even),
 // placed, and ranked exactly inside their bin, so that it is in (key, position)
@@ -2849,7 +2913,8 @@ static __device__ __noinline__ void join_sorted(__attribute__((address_space(3))
 // collected run by run and ranked by position within the run, so nothing depends
 // on the order of atomics. Pairs: R item i of a run and S item k have slot
 // E + i * b + k, with E the pairs before the run and b its S items; the probing
-// rows write both columns into LDS, from where they leave coalesced.
+// rows write both columns into LDS, from where they leave coalesced (blocks of
+// many pairs a row: see write_runs).
 // What bounds the block is its LDS work and its waits, not memory. Only the
 // table's rows are sorted, which are the fewer, where sorting both sides together
 // took three to five digit passes over all rows and a check of the order; and with
@@ -3220,18 +3285,34 @@ __attribute__((amdgpu_waves_per_eu(sizeof(KW) == 4 && !SELF ? 8 : 4))) void k_le
                 if (at[r] >> 13 > RUN_SCAN) rank[r] += cnt[(at[r] & 0x1fffu) / RUN_SCAN * NW + w];
         }
         fresh();
+        int32_t* const out_t = swap ? out_s : out_r;
+        int32_t* const out_p = swap ? out_r : out_s;
+        // many pairs a row: their runs are written as they come, from the row ids in order
+        const bool direct = uniform(ltot) > DIRECT_PAIRS * pn;
+        if (direct) {
 #pragma unroll
-        for (int r = 0; r < KI; r++)  // first slot, stride
-            at[r] = ((run[info[r] >> 13 ? info[r] & 0x1fffu : 0u] >> 13) + rank[r] * (swap ? info[r] >> 13 : 1u)) |
-                    (swap ? 1u : at[r] >> 13) << 19;
+            for (int r = 0; r < KI; r++) at[r] = (at[r] & 0x1fffu) + rank[r];  // the row's place
+        } else {
+#pragma unroll
+            for (int r = 0; r < KI; r++)  // first slot, stride
+                at[r] = ((run[info[r] >> 13 ? info[r] & 0x1fffu : 0u] >> 13) + rank[r] * (swap ? info[r] >> 13 : 1u)) |
+                        (swap ? 1u : at[r] >> 13) << 19;
+        }
         lds_barrier();
+        if (direct) {
+            int32_t* const prid = (int32_t*)prow;
+#pragma unroll
+            for (int r = 0; r < KI; r++)
+                if (info[r] >> 13) prid[at[r]] = rid[r];
+            lds_barrier();
+            write_runs<NW>(run, uniform(s_all), tn, uniform(ltot), swap, SELF ? 0 : s_base, capacity, trid, prid, out_t, out_p);
+            return;
+        }
         const uint64_t base = SELF ? 0 : s_base;
         // all but the table's row ids is free: a stretch of both output columns at a time
         const uint32_t slots = (JL::BYTES - tn4 * 4) / 8;
         int32_t* const col_t = (int32_t*)(pool + tn4 * 4);
         int32_t* const col_p = col_t + slots;
-        int32_t* const out_t = swap ? out_s : out_r;
-        int32_t* const out_p = swap ? out_r : out_s;
         for (uint32_t c0 = 0; c0 < ltot; c0 += slots) {
             const uint32_t cn = ltot - c0 < slots ? ltot - c0 : slots;
 #pragma unroll
