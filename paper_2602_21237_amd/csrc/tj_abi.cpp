@@ -204,12 +204,13 @@ const uint64_t kMaxRows = (1ull << 31) - 1;
 // range into equal parts. Levels of at least LINES_MIN_ROWS rows take them,
 // when at least 3/4 of the rows are in segments of LINES_SEG_ROWS or more that
 // two levels of LN_D digits bring down to leaves.
-// leaf_fill: rows a leaf bucket is planned for where keys are even: 5 standard
-// deviations and more below LEAF_CAP, for the sort (sd 87) and for the join of
-// foreign keys of about 4 rows each (sd 180). Elsewhere half of it, so that a
+// leaf_fill: rows a leaf bucket is planned for at most, where keys are even, and
+// for this rule: 5 standard deviations below LEAF_CAP for single rows (sd 87),
+// less for a join, whose rows come in groups of one key. How far they spread
+// shows after a pass (even_fill). Where keys are not even, half of it, so that a
 // bucket of twice the density still fits.
 constexpr uint64_t LINES_MIN_ROWS = 16ull << 20, LINES_SEG_ROWS = 1ull << 18;
-inline uint64_t leaf_fill(bool join) { return join ? 7300 : 7600; }
+inline uint32_t leaf_fill(bool join) { return join ? 7300 : 7600; }
 inline bool lines_seg(uint64_t rows, bool even, uint64_t fill)
 {
     if (rows < LINES_SEG_ROWS || rows > LN_D * LN_D * fill) return false;
@@ -217,9 +218,21 @@ inline bool lines_seg(uint64_t rows, bool even, uint64_t fill)
     return rows <= (even ? fit : fit / 2) || rows > 2 * fit;
 }
 
+// Rows a leaf bucket is planned for whose row count has the variance
+// `dispersion` times its mean: 6 standard deviations below LEAF_CAP (the
+// dispersion comes from a few hundred neighbours and is off by a tenth and more;
+// one bucket that overflows costs the level 0.5 ms at 2^29 rows, as its other
+// 90,000 leaves go back to the host), but at least half of it: beyond a
+// dispersion of about 110 some overflow whatever is planned.
+inline uint32_t even_fill(double dispersion, bool join)
+{
+    const double sd6 = 6.0 * std::sqrt(dispersion), root = (std::sqrt(sd6 * sd6 + 4.0 * LEAF_CAP) - sd6) / 2;
+    return (uint32_t)std::min<double>(leaf_fill(join), std::max<double>(LEAF_CAP / 2, root * root));
+}
+
 // Digit of such a segment: shift, multiplier, digits in use. A key range of
 // few values has no multiplier; its digits are a power of two of at most 2^8.
-inline void plan_lines(uint64_t span, uint64_t rows, bool even, uint64_t fill, uint32_t& shift, uint32_t& bits,
+inline void plan_lines(uint64_t span, uint64_t rows, bool even, uint32_t fill, uint32_t& shift, uint32_t& bits,
                        uint32_t& mul, uint32_t& ndig)
 {
     const uint64_t leaves = (rows + fill - 1) / fill;
@@ -311,6 +324,7 @@ struct Seg {
     // Its neighbours under its parent's digit hold about as many rows: keys
     // spread evenly, so digits of equal width get about equal rows.
     bool even = false;
+    uint32_t fill = 0;  // rows a leaf bucket of it is planned for (even_fill; 0: leaf_fill)
     // Far more rows than its radix digit gave each bucket of its parent on
     // average: likely crowded by one frequent key (see Exec::pick_pivots).
     bool skew = false;
@@ -718,7 +732,7 @@ struct Exec {
             }
             if (lines) {
                 Plan& pl = plan[i];
-                plan_lines(s.hi - s.lo, s.rn + s.sn, s.even, leaf_fill(sh.join), pl.shift, pl.bits, pl.mul, pl.ndig);
+                plan_lines(s.hi - s.lo, s.rn + s.sn, s.even, s.fill ? s.fill : leaf_fill(sh.join), pl.shift, pl.bits, pl.mul, pl.ndig);
                 const bool fits = pl.shift <= 32 && (((pl.mul ? (1ull << 32) / pl.mul + 1 : 1) << pl.shift) <= (1ull << 32));
                 pl.kb_out = sh.join && s.kb == 8 && fits ? 4u : s.kb;
                 all_narrow = all_narrow && pl.kb_out == 4;
@@ -1079,7 +1093,7 @@ struct Exec {
             // narrowed by this pass; a child with more than SKEW_FACTOR times its
             // share of the parent's rows under this digit (and more than a leaf
             // holds) is crowded, except below a pivot split (those go radix).
-            auto emit_child = [&](uint32_t gi, const ChildRec& cr, uint64_t r0, uint64_t s0, bool even) {
+            auto emit_child = [&](uint32_t gi, const ChildRec& cr, uint64_t r0, uint64_t s0, bool even, uint32_t fill) {
                 const GroupDesc& g0 = groups[gi];
                 const Seg& par = segs[gseg[gi]];
                 const uint32_t seg_kb = plan[gseg[gi]].kb_out;
@@ -1098,6 +1112,7 @@ struct Exec {
                 c.wdisp = par.wdisp;
                 c.wdisp_s = par.wdisp_s;
                 c.even = even;
+                c.fill = fill;
                 const uint64_t rows = c.rn + c.sn, share = (par.rn + par.sn) / g0.ndig;
                 c.skew = !(g0.flags & GROUP_PIVOT) && c.lo < c.hi && rows > (uint64_t)LEAF_CAP &&
                          rows > SKEW_FACTOR * share;
@@ -1143,7 +1158,7 @@ struct Exec {
                         if (b.seg >= ng / (uint32_t)nside) return TJ_E_INTERNAL;
                         const ChildRec cr{b.rn, b.sn, b.lo, b.hi};
                         emit_child(gi, cr, groups[gi].dst_start + b.r_off,
-                                   nside == 2 ? groups[gi + 1].dst_start + b.s_off : 0, false);
+                                   nside == 2 ? groups[gi + 1].dst_start + b.s_off : 0, false, 0);
                     }
                     continue;
                 }
@@ -1177,11 +1192,25 @@ struct Exec {
                     const uint64_t a = rows_of(d), b = rows_of(e);
                     return (a > b ? a - b : b - a) <= a / 16;
                 };
+                // The spread of its children's rows around their trend, for segments
+                // that may be cut evenly again: second differences, whose mean
+                // square is six times the variance.
+                uint32_t fill = 0;
+                if (segs[gseg[gi]].rn + segs[gseg[gi]].sn >= 2 * LINES_SEG_ROWS) {
+                    double sq = 0, rows = 0;
+                    for (uint32_t d = 1; d + 2 < g0.ndig; d++) {
+                        if (!alike(d, d - 1) || !alike(d, d + 1)) continue;
+                        const double a = (double)rows_of(d - 1), b = (double)rows_of(d), c = (double)rows_of(d + 1);
+                        sq += (a - 2 * b + c) * (a - 2 * b + c);
+                        rows += a + b + c;
+                    }
+                    if (rows > 0) fill = even_fill(sq / (2 * rows), sh.join);
+                }
                 for (uint32_t d = 0; d < nbins; d++) {
                     if (cr[d].rn == 0 && cr[d].sn == 0) continue;  // no rows: every sink ignores it
                     const bool even = !learned && !(g0.flags & GROUP_PIVOT) && (d == 0 || alike(d, d - 1)) &&
                                       (d + 1 >= g0.ndig || alike(d, d + 1));
-                    emit_child(gi, cr[d], r0, s0, even);
+                    emit_child(gi, cr[d], r0, s0, even, fill);
                     r0 += cr[d].rn;
                     s0 += cr[d].sn;
                 }
