@@ -309,8 +309,9 @@ struct Seg {
     uint64_t lo, hi;          // ordinal range present (lo > hi: no rows)
     uint32_t buf;
     uint32_t kb = 0;          // key bytes of the rows in `buf`
-    // Narrowed keys (kb 4 of an int64 input) hold ord - win; win is the
-    // original ordinal of their 2^32-aligned window. ~0: keys are not narrowed.
+    // Narrowed keys (kb 4 of an int64 input) hold ord - win; win is the original
+    // ordinal that they count from: the start of a 2^32-ordinal window of their
+    // group, or of their digit (groups with a multiplier). ~0: not narrowed.
     uint64_t win = ~0ull;
     // Row i's key sits at index i + koff of its side's key array. Narrowed
     // keys use koff = first row of the bucket that narrowed them, which keeps

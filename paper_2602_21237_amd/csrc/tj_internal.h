@@ -268,7 +268,8 @@ hipError_t launch_read_ords(const KeyRef* refs, uint32_t n, uint64_t* out, hipSt
 hipError_t launch_probe_step(int key_bytes, const void* a, uint64_t na, const void* b, uint64_t nb,
                              uint64_t step, uint64_t* minmax, hipStream_t st);
 // range_miss: set to nonzero when a GROUP_CHECK_RANGE group has a row outside its digit range.
-// root: the groups' digit is planned from the probe's partial extremes (see RootArgs).
+// root: the groups' digit is planned from the probe's partial extremes (see RootArgs); where these are one
+// key, nothing is counted and range_miss is set.
 hipError_t launch_hist(int key_bytes, const ChunkDesc* chunks, uint32_t nchunks,
                        GroupDesc* groups, BufSet bufs, uint32_t* hist,
                        uint64_t* gmin, uint64_t* gmax, uint32_t* range_miss, const RootArgs* root, hipStream_t st);

@@ -644,9 +644,10 @@ __global__ __launch_bounds__(NT) void k_hist(const ChunkDesc* __restrict__ chunk
     }
     if (LEARNED) rmi_to_lds<NT>((tj_rmi_t*)lm_raw, model);
     lds_barrier();
-    // GROUP_CHECK_RANGE: the digit range came from a sample; a row outside
-    // [base, base + nbins << shift) would take a wrong digit, so it is flagged
-    // (the planner then probes the exact range and repeats the pass).
+    // GROUP_CHECK_RANGE: the digit range came from a sample; a row below base, or
+    // whose digit is not below ndig (by shift, and multiplier if there is one),
+    // would take a wrong digit, so it is flagged (the planner then probes the exact
+    // range and repeats the pass).
     const bool check = !LEARNED && (g.flags & GROUP_CHECK_RANGE) != 0;
     const bool pivot = (g.flags & GROUP_PIVOT) != 0;
     bool miss = false;
@@ -1747,10 +1748,9 @@ hipError_t launch_expand(int32_t* dst, const int32_t* src, uint64_t n, uint64_t 
 // ---------------------------------------------------------------------------
 constexpr int LBINS = 256, LSTRIDE = LBINS + 1;
 // Block shape of a leaf of at most C rows, per key word. C = LEAF_CAP: 32-bit
-// keys use 512 threads x 16 rows (57 KB of LDS, two blocks per CU); 64-bit keys
-// 1024 threads x 8 rows (97 KB, one block of 16 waves per CU). The smaller
-// capacities are for inputs of one block, where nothing but the block's own
-// latency counts: 4 rows a thread.
+// keys use 512 threads x 16 rows (in k_leaf_sort_narrow 64 KiB of LDS, two blocks
+// per CU); 64-bit keys 1024 threads x 8 rows. The smaller capacities are for inputs
+// of one block, where nothing but the block's own latency counts: 4 rows a thread.
 // (A join block has 1024 threads x 8 rows with either key word: FULL.)
 template <typename KW, int C = LEAF_CAP, bool FULL = false> struct LeafShape {
     static constexpr int NT = C < LEAF_CAP ? C / 4 : sizeof(KW) == 4 && !FULL ? 512 : 1024;
@@ -1795,10 +1795,7 @@ struct LdsPad {
     }
     static constexpr uint32_t size(uint32_t n) { return n + (n / G) * S; }
 };
-// join blocks read their sorted items in blocked order (padded layout); the
-// sort blocks read them across lanes (plain layout)
-template <typename KW, int C = LEAF_CAP> using KeyLds = LdsPad<KW, LeafShape<KW, C>::KI, 1>;
-template <typename KW, int C = LEAF_CAP> using IdxLds = LdsPad<uint16_t, LeafShape<KW, C>::KI, 2>;
+// sort blocks read their sorted items across lanes: plain layout (for the join's, see JoinLds)
 template <typename KW, int C = LEAF_CAP> using KeyPlain = LdsPad<KW, LeafShape<KW, C>::KI, 0>;
 template <typename KW, int C = LEAF_CAP> using IdxPlain = LdsPad<uint16_t, LeafShape<KW, C>::KI, 0>;
 
@@ -2172,8 +2169,8 @@ __device__ __forceinline__ void leaf_sort_passes(char* pool, uint32_t n, uint64_
 }
 
 // The sort of one leaf. Each row is one word [key below its bin's bits | row] in
-// its bin of 2^13 (at most two rows a bin where keys are even), so that one
-// comparison of words decides the order (key, row) inside a bin whatever order
+// its bin of 2^13 (one to two rows a bin on average where keys are even), so that
+// one comparison of words decides the order (key, row) inside a bin whatever order
 // the bins were filled in. A row's key and row id stay with its thread, which
 // puts them in their places in LDS, from where they leave coalesced.
 // Bound by the memory traffic of its rows once two blocks share a CU: 2^29 rows
