@@ -42,6 +42,9 @@ serving: Poisson arrivals at 50, 200, 800 and 3200 requests/s of sorts and joins
 (per-side rows log-uniform in [10^3, 10^7]) against the serving loop with a
 32 GiB workspace budget, 8 slots against one at a time: P50/P99/P99.9 latency
 and tuples/s, every result compared with the same request run alone.
+
+The printed line holds the headline figures of these sections; their tables go
+to a file (--details).
 """
 from __future__ import annotations
 
@@ -59,6 +62,41 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 METRIC = "join input tuples/s + sort keys/s (%HBM peak); P50/P99 latency; learned vs radix"
+
+
+# sections of the record whose tables stay out of the printed line (see headline)
+DETAIL_SECTIONS = ("path_selection", "hbm_zipf", "learned_vs_radix", "composite_keys", "serving", "paper_shaped")
+
+
+def headline(line):
+    """The line to print: the record with each detail section cut down to its
+    headline figures, short enough (under 6 KB, from over 20) to stay whole where
+    only the end of a program's output is kept."""
+    out = {k: v for k, v in line.items() if k not in DETAIL_SECTIONS}
+    if "native_pinned" in out.get("cpu_baseline", {}):
+        out["cpu_baseline"] = {k: v for k, v in out["cpu_baseline"].items() if k != "native_pinned"}
+    ps = line.get("path_selection")
+    if ps:
+        out["path_selection"] = {k: ps[k]["ms"] for k in ("join", "sort")}
+        out["path_selection"]["crossover_rows"] = {k: v["rows_per_side"] if v else None
+                                                   for k, v in ps.get("crossover", {}).items()}
+    if "hbm_zipf" in line:
+        out["hbm_zipf"] = {k: {f: v[f] for f in ("sort_ms_p50", "join_ms_p50", "ms_p50") if f in v}
+                           for k, v in line["hbm_zipf"].items() if isinstance(v, dict)}
+    if "learned_vs_radix" in line:  # ms: radix, learned, automatic
+        out["learned_vs_radix"] = {d: {op: [r.get(m + "_ms") for m in ("radix", "learned", "auto")]
+                                       for op, r in ops.items() if isinstance(r, dict)}
+                                   for d, ops in line["learned_vs_radix"]["dists"].items()}
+    if "composite_keys" in line:
+        out["composite_keys"] = {k: {op: v[op]["ms"] for op in ("sort", "join")}
+                                 for k, v in line["composite_keys"].items() if isinstance(v, dict)}
+    if "serving" in line:  # P50, P99 ms, requests/s done
+        out["serving"] = {rate: {m: [v["p50_ms"], v["p99_ms"], v["requests_per_s"]] for m, v in modes.items()}
+                          for rate, modes in line["serving"]["rates"].items()}
+    if "paper_shaped" in line:  # P50, P99 ms
+        out["paper_shaped"] = {k: {op: [v[op]["p50_ms"], v[op]["p99_ms"]] for op in ("sort", "join")}
+                               for k, v in line["paper_shaped"].items() if isinstance(v, dict) and "sort" in v}
+    return out
 
 
 def log(msg):
@@ -847,6 +885,9 @@ def main():
     ap.add_argument("--copy-calibration", type=int, default=0, metavar="MIB",
                     help="before timing, copy MIB MiB device-to-device three times (a plain copy "
                          "of known size that scales the FETCH_SIZE / WRITE_SIZE counters)")
+    ap.add_argument("--details", default=os.path.join(ROOT, "bench_details.json"), metavar="PATH",
+                    help="file for the full record with every section's tables (the printed line holds their "
+                         "headline figures)")
     args = ap.parse_args()
 
     if args.gpus != 1 or int(os.environ.get("WORLD_SIZE", "1")) != 1:
@@ -1000,7 +1041,13 @@ def main():
             ps["oracle_sweep"] = lat["sweep"]
             ps["crossover"] = {"join": crossover(ps["sweep"], lat["sweep"], "join_ms"),
                                "sort": crossover(ps["sweep"], lat["sweep"], "sort_ms")}
-    print(json.dumps(line), flush=True)
+    try:
+        with open(args.details, "w") as f:
+            json.dump(line, f)
+            f.write("\n")
+    except OSError as e:
+        log("no details written: %s" % e)
+    print(json.dumps(headline(line)), flush=True)
 
 
 if __name__ == "__main__":
