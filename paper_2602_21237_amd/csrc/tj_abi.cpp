@@ -852,6 +852,7 @@ struct Exec {
                     g.flags = (g_debug_flags.load() & TJ_DEBUG_FORCE_REORDER) ? GROUP_FORCE_REORDER : 0u;
                     if (spec) g.flags |= GROUP_CHECK_RANGE;
                     if (plan[si].pivot) g.flags |= GROUP_PIVOT;
+                    if (plan[si].mul && s.hi - s.lo > 0xffffffffull) g.flags |= GROUP_DIGIT_WINDOWS;
                     g.src_koff = filter ? 0 : (side ? s.koff_s : s.koff_r);
                     // narrowed keys: at their rows' index in 4-byte key buffers, else
                     // inside the 8-byte footprint of the bucket that narrowed them
@@ -1121,8 +1122,9 @@ struct Exec {
                     // keys now hold (ord - g.base) mod 2^32 (see k_scatter), or count
                     // from the child's own first key
                     const uint64_t off = c.lo - g0.base;
-                    c.win = g0.base + (g0.mul ? digit_start((uint32_t)(((off >> g0.shift) * g0.mul) >> 32), g0.shift, g0.mul)
-                                              : off & ~0xffffffffull);
+                    const bool own = (g0.flags & GROUP_DIGIT_WINDOWS) != 0;
+                    c.win = g0.base + (own ? digit_start((uint32_t)(((off >> g0.shift) * g0.mul) >> 32), g0.shift, g0.mul)
+                                           : off & ~0xffffffffull);
                     c.lo -= c.win;
                     c.hi -= c.win;
                 }

@@ -51,12 +51,16 @@ constexpr uint32_t GROUP_FORCE_REORDER = 1u;
 // its 8-byte keys (its children still span more than 2^32 ordinals).
 constexpr uint32_t GROUP_WIDE = 2u;
 // GroupDesc::flags: the group's digit range comes from a sampled probe; the
-// histogram flags any row outside [base, base + (nbins << shift)).
+// histogram flags any row below base or whose digit is not below ndig.
 constexpr uint32_t GROUP_CHECK_RANGE = 4u;
 // The group splits three ways around one key instead of by a radix digit:
 // digit 0, 1, 2 for ord < base, ord == base, ord > base (bits = 2, shift 0;
 // keys keep their width).
 constexpr uint32_t GROUP_PIVOT = 8u;
+// A group with a multiplier that spans over 2^32 ordinals: keys that its pass
+// narrows count from their digit's first key. (Otherwise from the group's base,
+// so that neighbouring children can share a leaf.)
+constexpr uint32_t GROUP_DIGIT_WINDOWS = 16u;
 
 struct GroupDesc {
     uint64_t start;      // first row scanned in the source array

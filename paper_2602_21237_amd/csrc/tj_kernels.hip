@@ -931,7 +931,7 @@ __global__ __launch_bounds__(64) void k_batch_leaves(const GroupDesc* __restrict
         uint64_t clo = c.lo, chi = c.hi;
         win[j] = 0;
         if (a.narrowing && rows[j]) {
-            if (g0.mul) {  // each child has its own window, from the child's first key
+            if (g0.flags & GROUP_DIGIT_WINDOWS) {  // each child has its own window, from its first key
                 const uint64_t w0 = g0.base + digit_start(d, g0.shift, g0.mul);
                 win[j] = d;
                 clo -= w0;
@@ -1466,7 +1466,7 @@ __global__ __launch_bounds__(LN_NT) void k_scatter_lines(const ChunkDesc* __rest
         cur = (uint32_t)(cstart[g.child0 + t] + cbsum[(uint64_t)ch.cblock * NB + t] + hist[(uint64_t)blockIdx.x * NB + t]);
     if (t < nbins) s_first[t] = cur;
     if (NARROW && t < D)
-        s_sub[t] = (uint32_t)(g.base + (g.mul ? digit_start(t, g.shift, g.mul) : 0));
+        s_sub[t] = (uint32_t)(g.base + (g.flags & GROUP_DIGIT_WINDOWS ? digit_start(t, g.shift, g.mul) : 0));
 
     K key[KI];
     int32_t rid[RIDS ? KI : 1], next_rid[RIDS ? KI : 1];
