@@ -39,6 +39,7 @@ namespace {
 constexpr uint64_t ALIGN = 256;
 constexpr int TABLE_TIERS = 9;
 constexpr uint64_t TARGET_CHUNKS = 2048;  // blocks per partition pass
+constexpr size_t MAX_WIDTH_TURNS = 16;        // changes of key width along a join's leaves before launches take any
 constexpr size_t DEVICE_BATCH_MIN_SEGS = 16;  // segments of a pass before leaves are batched on the device
 // learned partitioner defaults (tj_options_t)
 constexpr uint32_t LEARNED_BUCKETS = 512;        // buckets of the learned pass: one full-width digit
@@ -1867,6 +1868,11 @@ struct Exec {
             auto leaf_at = [&](size_t i) -> const LeafDesc& { return ord ? leaves[(*ord)[i].second] : leaves[i]; };
             auto cr0 = [](const CrossDesc& a, const CrossDesc& b) { return a.out < b.out; };
             if (!std::is_sorted(crosses.begin(), crosses.end(), cr0)) std::sort(crosses.begin(), crosses.end(), cr0);
+            // A launch takes one key width, or any where the widths alternate often:
+            // the blocks of one width are faster, but a launch and its wait cost 30 us.
+            size_t turns = 0;
+            for (size_t i = 1; i < leaves.size(); i++) turns += leaf_at(i).kb != leaf_at(i - 1).kb ? 1 : 0;
+            const bool any_width = turns > MAX_WIDTH_TURNS;
             uint64_t carry = base;
             size_t li = 0, ci = 0;
             std::vector<LeafDesc>& bl = hv.batch_leaves;
@@ -1876,6 +1882,7 @@ struct Exec {
                 bc.clear();
                 uint64_t pre = 0;  // single-key pairs of this batch so far
                 int bkb = 0;       // key width of the batch's leaves
+                bool mixed = false;
                 while (li < leaves.size() || ci < crosses.size()) {
                     const bool take_cross =
                         ci < crosses.size() && (li == leaves.size() || crosses[ci].out < leaf_at(li).out);
@@ -1889,7 +1896,8 @@ struct Exec {
                         bc.push_back(c);
                     } else {
                         if (bl.size() == caps.leaves) break;
-                        if (bkb != 0 && leaf_at(li).kb != bkb) break;  // one launch, one key width
+                        if (bkb != 0 && leaf_at(li).kb != bkb && !any_width) break;  // one launch, one key width
+                        mixed = mixed || (bkb != 0 && leaf_at(li).kb != bkb);
                         bkb = leaf_at(li).kb;
                         LeafDesc L = leaf_at(li++);
                         L.out = pre;
@@ -1904,18 +1912,18 @@ struct Exec {
                 TJ_CK(stage_join(bl.data(), nl, carry));
                 size_t leaf_timer = (size_t)-1;
                 if (nl) {
-                    uint64_t rows = 0;
+                    uint64_t bytes = 0;
                     bool wide = false;
                     for (const LeafDesc& L : bl) {
-                        rows += L.rn + L.sn;
+                        bytes += (L.rn + L.sn) * row_bytes(L.kb, true);
                         wide = wide || L.bits > 32;
                     }
                     leaf_timer = pending.size();
-                    TJ_CK(timed(F_LEAF_MAT, rows * row_bytes(bkb, true), [&] {
-                        return launch_leaf_join(bkb, wide, true, d_leaves, nl, bufs, d_status, d_ticket,
+                    TJ_CK(timed(F_LEAF_MAT, bytes, [&] {
+                        return launch_leaf_join(mixed ? 0 : bkb, wide, true, d_leaves, nl, bufs, d_status, d_ticket,
                                                 &fin->total, &fin->err, out_r, out_s, capacity, st);
                     }));
-                    stats.bytes_read += rows * row_bytes(bkb, true);
+                    stats.bytes_read += bytes;
                 }
                 if (nc) {
                     uint64_t t = 0, in_rows = 0;

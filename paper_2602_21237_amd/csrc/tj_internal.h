@@ -100,7 +100,7 @@ struct LeafDesc {
                          // the single-key units before this block in key order
     uint32_t rn, sn;     // rows per side (sn = 0 for the sort)
     uint16_t bits;       // significant bits of (ord - base) over the block's rows
-    uint16_t kb;         // key bytes of the rows in the buffer (host bookkeeping)
+    uint16_t kb;         // key bytes of the rows in the buffer
     uint16_t buf;        // buffer holding the rows
     uint16_t flags;      // LEAF_* bits
 };
@@ -312,6 +312,7 @@ hipError_t launch_batch_leaves(const GroupDesc* groups, const ChildRec* crec, co
                                hipStream_t st);
 hipError_t launch_leaf_sort(int key_bytes, bool wide, LeafDesc* leaves, uint32_t n,
                             BufSet bufs, void* out_k, int32_t* out_r, hipStream_t st);
+// key_bytes 0 (materialise only): leaves of either width, as each says (LeafDesc::kb).
 // Count mode adds the leaves' pair counts to *total. Materialise mode needs
 // status[0] = inclusive-flagged carry-in offset, status[1..n] = 0, *ticket = 0;
 // afterwards *total holds the inclusive pair total (carry-in included) and *err

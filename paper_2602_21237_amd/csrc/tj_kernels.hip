@@ -2629,6 +2629,9 @@ template <typename KW, bool MAT, int C> struct JoinLds {
     static constexpr int BYTES = ((MOST > SORTED ? MOST : SORTED) + 15) / 16 * 16;
 };
 
+// The argument `bits` of join_sorted, from a block of either key width (ANY) whose keys have 4 bytes.
+constexpr int ANY_FOUR = 256;
+
 template <typename K> struct JoinIn {
     const K *rk, *sk;
     const int32_t *rr, *sr;
@@ -2637,7 +2640,7 @@ template <typename K> struct JoinIn {
 // The join of one block by sorting R's and S's rows together (see above), for
 // leaves that the binned way does not take. Not inlined: its registers would
 // weigh on the other way's.
-template <typename K, typename KW, bool MAT, bool SELF, int C>
+template <typename K, typename KW, bool MAT, bool SELF, int C, bool ANY>
 static __device__ __noinline__ void join_sorted(__attribute__((address_space(3))) char* pool3, uint32_t rn, uint32_t n,
                                                 uint64_t leaf_base, uint64_t out, int bits, bool reorder, uint32_t li,
                                                 const K* rk_, const K* sk_, const int32_t* rr_, const int32_t* sr_,
@@ -2657,6 +2660,8 @@ static __device__ __noinline__ void join_sorted(__attribute__((address_space(3))
     const GK *const rk = (const GK*)rk_, *const sk = (const GK*)sk_;
     const G32 *const rr = (const G32*)rr_, *const sr = (const G32*)sr_;
     G32 *const out_r = (G32*)out_r_, *const out_s = (G32*)out_s_;
+    const bool four = ANY && bits >= ANY_FOUR;
+    if (ANY) bits &= ANY_FOUR - 1;
     KW* const lds_key_raw = (KW*)pool;
     uint16_t* const lds_idx_raw = (uint16_t*)(pool + JL::KEYS);
     const KA lds_key{lds_key_raw};
@@ -2683,8 +2688,10 @@ static __device__ __noinline__ void join_sorted(__attribute__((address_space(3))
             for (int r = 0; r < KI; r++) {
                 const uint32_t q = (w * KI + r) * 64 + l;
                 const uint32_t qc = q < n ? q : n - 1;  // every lane loads a real row
-                const K v = qc < rn ? rk[qc] : sk[qc - rn];
-                if (q < n) key[r] = (KW)(ord_of(v) - leaf_base);
+                uint64_t o;
+                if (ANY && four) o = ord_of((int32_t)(qc < rn ? ((const G32*)rk)[qc] : ((const G32*)sk)[qc - rn]));
+                else o = ord_of((K)(qc < rn ? rk[qc] : sk[qc - rn]));
+                if (q < n) key[r] = (KW)(o - leaf_base);
             }
         }
     };
@@ -2925,7 +2932,12 @@ __device__ __forceinline__ void write_runs(const uint32_t* run, uint32_t all, ui
 // SELF (a whole input that fits one block): the leaf is `self`, whose key
 // range the block finds itself; its pairs start at 0 and their number is
 // stored to *total (in either mode). One launch then serves the whole call.
-template <typename K, typename KW, bool MAT, bool SELF = false, int C = LEAF_CAP>
+// ANY (K of 8 bytes): leaves of either key width, which each leaf tells. A level
+// whose segments narrow their keys only in part leaves widths that alternate in
+// key order, and a launch (and a wait) for every stretch of one width: 2^24 x 2^26
+// rows of exponential keys, 12.0 ms in 258 launches and 4.7 in one; 2^26 x 2^28 of
+// normal ones took 350 ms in 3663.
+template <typename K, typename KW, bool MAT, bool SELF = false, int C = LEAF_CAP, bool ANY = false>
 __global__ __launch_bounds__((JoinLds<KW, MAT, C>::SH::NT))
 __attribute__((amdgpu_waves_per_eu(sizeof(KW) == 4 && !SELF ? 8 : 4))) void k_leaf_join(const LeafDesc* __restrict__ leaves,
                                                             BufSet bufs, uint64_t* __restrict__ status,
@@ -2955,8 +2967,14 @@ __attribute__((amdgpu_waves_per_eu(sizeof(KW) == 4 && !SELF ? 8 : 4))) void k_le
     if constexpr (SELF) L = self;
     else L = leaves[li];
     JoinIn<K> in;
+    bool four = false;
+    if constexpr (ANY) four = uniform((uint32_t)L.kb) == 4;
     in.rk = (const K*)bufs.key[L.buf][0] + L.kr0;
     in.sk = (const K*)bufs.key[L.buf][1] + L.ks0;
+    if (ANY && four) {
+        in.rk = (const K*)((const int32_t*)bufs.key[L.buf][0] + L.kr0);
+        in.sk = (const K*)((const int32_t*)bufs.key[L.buf][1] + L.ks0);
+    }
     in.rr = MAT ? bufs.rid[L.buf][0] + L.r0 : nullptr;
     in.sr = MAT ? bufs.rid[L.buf][1] + L.s0 : nullptr;
     // the table: the side of fewer rows (R, if alike)
@@ -2986,13 +3004,20 @@ __attribute__((amdgpu_waves_per_eu(sizeof(KW) == 4 && !SELF ? 8 : 4))) void k_le
     constexpr int TI = C / 2 / NT;
     const uint32_t tlast = tn ? tn - 1 : 0u, plast = pn ? pn - 1 : 0u;
     K tv[TI];
-#pragma unroll
-    for (int i = 0; i < TI; i++) tv[i] = ld_now(tk, min(t + i * NT, tlast));
     KW key[KI];
     {
         K v[KI];
+        if (ANY && four) {  // as keys of K with the same ordinals
 #pragma unroll
-        for (int r = 0; r < KI; r++) v[r] = ld_now(pk, min(row(r), plast));
+            for (int i = 0; i < TI; i++) tv[i] = key_of<K>(ord_of(ld_now((const int32_t*)tk, min(t + i * NT, tlast))));
+#pragma unroll
+            for (int r = 0; r < KI; r++) v[r] = key_of<K>(ord_of(ld_now((const int32_t*)pk, min(row(r), plast))));
+        } else {
+#pragma unroll
+            for (int i = 0; i < TI; i++) tv[i] = ld_now(tk, min(t + i * NT, tlast));
+#pragma unroll
+            for (int r = 0; r < KI; r++) v[r] = ld_now(pk, min(row(r), plast));
+        }
         if constexpr (SELF) {
             uint64_t lo = ~0ull, hi = 0;
 #pragma unroll
@@ -3064,8 +3089,8 @@ __attribute__((amdgpu_waves_per_eu(sizeof(KW) == 4 && !SELF ? 8 : 4))) void k_le
         }
     }
     if (!fast) {
-        join_sorted<K, KW, MAT, SELF, C>((__attribute__((address_space(3))) char*)pool, L.rn, L.rn + L.sn, L.base, L.out,
-                                         (int)L.bits, L.flags & LEAF_FORCE_REORDER, li, in.rk, in.sk, in.rr, in.sr,
+        join_sorted<K, KW, MAT, SELF, C, ANY>((__attribute__((address_space(3))) char*)pool, L.rn, L.rn + L.sn, L.base, L.out,
+                                         (int)L.bits + (four ? ANY_FOUR : 0), L.flags & LEAF_FORCE_REORDER, li, in.rk, in.sk, in.rr, in.sr,
                                          status, total, err, out_r, out_s, capacity);
         return;
     }
@@ -3355,7 +3380,11 @@ hipError_t launch_leaf_join(int key_bytes, bool wide, bool materialize, const Le
 #define TJ_LJ(K, KW, M)                                                                              \
     hipLaunchKernelGGL((k_leaf_join<K, KW, M>), grid, block, 0, st, leaves, bufs, status, ticket,    \
                        total, err, out_r, out_s, capacity, LeafDesc{})
-    if (key_bytes == 4) {
+    if (key_bytes == 0) {
+        if (!materialize) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((k_leaf_join<int64_t, uint64_t, true, false, LEAF_CAP, true>), grid, block, 0, st, leaves, bufs,
+                           status, ticket, total, err, out_r, out_s, capacity, LeafDesc{});
+    } else if (key_bytes == 4) {
         if (wide) { if (materialize) TJ_LJ(int32_t, uint64_t, true); else TJ_LJ(int32_t, uint64_t, false); }
         else      { if (materialize) TJ_LJ(int32_t, uint32_t, true); else TJ_LJ(int32_t, uint32_t, false); }
     } else {
