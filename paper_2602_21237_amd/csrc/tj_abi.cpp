@@ -204,7 +204,11 @@ const uint64_t kMaxRows = (1ull << 31) - 1;
 // Passes whose scatter writes whole lines (k_scatter_lines) cut a segment's key
 // range into equal parts. Levels of at least LINES_MIN_ROWS rows take them,
 // when at least 3/4 of the rows are in segments of LINES_SEG_ROWS or more that
-// two levels of LN_D digits bring down to leaves.
+// two levels of LN_D digits bring down to leaves. A segment of few values, which
+// one radix digit (up to 9 bits) takes apart, moves its rows once either way or
+// twice with lines: sorts of n int64 rows of D dense keys, runs against lines
+// (us), n 60M: D 64 690 and 840, D 200 740 and 666, D 400 800 and 1760 (lines of
+// 8 bits and a second pass); so such segments take lines for 7 and 8 bits only.
 // leaf_fill: rows a leaf bucket is planned for at most, where keys are even, and
 // for this rule: 5 standard deviations below LEAF_CAP for single rows (sd 87),
 // less for a join, whose rows come in groups of one key. How far they spread
@@ -212,8 +216,9 @@ const uint64_t kMaxRows = (1ull << 31) - 1;
 // bucket of twice the density still fits.
 constexpr uint64_t LINES_MIN_ROWS = 16ull << 20, LINES_SEG_ROWS = 1ull << 18;
 inline uint32_t leaf_fill(bool join) { return join ? 7300 : 7600; }
-inline bool lines_seg(uint64_t rows, bool even, uint64_t fill)
+inline bool lines_seg(uint64_t rows, uint64_t span, bool even, uint64_t fill)
 {
+    if (span < 64 || (span >= 256 && span < 512)) return false;
     if (rows < LINES_SEG_ROWS || rows > LN_D * LN_D * fill) return false;
     const uint64_t fit = LN_D * fill;  // rows that one level brings down to leaves
     return rows <= (even ? fit : fit / 2) || rows > 2 * fit;
@@ -715,7 +720,7 @@ struct Exec {
         uint64_t total_rows = 0, line_rows = 0;
         for (const Seg& s : segs) {
             total_rows += s.rn + s.sn;
-            if (lines_seg(s.rn + s.sn, s.even, leaf_fill(sh.join))) line_rows += s.rn + s.sn;
+            if (lines_seg(s.rn + s.sn, s.hi - s.lo, s.even, leaf_fill(sh.join))) line_rows += s.rn + s.sn;
         }
         const bool lines = !filter && !learned && !root && write_keys && total_rows >= LINES_MIN_ROWS &&
                            line_rows >= total_rows / 4 * 3;
@@ -2288,8 +2293,17 @@ int sampled_range(Exec& x, const void* a, uint64_t na, const void* b, uint64_t n
     lo = mm[0];
     if (na + nb >= LINES_MIN_ROWS && hi > lo) {
         // digits of any width (plan_lines): both ends move out to multiples of
-        // a 64th to a 128th of the range
-        const uint32_t g = nbits64(hi - lo) > 7 ? nbits64(hi - lo) - 7 : 0;
+        // a 64th to a 128th of the range; up to 512 values, which one radix
+        // digit tells apart (lines_seg), to as many as that digit has
+        const uint32_t bits = nbits64(hi - lo);
+        if (bits <= 9) {
+            const uint64_t last = x.sh.kb == 4 ? 0xffffffffull : ~0ull, spare = (1ull << bits) - 1 - (hi - lo);
+            const uint64_t below = spare / 2 < lo ? spare / 2 : lo, above = spare - below;
+            lo -= below;
+            hi = above < last - hi ? hi + above : last;
+            return TJ_OK;
+        }
+        const uint32_t g = bits - 7;
         lo &= ~((1ull << g) - 1);
         hi |= (1ull << g) - 1;
         return TJ_OK;
