@@ -387,11 +387,12 @@ hipError_t launch_publish(uint64_t* dst, const uint64_t* src, uint32_t n, hipStr
 // ---------------------------------------------------------------------------
 // range probe: minimum and maximum ordinal over one or two key columns
 // ---------------------------------------------------------------------------
-// step > 1: the minimum and maximum of every step-th element only (a sample).
+// step_a, step_b > 1: the minimum and maximum of every step-th element of the
+// column only (a sample), and of its last.
 template <typename K>
 __global__ __launch_bounds__(256) void k_probe(const K* __restrict__ a, uint64_t na,
                                                const K* __restrict__ b, uint64_t nb,
-                                               uint64_t* __restrict__ minmax, uint64_t step)
+                                               uint64_t* __restrict__ minmax, uint64_t step_a, uint64_t step_b)
 {
     __shared__ uint64_t smin[4], smax[4];
     uint64_t mn = ~0ull, mx = 0;
@@ -400,11 +401,11 @@ __global__ __launch_bounds__(256) void k_probe(const K* __restrict__ a, uint64_t
     // U loads in flight per thread; a clamped index re-reads a real element,
     // which leaves the minimum and maximum unchanged.
     constexpr int U = 8;
-    const uint64_t sa = (na + step - 1) / step, sb = (nb + step - 1) / step;  // sampled elements
+    const uint64_t sa = (na + step_a - 1) / step_a, sb = (nb + step_b - 1) / step_b;  // sampled elements
     for (uint64_t i0 = t0; i0 < sa; i0 += stride * U) {
         K v[U];
 #pragma unroll
-        for (int u = 0; u < U; u++) v[u] = ld_clamp(a, (i0 + u * stride) * step, na);
+        for (int u = 0; u < U; u++) v[u] = ld_clamp(a, (i0 + u * stride) * step_a, na);
 #pragma unroll
         for (int u = 0; u < U; u++) {
             const uint64_t o = ord_of(v[u]);
@@ -415,7 +416,7 @@ __global__ __launch_bounds__(256) void k_probe(const K* __restrict__ a, uint64_t
     for (uint64_t i0 = t0; i0 < sb; i0 += stride * U) {
         K v[U];
 #pragma unroll
-        for (int u = 0; u < U; u++) v[u] = ld_clamp(b, (i0 + u * stride) * step, nb);
+        for (int u = 0; u < U; u++) v[u] = ld_clamp(b, (i0 + u * stride) * step_b, nb);
 #pragma unroll
         for (int u = 0; u < U; u++) {
             const uint64_t o = ord_of(v[u]);
@@ -441,30 +442,31 @@ __global__ __launch_bounds__(256) void k_probe(const K* __restrict__ a, uint64_t
 }
 
 hipError_t launch_probe_step(int key_bytes, const void* a, uint64_t na, const void* b, uint64_t nb,
-                             uint64_t step, uint64_t* minmax, hipStream_t st)
+                             uint64_t step_a, uint64_t step_b, uint64_t* minmax, hipStream_t st)
 {
     hipError_t e = launch_fill_u64(minmax, 1, ~0ull, st);
     if (e != hipSuccess) return e;
     e = launch_fill_u64(minmax + 1, 1, 0ull, st);
     if (e != hipSuccess) return e;
-    if (step < 1) step = 1;
-    const uint64_t n = ((na > nb ? na : nb) + step - 1) / step;
+    if (step_a < 1) step_a = 1;
+    if (step_b < 1) step_b = 1;
+    const uint64_t ma = (na + step_a - 1) / step_a, mb = (nb + step_b - 1) / step_b, n = ma > mb ? ma : mb;
     uint64_t blocks = (n + 256 * 16 - 1) / (256 * 16);
     if (blocks < 1) blocks = 1;
     if (blocks > 8192) blocks = 8192;
     if (key_bytes == 4)
         hipLaunchKernelGGL(k_probe<int32_t>, dim3((uint32_t)blocks), dim3(256), 0, st,
-                           (const int32_t*)a, na, (const int32_t*)b, nb, minmax, step);
+                           (const int32_t*)a, na, (const int32_t*)b, nb, minmax, step_a, step_b);
     else
         hipLaunchKernelGGL(k_probe<int64_t>, dim3((uint32_t)blocks), dim3(256), 0, st,
-                           (const int64_t*)a, na, (const int64_t*)b, nb, minmax, step);
+                           (const int64_t*)a, na, (const int64_t*)b, nb, minmax, step_a, step_b);
     return hipGetLastError();
 }
 
 hipError_t launch_probe(int key_bytes, const void* a, uint64_t na, const void* b, uint64_t nb,
                         uint64_t* minmax, hipStream_t st)
 {
-    return launch_probe_step(key_bytes, a, na, b, nb, 1, minmax, st);
+    return launch_probe_step(key_bytes, a, na, b, nb, 1, 1, minmax, st);
 }
 
 // The probe of a call whose first pass plans its digit on the device: each
