@@ -555,6 +555,7 @@ struct Exec {
     bool learned_pass = false;      // the next partition pass is the learned one
     bool auto_probe = false;        // the next pass may hand over to the learned partitioner
     bool spec_range = false;        // the next pass's digit range comes from a sampled probe
+    uint64_t exact_lo = 0, exact_hi = 0;  // (after TJ_RANGE_MISS) the range of all keys
     bool root_probe = false;        // the next pass probes its key range and plans its digit on the device
 
     // data buffer capacities (rows per side) when the buffers live in the workspace
@@ -688,6 +689,20 @@ struct Exec {
         const uint64_t ub = sizeof(CrossDesc) > sizeof(CopyDesc) ? sizeof(CrossDesc) : sizeof(CopyDesc);
         d_units = take((uint64_t)caps.units * ub);
         return p <= end ? TJ_OK : TJ_E_WORKSPACE;
+    }
+
+    // The range of all keys from the records of the first pass's children: its
+    // histogram has seen every row, if in a wrong digit, so a call whose sampled
+    // range was too narrow need not read the keys once more for it.
+    void exact_range(const ChildRec* rec, uint32_t n)
+    {
+        static_assert(DEVICE_BATCH_MIN_SEGS > 1, "the records of a first pass are read back");
+        exact_lo = ~0ull;
+        exact_hi = 0;
+        for (uint32_t i = 0; i < n; i++) {
+            exact_lo = std::min(exact_lo, rec[i].lo);
+            exact_hi = std::max(exact_hi, rec[i].hi);
+        }
     }
 
     // ---- one partition pass over a list of segments that live in `src` ----
@@ -1042,6 +1057,7 @@ struct Exec {
                 auto_probe = false;
                 if (spec && hdr->miss) {
                     stats.passes--;
+                    exact_range(hrec, nrec);
                     return TJ_RANGE_MISS;
                 }
                 uint64_t rows = 0, largest = 0;
@@ -1070,8 +1086,9 @@ struct Exec {
             if (ready) TJ_CK(hipEventSynchronize(ready));
             if (spec && hdr->miss) {
                 // a row outside the sampled digit range: nothing moved, the
-                // caller probes the exact range and starts again
+                // caller starts again with the exact range
                 stats.passes--;
+                exact_range(hrec, nrec);
                 return TJ_RANGE_MISS;
             }
             if (root && hdr->lo == hdr->hi) {
@@ -2568,7 +2585,8 @@ static int sort_body(int key_type, const void* keys_in, const int32_t* rids_in, 
         x.spec_range = spec;
         int rc = learned ? x.process_range(0, ~0ull, n, 0, false, 0) : x.process_range(lo, hi, n, 0, false, 0);
         if (rc == TJ_RANGE_MISS) {
-            TJ_RET(probe(x, keys_in, n, nullptr, 0, lo, hi));
+            lo = x.exact_lo;
+            hi = x.exact_hi;
             spec = false;
             rc = x.process_range(lo, hi, n, 0, false, 0);
         }
@@ -2723,7 +2741,8 @@ static int join_body(int key_type, const void* r_keys, const int32_t* r_rids, ui
         x.spec_range = spec;
         int rc = learned ? x.process_range(0, ~0ull, n_r, n_s, false, 0) : x.process_range(lo, hi, n_r, n_s, false, 0);
         if (rc == TJ_RANGE_MISS) {
-            TJ_RET(probe(x, r_keys, n_r, s_keys, n_s, lo, hi));
+            lo = x.exact_lo;
+            hi = x.exact_hi;
             spec = false;
             rc = x.process_range(lo, hi, n_r, n_s, false, 0);
         }

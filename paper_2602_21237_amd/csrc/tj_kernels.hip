@@ -648,7 +648,7 @@ __global__ __launch_bounds__(NT) void k_hist(const ChunkDesc* __restrict__ chunk
     lds_barrier();
     // GROUP_CHECK_RANGE: the digit range came from a sample; a row below base, or
     // whose digit is not below ndig (by shift, and multiplier if there is one),
-    // would take a wrong digit, so it is flagged (the planner then probes the exact
+    // would take a wrong digit, so it is flagged (the planner then takes the exact
     // range and repeats the pass).
     const bool check = !LEARNED && (g.flags & GROUP_CHECK_RANGE) != 0;
     const bool pivot = (g.flags & GROUP_PIVOT) != 0;
