@@ -209,6 +209,8 @@ const uint64_t kMaxRows = (1ull << 31) - 1;
 // twice with lines: sorts of n int64 rows of D dense keys, runs against lines
 // (us), n 60M: D 64 690 and 840, D 200 740 and 666, D 400 800 and 1760 (lines of
 // 8 bits and a second pass); so such segments take lines for 7 and 8 bits only.
+// (values: the span, or its strides where the sample of a first pass has one;
+// 500 keys 2^20 apart, 18M int32 rows: 333 us and 567.)
 // leaf_fill: rows a leaf bucket is planned for at most, where keys are even, and
 // for this rule: 5 standard deviations below LEAF_CAP for single rows (sd 87),
 // less for a join, whose rows come in groups of one key. How far they spread
@@ -216,9 +218,9 @@ const uint64_t kMaxRows = (1ull << 31) - 1;
 // bucket of twice the density still fits.
 constexpr uint64_t LINES_MIN_ROWS = 16ull << 20, LINES_SEG_ROWS = 1ull << 18;
 inline uint32_t leaf_fill(bool join) { return join ? 7300 : 7600; }
-inline bool lines_seg(uint64_t rows, uint64_t span, bool even, uint64_t fill)
+inline bool lines_seg(uint64_t rows, uint64_t values, bool even, uint64_t fill)
 {
-    if (span < 64 || (span >= 256 && span < 512)) return false;
+    if (values < 64 || (values >= 256 && values < 512)) return false;
     if (rows < LINES_SEG_ROWS || rows > LN_D * LN_D * fill) return false;
     const uint64_t fit = LN_D * fill;  // rows that one level brings down to leaves
     return rows <= (even ? fit : fit / 2) || rows > 2 * fit;
@@ -547,7 +549,7 @@ struct Exec {
     uint64_t* d_status = nullptr;  // caps.leaves + 1 look-back words
     ChildRec* d_crec = nullptr;     // caps.children folded child records
     uint32_t* d_segcount = nullptr; // caps.groups leaf counts (device batching)
-    // scalars in the probe block: [0..1] min/max, [2] pair total, [3] ticket (low) + error (high),
+    // scalars in the probe block: [0..1] min/max, [2] pair total (and see sampled_range), [3] ticket (low) + error (high),
     // [4..6] device batching summary (leaves, rows, flags)
     void* d_units = nullptr;
     tj_rmi_t* d_model = nullptr;    // learned bucket function (when trained)
@@ -555,6 +557,7 @@ struct Exec {
     bool learned_pass = false;      // the next partition pass is the learned one
     bool auto_probe = false;        // the next pass may hand over to the learned partitioner
     bool spec_range = false;        // the next pass's digit range comes from a sampled probe
+    uint32_t spec_stride = 0;       // (log2) few keys, this far apart, by that sample
     uint64_t exact_lo = 0, exact_hi = 0;  // (after TJ_RANGE_MISS) the range of all keys
     bool root_probe = false;        // the next pass probes its key range and plans its digit on the device
 
@@ -719,6 +722,7 @@ struct Exec {
         learned_pass = false;
         const bool spec = spec_range && !filter && !learned;
         spec_range = false;
+        const uint32_t stride = spec ? spec_stride : 0;
         const bool root = root_probe && !filter && !learned && segs.size() == 1;
         root_probe = false;
         // per segment digit choice
@@ -735,7 +739,7 @@ struct Exec {
         uint64_t total_rows = 0, line_rows = 0;
         for (const Seg& s : segs) {
             total_rows += s.rn + s.sn;
-            if (lines_seg(s.rn + s.sn, s.hi - s.lo, s.even, leaf_fill(sh.join))) line_rows += s.rn + s.sn;
+            if (lines_seg(s.rn + s.sn, (s.hi - s.lo) >> stride, s.even, leaf_fill(sh.join))) line_rows += s.rn + s.sn;
         }
         const bool lines = !filter && !learned && !root && write_keys && total_rows >= LINES_MIN_ROWS &&
                            line_rows >= total_rows / 4 * 3;
@@ -2296,7 +2300,7 @@ int probe(Exec& x, const void* a, uint64_t na, const void* b, uint64_t nb, uint6
 // histogram checks every row against the range (GROUP_CHECK_RANGE).
 int sampled_range(Exec& x, const void* a, uint64_t na, const void* b, uint64_t nb, uint64_t& lo, uint64_t& hi)
 {
-    uint64_t* mm = (uint64_t*)pinned_down(16);
+    uint64_t* mm = (uint64_t*)pinned_down(24);
     if (!mm) return TJ_E_HIP;
     // A side of few rows has as many of them read as a large one: 1/4093 of
     // 4*10^5 evenly spread keys, 100 of them, span too little of their range
@@ -2306,25 +2310,30 @@ int sampled_range(Exec& x, const void* a, uint64_t na, const void* b, uint64_t n
     const uint64_t step_a = step_of(na), step_b = step_of(nb);
     const uint64_t sampled = (na + step_a - 1) / step_a + (nb + step_b - 1) / step_b;
     TJ_CK(x.timed(F_PROBE, sampled * (uint64_t)x.sh.kb, [&] {
-        return launch_probe_step(x.sh.kb, a, na, b, nb, step_a, step_b, x.d_probe, x.st);
+        return launch_probe_step(x.sh.kb, a, na, b, nb, step_a, step_b, x.d_probe, true, x.st);
     }));
-    TJ_CK(hipMemcpyAsync(mm, x.d_probe, 16, hipMemcpyDeviceToHost, x.st));
+    TJ_CK(hipMemcpyAsync(mm, x.d_probe, 24, hipMemcpyDeviceToHost, x.st));
     TJ_CK(hipStreamSynchronize(x.st));
     x.stats.bytes_read += sampled * (uint64_t)x.sh.kb;
     hi = mm[1];
     lo = mm[0];
     if (na + nb >= LINES_MIN_ROWS && hi > lo) {
         // digits of any width (plan_lines): both ends move out to multiples of
-        // a 64th to a 128th of the range; up to 512 values, which one radix
-        // digit tells apart (lines_seg), to as many as that digit has
-        const uint32_t bits = nbits64(hi - lo);
-        if (bits <= 9) {
-            const uint64_t last = x.sh.kb == 4 ? 0xffffffffull : ~0ull, spare = (1ull << bits) - 1 - (hi - lo);
-            const uint64_t below = spare / 2 < lo ? spare / 2 : lo, above = spare - below;
-            lo -= below;
-            hi = above < last - hi ? hi + above : last;
+        // a 64th to a 128th of the range; up to 512 values (of a stride, if the
+        // sample's low bits are all alike), which one radix digit tells apart
+        // (lines_seg), to as many as that digit has
+        const uint32_t stride = (uint32_t)__builtin_ctzll(mm[2]);
+        const uint64_t values = (hi - lo) >> stride;
+        if (nbits64(values) <= 9) {
+            const uint64_t last = x.sh.kb == 4 ? 0xffffffffull : ~0ull;
+            const uint64_t spare = (1ull << nbits64(values)) - 1 - values;
+            const uint64_t below = std::min(spare / 2, lo >> stride);
+            lo -= below << stride;
+            hi += std::min(spare - below, (last - hi) >> stride) << stride;
+            x.spec_stride = stride;
             return TJ_OK;
         }
+        const uint32_t bits = nbits64(hi - lo);
         const uint32_t g = bits - 7;
         lo &= ~((1ull << g) - 1);
         hi |= (1ull << g) - 1;

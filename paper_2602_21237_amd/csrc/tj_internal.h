@@ -270,7 +270,7 @@ hipError_t launch_gather_step(int key_bytes, const void* a, uint64_t n, uint64_t
 // out[i] = ordinal of the key at refs[i] (one 4- or 8-byte key each).
 hipError_t launch_read_ords(const KeyRef* refs, uint32_t n, uint64_t* out, hipStream_t st);
 hipError_t launch_probe_step(int key_bytes, const void* a, uint64_t na, const void* b, uint64_t nb,
-                             uint64_t step_a, uint64_t step_b, uint64_t* minmax, hipStream_t st);
+                             uint64_t step_a, uint64_t step_b, uint64_t* minmax, bool vary, hipStream_t st);
 // range_miss: set to nonzero when a GROUP_CHECK_RANGE group has a row outside its digit range.
 // root: the groups' digit is planned from the probe's partial extremes (see RootArgs); where these are one
 // key, nothing is counted and range_miss is set.

@@ -156,6 +156,13 @@ __device__ __forceinline__ uint64_t wave_max64(uint64_t v)
     return v;
 }
 
+__device__ __forceinline__ uint64_t wave_or64(uint64_t v)
+{
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) v |= __shfl_xor(v, d, 64);
+    return v;
+}
+
 // Exclusive prefix of one value per thread over the block (NT threads);
 // `tmp` holds NT/64 words of LDS. Returns the prefix; *total gets the sum.
 template <int NT>
@@ -388,14 +395,17 @@ hipError_t launch_publish(uint64_t* dst, const uint64_t* src, uint32_t n, hipStr
 // range probe: minimum and maximum ordinal over one or two key columns
 // ---------------------------------------------------------------------------
 // step_a, step_b > 1: the minimum and maximum of every step-th element of the
-// column only (a sample), and of its last.
+// column only (a sample), and of its last. vary: minmax[2] receives the bits in
+// which any of them differs from a's first.
 template <typename K>
 __global__ __launch_bounds__(256) void k_probe(const K* __restrict__ a, uint64_t na,
                                                const K* __restrict__ b, uint64_t nb,
-                                               uint64_t* __restrict__ minmax, uint64_t step_a, uint64_t step_b)
+                                               uint64_t* __restrict__ minmax, uint64_t step_a, uint64_t step_b,
+                                               bool vary)
 {
     __shared__ uint64_t smin[4], smax[4];
-    uint64_t mn = ~0ull, mx = 0;
+    uint64_t mn = ~0ull, mx = 0, vr = 0;
+    const uint64_t first = vary && na ? ord_of(a[0]) : 0;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     const uint64_t t0 = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
     // U loads in flight per thread; a clamped index re-reads a real element,
@@ -411,6 +421,7 @@ __global__ __launch_bounds__(256) void k_probe(const K* __restrict__ a, uint64_t
             const uint64_t o = ord_of(v[u]);
             mn = o < mn ? o : mn;
             mx = o > mx ? o : mx;
+            vr |= o ^ first;
         }
     }
     for (uint64_t i0 = t0; i0 < sb; i0 += stride * U) {
@@ -422,7 +433,12 @@ __global__ __launch_bounds__(256) void k_probe(const K* __restrict__ a, uint64_t
             const uint64_t o = ord_of(v[u]);
             mn = o < mn ? o : mn;
             mx = o > mx ? o : mx;
+            vr |= o ^ first;
         }
+    }
+    if (vary) {
+        vr = wave_or64(vr);
+        if ((threadIdx.x & 63) == 0 && vr) atomicOr((unsigned long long*)&minmax[2], (unsigned long long)vr);
     }
     mn = wave_min64(mn);
     mx = wave_max64(mx);
@@ -442,11 +458,11 @@ __global__ __launch_bounds__(256) void k_probe(const K* __restrict__ a, uint64_t
 }
 
 hipError_t launch_probe_step(int key_bytes, const void* a, uint64_t na, const void* b, uint64_t nb,
-                             uint64_t step_a, uint64_t step_b, uint64_t* minmax, hipStream_t st)
+                             uint64_t step_a, uint64_t step_b, uint64_t* minmax, bool vary, hipStream_t st)
 {
     hipError_t e = launch_fill_u64(minmax, 1, ~0ull, st);
     if (e != hipSuccess) return e;
-    e = launch_fill_u64(minmax + 1, 1, 0ull, st);
+    e = launch_fill_u64(minmax + 1, vary ? 2 : 1, 0ull, st);
     if (e != hipSuccess) return e;
     if (step_a < 1) step_a = 1;
     if (step_b < 1) step_b = 1;
@@ -456,17 +472,17 @@ hipError_t launch_probe_step(int key_bytes, const void* a, uint64_t na, const vo
     if (blocks > 8192) blocks = 8192;
     if (key_bytes == 4)
         hipLaunchKernelGGL(k_probe<int32_t>, dim3((uint32_t)blocks), dim3(256), 0, st,
-                           (const int32_t*)a, na, (const int32_t*)b, nb, minmax, step_a, step_b);
+                           (const int32_t*)a, na, (const int32_t*)b, nb, minmax, step_a, step_b, vary);
     else
         hipLaunchKernelGGL(k_probe<int64_t>, dim3((uint32_t)blocks), dim3(256), 0, st,
-                           (const int64_t*)a, na, (const int64_t*)b, nb, minmax, step_a, step_b);
+                           (const int64_t*)a, na, (const int64_t*)b, nb, minmax, step_a, step_b, vary);
     return hipGetLastError();
 }
 
 hipError_t launch_probe(int key_bytes, const void* a, uint64_t na, const void* b, uint64_t nb,
                         uint64_t* minmax, hipStream_t st)
 {
-    return launch_probe_step(key_bytes, a, na, b, nb, 1, 1, minmax, st);
+    return launch_probe_step(key_bytes, a, na, b, nb, 1, 1, minmax, false, st);
 }
 
 // The probe of a call whose first pass plans its digit on the device: each
