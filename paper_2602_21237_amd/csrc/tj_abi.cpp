@@ -211,6 +211,9 @@ const uint64_t kMaxRows = (1ull << 31) - 1;
 // 8 bits and a second pass); so such segments take lines for 7 and 8 bits only.
 // (values: the span, or its strides where the sample of a first pass has one;
 // 500 keys 2^20 apart, 18M int32 rows: 333 us and 567.)
+// Nor does a crowded segment: its rows go to few digits again, or to the three
+// of a pivot, of which lines have no gain, and 512 digits narrow it down in
+// fewer levels than 320.
 // leaf_fill: rows a leaf bucket is planned for at most, where keys are even, and
 // for this rule: 5 standard deviations below LEAF_CAP for single rows (sd 87),
 // less for a join, whose rows come in groups of one key. How far they spread
@@ -739,7 +742,7 @@ struct Exec {
         uint64_t total_rows = 0, line_rows = 0;
         for (const Seg& s : segs) {
             total_rows += s.rn + s.sn;
-            if (lines_seg(s.rn + s.sn, (s.hi - s.lo) >> stride, s.even, leaf_fill(sh.join))) line_rows += s.rn + s.sn;
+            if (!s.skew && lines_seg(s.rn + s.sn, (s.hi - s.lo) >> stride, s.even, leaf_fill(sh.join))) line_rows += s.rn + s.sn;
         }
         const bool lines = !filter && !learned && !root && write_keys && total_rows >= LINES_MIN_ROWS &&
                            line_rows >= total_rows / 4 * 3;
