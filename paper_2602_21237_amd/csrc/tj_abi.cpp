@@ -257,7 +257,7 @@ inline void plan_lines(uint64_t span, uint64_t rows, bool even, uint32_t fill, u
         bits = std::max<uint32_t>(1, nbits64(ndig - 1));
         return;
     }
-    plan_digit(span, rows, false, shift, bits);
+    plan_digit(span, rows, 0, shift, bits);
     while (bits > 8) {
         shift++;
         bits--;
@@ -747,6 +747,20 @@ struct Exec {
         const bool lines = !filter && !learned && !root && write_keys && total_rows >= LINES_MIN_ROWS &&
                            line_rows >= total_rows / 4 * 3;
         if (filter) total_rows = sh.n_r + sh.n_s;
+        // Device batching pays where the children are many: one wave per
+        // segment batches them (tens of microseconds for a level), while the
+        // host needs about 5 ns per child. Children too large for a leaf are
+        // listed for the host, which plans only those.
+        if (segs.size() < DEVICE_BATCH_MIN_SEGS || learned) dev_ok = false;
+        bool windowed = false;  // rows packed into a workspace window
+        for (const Seg& sg : segs) windowed = windowed || sg.wdisp || sg.wdisp_s;
+        if (windowed) dev_ok = false;  // device leaves: one buffer mapping
+        // (windows are planned one after another by the host, and their buckets
+        // are not the crowded ones: sixty of 512 digits took it 170 us a window,
+        // as long as the window's kernels)
+        const uint32_t least = segs.size() > FEW_SEGS ? 0u
+                               : windowed             ? (uint32_t)(FEW_CHILDREN / std::max<size_t>(1, segs.size()))
+                                                      : FULL_DIGIT;
         bool all_narrow = true;  // (lines) every segment of 8-byte keys can narrow them
         for (size_t i = 0; i < segs.size(); i++) {
             const Seg& s = segs[i];
@@ -767,8 +781,8 @@ struct Exec {
                 all_narrow = all_narrow && pl.kb_out == 4;
                 continue;
             }
-            plan_digit(s.hi - s.lo, s.rn + s.sn, segs.size() <= FEW_SEGS, plan[i].shift, plan[i].bits);
-            if (filter && narrow_ranges) plan_digit(s.hi - s.lo, SMALL_SEG_ROWS, true, plan[i].shift, plan[i].bits);
+            plan_digit(s.hi - s.lo, s.rn + s.sn, least, plan[i].shift, plan[i].bits);
+            if (filter && narrow_ranges) plan_digit(s.hi - s.lo, SMALL_SEG_ROWS, FULL_DIGIT, plan[i].shift, plan[i].bits);
             // join keys are narrowed to 4 bytes once every child spans at most
             // 2^32 ordinals; the sort writes its keys out and never narrows
             plan[i].kb_out = sh.join && write_keys && s.kb == 8 && plan[i].shift <= 32 ? 4u : s.kb;
@@ -787,13 +801,6 @@ struct Exec {
         // (one written key width a launch, in key order)
         if (lines && !all_narrow)
             for (size_t i = 0; i < segs.size(); i++) plan[i].kb_out = segs[i].kb;
-        // Device batching pays where the children are many: one wave per
-        // segment batches them (tens of microseconds for a level), while the
-        // host needs about 5 ns per child. Children too large for a leaf are
-        // listed for the host, which plans only those.
-        if (segs.size() < DEVICE_BATCH_MIN_SEGS || learned) dev_ok = false;
-        for (const Seg& sg : segs)
-            if (sg.wdisp || sg.wdisp_s) dev_ok = false;  // device leaves: one buffer mapping
         uint64_t ch_rows = align_up((total_rows + TARGET_CHUNKS - 1) / TARGET_CHUNKS, PART_TILE);
         if (ch_rows < PART_TILE) ch_rows = PART_TILE;
         if (lines) {
@@ -1108,7 +1115,7 @@ struct Exec {
             }
             if (root) {
                 Plan& pl = plan[0];
-                plan_digit(hdr->hi - hdr->lo, ra.rows, true, pl.shift, pl.bits);
+                plan_digit(hdr->hi - hdr->lo, ra.rows, FULL_DIGIT, pl.shift, pl.bits);
                 pl.kb_out = ra.narrow && pl.shift <= 32 ? 4u : kb_in;
                 for (uint32_t gi = 0; gi < ng; gi++) {
                     groups[gi].base = hdr->lo;
@@ -2345,7 +2352,7 @@ int sampled_range(Exec& x, const void* a, uint64_t na, const void* b, uint64_t n
     // the digit width depends on the span, which depends on the rounded minimum
     for (int it = 0; it < 3; it++) {
         uint32_t shift, bits;
-        plan_digit(hi - lo, na + nb, true, shift, bits);  // as the first pass (one segment)
+        plan_digit(hi - lo, na + nb, FULL_DIGIT, shift, bits);  // as the first pass (one segment)
         const uint64_t aligned = shift >= 64 ? 0 : (mm[0] & ~((1ull << shift) - 1));
         if (aligned == lo) break;
         lo = aligned;
@@ -2371,7 +2378,7 @@ int sample_wants_learned(Exec& x, const void* a, uint64_t na, const void* b, uin
     TJ_CK(hipStreamSynchronize(x.st));
     x.stats.bytes_read += (ma + mb) * (uint64_t)x.sh.kb;
     uint32_t shift, bits;
-    plan_digit(hi - lo, na + nb, true, shift, bits);  // the first pass's digit
+    plan_digit(hi - lo, na + nb, FULL_DIGIT, shift, bits);  // the first pass's digit
     std::vector<uint64_t> cnt((size_t)1 << bits, 0);
     const uint64_t mask = (1ull << bits) - 1;
     uint64_t largest = 0;

@@ -222,26 +222,25 @@ constexpr int PASS_DIGIT_BITS = TJ_PASS_DIGIT_BITS;
 // enough digits that a child averages LEAF_CAP / 2 rows (at least 2, at most a
 // full digit), at the largest shift at which (span >> shift) + 1 digits still
 // reach that many, so a span that is not a power of two still puts them to
-// use. With `few` (a level of at most FEW_SEGS segments) a segment of at most
-// SMALL_SEG_ROWS rows (mostly a bucket crowded by a few frequent keys) takes
-// a full digit: such a level costs about its launches and read-back whatever
-// the width, and the wider digit separates the frequent keys from their
-// neighbours in fewer levels. (A level of many segments keeps the narrower
-// digit: the children's bookkeeping grows with the width.) A span of 0
-// (filtered roots of a single-key range, which still need a compaction pass)
-// gets one bit.
+// use. A segment of at most SMALL_SEG_ROWS rows (mostly a bucket crowded by a
+// few frequent keys) takes at least `least` digits: a full digit in a level of
+// few segments, which costs about its launches and read-back whatever the
+// width, and the wider digit separates the frequent keys from their neighbours
+// in fewer levels; but only FEW_CHILDREN in all in a window of a binding budget,
+// and no more than its rows ask for in a level of over FEW_SEGS segments (the
+// children's bookkeeping grows with the width). A span of 0 (filtered roots of a single-key range, which still need
+// a compaction pass) gets one bit.
 constexpr uint64_t SMALL_SEG_ROWS = 16ull * LEAF_CAP;
-constexpr size_t FEW_SEGS = 64;
+constexpr size_t FEW_SEGS = 64, FEW_CHILDREN = 4096;
+constexpr uint32_t FULL_DIGIT = 1u << PASS_DIGIT_BITS;
 __host__ __device__ inline uint32_t nbits64(uint64_t x) { return x ? 64u - (uint32_t)__builtin_clzll(x) : 0u; }
 
 __host__ __device__ inline uint64_t clamp64(uint64_t x, uint64_t lo, uint64_t hi) { return x < lo ? lo : x > hi ? hi : x; }
 
-__host__ __device__ inline void plan_digit(uint64_t span, uint64_t rows, bool few, uint32_t& shift, uint32_t& bits)
+__host__ __device__ inline void plan_digit(uint64_t span, uint64_t rows, uint32_t least, uint32_t& shift, uint32_t& bits)
 {
-    const uint64_t want =
-        few && rows <= SMALL_SEG_ROWS
-            ? 1ull << PASS_DIGIT_BITS
-            : clamp64((rows + LEAF_CAP / 2 - 1) / (LEAF_CAP / 2), 2, 1ull << PASS_DIGIT_BITS);
+    const uint64_t fit = (rows + LEAF_CAP / 2 - 1) / (LEAF_CAP / 2), small = rows <= SMALL_SEG_ROWS ? least : 0;
+    const uint64_t want = clamp64(fit > small ? fit : small, 2, FULL_DIGIT);
     shift = 0;
     for (uint32_t sh = nbits64(span); sh-- > 0;)
         if ((span >> sh) + 1 >= want) {

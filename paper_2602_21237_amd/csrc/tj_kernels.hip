@@ -636,7 +636,7 @@ __global__ __launch_bounds__(NT) void k_hist(const ChunkDesc* __restrict__ chunk
             hi = root.parts[2 * threadIdx.x + 1];
         }
         block_minmax64<NT>(lo, hi, rtmp);
-        plan_digit(hi - lo, root.rows, true, g.shift, g.bits);
+        plan_digit(hi - lo, root.rows, FULL_DIGIT, g.shift, g.bits);
         g.base = lo;
         if (threadIdx.x == 0 && blockIdx.x == g.chunk0) {  // (no block of this launch uses what another one writes here)
             GroupDesc* w = groups + ch.group;
