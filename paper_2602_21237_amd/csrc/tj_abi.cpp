@@ -209,7 +209,7 @@ const uint64_t kMaxRows = (1ull << 31) - 1;
 // twice with lines: sorts of n int64 rows of D dense keys, runs against lines
 // (us), n 60M: D 64 690 and 840, D 200 740 and 666, D 400 800 and 1760 (lines of
 // 8 bits and a second pass); so such segments take lines for 7 and 8 bits only.
-// (values: the span, or its strides where the sample of a first pass has one;
+// (values: the span, or its strides where the probe of a first pass found one;
 // 500 keys 2^20 apart, 18M int32 rows: 333 us and 567.)
 // Nor does a crowded segment: its rows go to few digits again, or to the three
 // of a pivot, of which lines have no gain, and 512 digits narrow it down in
@@ -560,7 +560,7 @@ struct Exec {
     bool learned_pass = false;      // the next partition pass is the learned one
     bool auto_probe = false;        // the next pass may hand over to the learned partitioner
     bool spec_range = false;        // the next pass's digit range comes from a sampled probe
-    uint32_t spec_stride = 0;       // (log2) few keys, this far apart, by that sample
+    uint32_t root_stride = 0;       // (log2) the probed keys are multiples of this apart (first pass over the input)
     uint64_t exact_lo = 0, exact_hi = 0;  // (after TJ_RANGE_MISS) the range of all keys
     bool root_probe = false;        // the next pass probes its key range and plans its digit on the device
 
@@ -725,7 +725,8 @@ struct Exec {
         learned_pass = false;
         const bool spec = spec_range && !filter && !learned;
         spec_range = false;
-        const uint32_t stride = spec ? spec_stride : 0;
+        const uint32_t stride = filter || learned ? 0 : root_stride;
+        root_stride = 0;
         const bool root = root_probe && !filter && !learned && segs.size() == 1;
         root_probe = false;
         // per segment digit choice
@@ -2292,15 +2293,16 @@ void layout_join_window(Exec& x, char* p, uint64_t data_bytes)
 
 int probe(Exec& x, const void* a, uint64_t na, const void* b, uint64_t nb, uint64_t& lo, uint64_t& hi)
 {
-    uint64_t* mm = (uint64_t*)pinned_down(16);
+    uint64_t* mm = (uint64_t*)pinned_down(24);
     if (!mm) return TJ_E_HIP;
     TJ_CK(x.timed(F_PROBE, (na + nb) * (uint64_t)x.sh.kb,
-                  [&] { return launch_probe(x.sh.kb, a, na, b, nb, x.d_probe, x.st); }));
-    TJ_CK(hipMemcpyAsync(mm, x.d_probe, 16, hipMemcpyDeviceToHost, x.st));
+                  [&] { return launch_probe_step(x.sh.kb, a, na, b, nb, 1, 1, x.d_probe, true, x.st); }));
+    TJ_CK(hipMemcpyAsync(mm, x.d_probe, 24, hipMemcpyDeviceToHost, x.st));
     TJ_CK(hipStreamSynchronize(x.st));
     x.stats.bytes_read += (na + nb) * (uint64_t)x.sh.kb;
     lo = mm[0];
     hi = mm[1];
+    x.root_stride = mm[2] ? (uint32_t)__builtin_ctzll(mm[2]) : 0;
     return TJ_OK;
 }
 
@@ -2340,7 +2342,7 @@ int sampled_range(Exec& x, const void* a, uint64_t na, const void* b, uint64_t n
             const uint64_t below = std::min(spare / 2, lo >> stride);
             lo -= below << stride;
             hi += std::min(spare - below, (last - hi) >> stride) << stride;
-            x.spec_stride = stride;
+            x.root_stride = stride;
             return TJ_OK;
         }
         const uint32_t bits = nbits64(hi - lo);
