@@ -2820,10 +2820,19 @@ static __device__ __noinline__ void join_sorted(__attribute__((address_space(3))
     lds_barrier();
     const uint64_t base = SELF ? 0 : s_base;
     // Pairs are written R item by R item: its b slots are consecutive, and so are
-    // their S items (kv: minus the R item's distance to its run's S part). A wave
-    // writes an item of many slots together, a lane one of few. Both columns leave
-    // in stretches: 2^21 x 2^21 rows of 21000 keys, 32-bit, 209 million pairs in
-    // 1.2 ms, from 3.6 with S items writing their slots b apart.
+    // their S items (kv: minus the R item's distance to its run's S part). A lane
+    // writes an item of few slots, a wave one of many, and these go round the
+    // block's waves through LDS: the R items of one key sit with one wave. Both
+    // columns leave in stretches. 2^21 x 2^21 rows of 21000 keys, 32-bit, 209
+    // million pairs in 1.2 ms, from 3.6 with S items writing their slots b apart;
+    // one block of 490 x 5089 rows of one key: 0.26 ms, from 3.1 with one wave at work.
+    struct Shared { uint32_t e, sb; };  // first slot; first S position << 13 | slots
+    static_assert(NT * 8 <= JL::IDX + JL::CNT && C <= 8192, "sorting is over: its memory is free");
+    Shared* const shared = (Shared*)lds_idx_raw;
+    bool many = false;
+#pragma unroll
+    for (int i = 0; i < KI; i++) many = many || ((abv[i] >> 31) && (abv[i] & 0x3fffu) > COOP_PAIRS);
+    if (threadIdx.x == 0) s_unordered = 0;
     int32_t rid[KI];
 #pragma unroll
     for (int i = 0; i < KI; i++) rid[i] = p0 + i < n ? lds_w[id[i]] : 0;
@@ -2832,7 +2841,9 @@ static __device__ __noinline__ void join_sorted(__attribute__((address_space(3))
 #pragma unroll
     for (int i = 0; i < KI; i++)
         if (p0 + i < n) sid[p0 + i] = rid[i];
+    if (many) s_unordered = 1;
     lds_barrier();
+    const bool some_many = uniform(s_unordered) != 0;
 #pragma unroll
     for (int i = 0; i < KI; i++) {
         const uint32_t b = (abv[i] >> 31) ? abv[i] & 0x3fffu : 0u;
@@ -2848,14 +2859,19 @@ static __device__ __noinline__ void join_sorted(__attribute__((address_space(3))
                 }
             }
         }
-        uint64_t m = ballot(b > COOP_PAIRS);
+        if (!some_many) continue;
+        shared[threadIdx.x] = Shared{e, b > COOP_PAIRS ? s0 << 13 | b : 0u};
+        lds_barrier();
+        const uint32_t from = w + (NT / 64) * l;
+        const Shared it = shared[from];
+        uint64_t m = ballot(it.sb != 0);
         while (m) {
             const int src = __ffsll((unsigned long long)m) - 1;
             m &= m - 1;
-            const uint32_t cb = (uint32_t)__builtin_amdgcn_readlane((int)b, src);
-            const uint32_t cs = (uint32_t)__builtin_amdgcn_readlane((int)s0, src);
-            const uint64_t ce = base + (uint32_t)__builtin_amdgcn_readlane((int)e, src);
-            const int32_t cr = sid[(uint32_t)__builtin_amdgcn_readlane((int)(p0 + i), src)];
+            const uint32_t sb = (uint32_t)__builtin_amdgcn_readlane((int)it.sb, src);
+            const uint32_t cb = sb & 0x1fffu, cs = sb >> 13;
+            const uint64_t ce = base + (uint32_t)__builtin_amdgcn_readlane((int)it.e, src);
+            const int32_t cr = sid[(uint32_t)__builtin_amdgcn_readlane((int)from, src) * KI + i];
 #pragma unroll 1
             for (uint32_t j = l; j < cb; j += 64) {
                 if (ce + j < capacity) {
@@ -2864,6 +2880,7 @@ static __device__ __noinline__ void join_sorted(__attribute__((address_space(3))
                 }
             }
         }
+        lds_barrier();
     }
 }
 
