@@ -227,7 +227,7 @@ typedef struct {
  * level narrows the digit to its bucket's key range, which splits a few dense
  * intervals at the next level but not a heavy tail), and the call trains the
  * learned model and partitions with it; otherwise it runs radix. Calls of at
- * least 2^22 rows with the full workspace count every 4096th key (the sample
+ * least 2^22 rows with the full workspace count every 4093rd key (the sample
  * their first digit range is taken from, read back to the host); smaller ones
  * count the first pass's histogram, before anything is moved.
  */
@@ -463,13 +463,13 @@ int tj_server_destroy(tj_server_t *server);
  * for a join, est_output >= min_output (TJ_SEL_OUTPUT); otherwise
  * TJ_PATH_LINEAR. Options (may be NULL): a zero field takes its default,
  * TJ_SELECT_DEFAULT_MIN_ROWS and TJ_SELECT_DEFAULT_MIN_OUTPUT. The paper
- * leaves the thresholds open; the defaults come from a measured crossover on
- * one MI355X against a single-core CPU hash join and std::sort (built -O3
- * -march=native, inputs in host memory): over FK joins of 2^8 ... 2^22 rows per
- * side, the tensor path's join (device inputs, wall time of the call) is
- * faster from about 1,300 rows per side (scale 2,600, about 1,050 output
- * pairs) and its sort from about 1,760 rows, below which its fixed cost of
- * roughly 0.06-0.25 ms per call dominates.
+ * leaves the thresholds open; the defaults are conservative for what was
+ * measured on one MI355X against a single-core CPU hash join and std::sort
+ * (built -O3 -march=native, inputs in host memory): over FK joins of 2^8 ...
+ * 2^22 rows per side, the tensor path's join (device inputs, wall time of the
+ * call) is faster from about 310 rows per side (scale 620, about 250 output
+ * pairs) and its sort from about 1,220 rows, below which its fixed cost of
+ * roughly 0.03-0.06 ms per call dominates.
  *
  *   op: TJ_OP_SORT (s_keys ignored, n_s must be 0) or a join op;
  *   r_keys[n_r], s_keys[n_s]: device key columns of key_type;
